@@ -7,10 +7,9 @@
 // Population storage is structure-of-arrays: plane i (velocity i) holds the
 // cells row by row, x fastest, rows `pitch` elements apart (pitch is a
 // multiple of 64 elements, so every row starts on a 256-byte boundary for
-// 4-byte storage).  Three state buffers rotate: the state entering step t
-// (f^new of step t-1) lives in buffer t mod 3, so a launch that advances one
-// step (t -> t+1) or two steps (t -> t+2) always writes a buffer it does not
-// read.
+// 4-byte storage).  Two state buffers alternate: a launch reads the buffer
+// the previous one wrote and writes the other, however many steps it advances
+// (the device counter holds the index of the current one).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -139,10 +138,12 @@ struct AccDev {
     int32_t pad;
 };
 
-constexpr int kNumBuf = 3;   // state buffers, indexed by step mod 3
+// State buffers, read and written in turn by successive launches.  Two, not three indexed by the
+// step: one FP32 sphere of 256 x 128 x 128 (117 MB a buffer) stays inside the 256 MB memory-side
+// cache and takes 24.5 us a step, 29.0 with three.
+constexpr int kNumBuf = 2;
 constexpr int kNumSlot = 4;  // moment boxes and partial sums, indexed by step mod 4
 
-__host__ __device__ inline int buf_of(int64_t t) { return (int)(t % kNumBuf); }
 __host__ __device__ inline int slot_of(int64_t t) { return (int)(t & (kNumSlot - 1)); }
 
 struct InstDev {
@@ -200,20 +201,20 @@ struct SegInfo {
 //    accumulate.
 // Every stage reads what an earlier launch wrote, and the slots written and
 // read by one launch differ mod 4, so no stage waits on another inside a
-// launch.  The lattice step of a launch is t = *tp + dt: the counter lives
-// in device memory so that a captured sequence of launches can be replayed
-// at any t.
+// launch.  The lattice step of a launch is t = tp[0] + dt and the buffer it reads
+// (tp[1] + dbuf) mod 2: the counter lives in device memory so that a captured
+// sequence of launches can be replayed at any t and from either buffer.
 struct StepArgs {
     const InstDev *inst;
-    const int64_t *tp;        // device step counter: {t, t mod 3}
-    int32_t dt;               // offset of this launch from *tp
+    const int64_t *tp;        // device step counter: {t, index of the current state buffer}
+    int32_t dt;               // step offset of this launch from tp[0]
+    int32_t dbuf;             // launches since tp[1] was set, mod 2
     int32_t meas_off, n_ms;   // surface stage measures t - meas_off + j, j < n_ms
     int32_t red_off, n_rs;    // reducer stage reduces t - red_off + j, j < n_rs
     int32_t nseg;
     int32_t ntask;            // lattice tasks (one-step launch) or blocks (two-step launch)
     int32_t n_red, n_sb;      // reducer blocks; surface blocks per measured step
     int32_t zchunk;           // planes per row-group chunk (two-step launch)
-    int32_t pad;
     SegInfo seg[kMaxSeg];
     const int32_t *sb_inst;   // per surface block: internal instance
     const int32_t *sb_chunk;  // per surface block: chunk of 64 elements
@@ -320,7 +321,7 @@ __device__ inline void lattice_task(const StepArgs &a, const int64_t t, const in
     const C phi = (C)I.wall_phi;
     const double src_amp = I.src_amp, omega = I.omega;
     const gptr<const R> src = to_global<R>(static_cast<const void *>(I.buf[bsrc]));
-    const gptr<R> dst = to_global<R>(I.buf[bsrc == kNumBuf - 1 ? 0 : bsrc + 1]);
+    const gptr<R> dst = to_global<R>(I.buf[bsrc ^ 1]);
 
     const int ym = (y == 0) ? ny - 1 : y - 1;
     const int yp = (y == ny - 1) ? 0 : y + 1;
@@ -561,7 +562,7 @@ __device__ inline void lattice2_block(const StepArgs &a, const int64_t t, const 
         rs_b = (C)(I.src_amp * sin(I.omega * (double)(t + 1)));
     }
     const gptr<const E> src = to_global<E>(static_cast<const void *>(I.buf[bsrc]));
-    const gptr<E> dst = to_global<E>(I.buf[bsrc == 0 ? 2 : bsrc - 1]);  // buffer (t + 2) mod 3
+    const gptr<E> dst = to_global<E>(I.buf[bsrc ^ 1]);
     const uint32_t ux = (uint32_t)x;
 
     // step-t values of plane p - 1, pull-ready for step t + 1 (owned rows)
@@ -889,7 +890,7 @@ __global__ void __launch_bounds__(kStepThreads) step_kernel(StepArgs a)
     const int64_t t = a.tp[0] + a.dt;
     const int b = blockIdx.x;
     if (measure_part<DIM, typename StoreTraits<S>::C>(a, t, b, lds)) return;
-    const int bsrc = ((int)a.tp[1] + a.dt) % kNumBuf;  // t mod 3 without 64-bit division
+    const int bsrc = ((int)a.tp[1] + a.dbuf) & 1;
     const int wave = wave_uniform(threadIdx.x >> 6);
     const int task = (b - a.n_red - a.n_ms * a.n_sb) * (kStepThreads / 64) + wave;
     if (task >= a.ntask) return;
@@ -918,22 +919,20 @@ __global__ void __launch_bounds__(kStepThreads, PF ? 2 : 4) step2_kernel(StepArg
     const int b = blockIdx.x;
     // the long lattice blocks first, the short measurement blocks fill the tail
     if (b < a.ntask) {
-        lattice2_block<S, R, NT, PF>(a, t, ((int)a.tp[1] + a.dt) % kNumBuf, xcd_block(b, a.ntask),
-                                     xe);
+        lattice2_block<S, R, NT, PF>(a, t, ((int)a.tp[1] + a.dbuf) & 1, xcd_block(b, a.ntask), xe);
         return;
     }
     measure_part<3, C>(a, t, b - a.ntask, lds);
 }
 
-// Device step counter: set, or advance after a replayed sequence.
-// The counter holds {t, t mod 3} (the phase saves the kernels a 64-bit division).
 // Point source (the paper's oscillating point source): after the lattice
 // step t, the source node of every instance that has one takes
 // f^eq(rho_a sin(omega t), J1) from its own pre-collision populations, as the
 // source sheet does; x, y and z are periodic.  One thread per instance, in
 // stream order after the step's lattice launch and before the next one.
 template <int DIM, typename S>
-__global__ void point_source_kernel(const InstDev *inst, int n_inst, const int64_t *tp, int32_t dt)
+__global__ void point_source_kernel(const InstDev *inst, int n_inst, const int64_t *tp, int32_t dt,
+                                    int32_t dbuf)
 {
     using T = StoreTraits<S>;
     using R = typename T::R;
@@ -944,9 +943,9 @@ __global__ void point_source_kernel(const InstDev *inst, int n_inst, const int64
     const InstDev &I = inst[k];
     const int64_t t = tp[0] + dt;
     if (!I.src_point || (I.max_steps > 0 && t >= I.max_steps)) return;
-    const int bsrc = ((int)tp[1] + dt) % kNumBuf;
+    const int bsrc = ((int)tp[1] + dbuf) & 1;
     const R *src = static_cast<const R *>(I.buf[bsrc]);
-    R *dst = static_cast<R *>(I.buf[bsrc == kNumBuf - 1 ? 0 : bsrc + 1]);
+    R *dst = static_cast<R *>(I.buf[bsrc ^ 1]);
     const int x = I.src_pt[0], y = I.src_pt[1], z = I.src_pt[2];
     auto at = [&](int i, int xx, int yy, int zz) {
         xx = xx < 0 ? xx + I.nx : (xx >= I.nx ? xx - I.nx : xx);
@@ -1000,18 +999,20 @@ __global__ void probe_rho_kernel(const void *buf, int64_t plane, int Q, int nx, 
     out[i] = s / scale;
 }
 
-__global__ void set_step_kernel(int64_t *tp, int64_t v)
+// Device counter {t, index of the current state buffer}: set, or advanced by k steps in
+// n_launch launches after a replayed sequence.
+__global__ void set_step_kernel(int64_t *tp, int64_t t, int64_t buf)
 {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        tp[0] = v;
-        tp[1] = v % kNumBuf;
+        tp[0] = t;
+        tp[1] = buf;
     }
 }
-__global__ void advance_step_kernel(int64_t *tp, int64_t k)
+__global__ void advance_step_kernel(int64_t *tp, int64_t k, int64_t n_launch)
 {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         tp[0] = tp[0] + k;
-        tp[1] = (tp[1] + k) % kNumBuf;
+        tp[1] = (tp[1] + n_launch) & 1;
     }
 }
 

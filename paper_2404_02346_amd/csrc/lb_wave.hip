@@ -456,8 +456,11 @@ struct lb_wave {
     int64_t meas = 0;                 // steps whose chunk partials exist
     int64_t red = 0;                  // steps reduced into the accumulators
     bool nan_seen = false;
-    int64_t *d_t = nullptr;           // device step counter {t, t mod 3}
-    int64_t tdev = 0;                 // its value in stream order
+    int cur = 0;                      // state buffer holding the state after step t - 1
+    std::vector<int> stop_buf;        // internal order: that buffer when the instance stopped
+    int64_t *d_t = nullptr;           // device counter {t, index of the current state buffer}
+    int64_t tdev = 0;                 // its values in stream order
+    int bufdev = 0;
     int graph_chunk = 0;              // replay steady steps as captured graphs of this length
     hipStream_t cap_stream = nullptr; // private stream used only for capture
     struct GraphEntry {
@@ -474,10 +477,11 @@ struct lb_wave {
 
 namespace {
 
-int64_t steps_of(const lb_wave *h, int internal)
+// the buffer that holds the current state of an instance
+int state_buf(const lb_wave *h, int internal)
 {
     const int64_t ms = h->hinst[internal].max_steps;
-    return ms > 0 ? std::min(h->t, ms) : h->t;
+    return ms > 0 && h->t >= ms ? h->stop_buf[internal] : h->cur;
 }
 
 int active_prefix(const lb_wave *h, int64_t t)
@@ -557,7 +561,7 @@ template <int DIM, typename S>
 void launch_point_s(const lb_wave *h, const StepArgs &a, hipStream_t st)
 {
     hipLaunchKernelGGL((point_source_kernel<DIM, S>), dim3((h->n + 63) / 64), dim3(64), 0, st,
-                       a.inst, h->n, a.tp, a.dt);
+                       a.inst, h->n, a.tp, a.dt, a.dbuf);
 }
 void launch_point(const lb_wave *h, const StepArgs &a, hipStream_t st)
 {
@@ -646,13 +650,15 @@ void plan_measure(lb_wave *h, StepArgs &a, int64_t t_launch)
 // live prefix) and launch, one launch per kMaxSeg segments; the measurement
 // blocks ride on the first launch.  nst = 1: wave tasks of step_kernel;
 // nst = 2: blocks of step2_kernel (the live prefix is the same for both steps).
-void emit_step(const lb_wave *h, StepArgs a, int64_t t, int32_t dt, int nst, hipStream_t st)
+void emit_step(const lb_wave *h, StepArgs a, int64_t t, int32_t dt, int dbuf, int nst,
+               hipStream_t st)
 {
     const int na = active_prefix(h, t);
     const bool two = nst == 2;
     auto first_of = [&](const SegInfo &sg) { return two ? sg.blk0 : sg.task0; };
     const int n_active = two ? h->blk0[na] : h->task0[na];
     a.dt = dt;
+    a.dbuf = dbuf;
     a.zchunk = h->zchunk;
     size_t s = 0;
     bool first = true;
@@ -680,13 +686,29 @@ void emit_step(const lb_wave *h, StepArgs a, int64_t t, int32_t dt, int nst, hip
     if (h->any_point && !two) launch_point(h, a, st);
 }
 
-// Make the device counter equal `t` in stream order if dt would not fit.
-void sync_counter(lb_wave *h, int64_t t)
+// Set the device counter to the handle's step and buffer, in stream order.
+void set_counter(lb_wave *h)
 {
-    if (t - h->tdev > (1 << 30) || t < h->tdev) {
-        hipLaunchKernelGGL(set_step_kernel, dim3(1), dim3(64), 0, h->stream, h->d_t, t);
-        h->tdev = t;
-    }
+    hipLaunchKernelGGL(set_step_kernel, dim3(1), dim3(64), 0, h->stream, h->d_t, h->t,
+                       (int64_t)h->cur);
+    h->tdev = h->t;
+    h->bufdev = h->cur;
+}
+
+// ... if dt would not fit
+void sync_counter(lb_wave *h)
+{
+    if (h->t - h->tdev > (1 << 30) || h->t < h->tdev) set_counter(h);
+}
+
+// k steps in n_launch launches are enqueued: advance the host's counters, and note
+// where the state of every instance that has just stopped lies.
+void advance(lb_wave *h, int64_t k, int n_launch)
+{
+    const int live = active_prefix(h, h->t);
+    h->t += k;
+    h->cur = (h->cur + n_launch) & 1;
+    for (int ii = active_prefix(h, h->t); ii < live; ++ii) h->stop_buf[ii] = h->cur;
 }
 
 // nst lattice steps (1 or 2) for every live instance, with the measurement
@@ -694,15 +716,15 @@ void sync_counter(lb_wave *h, int64_t t)
 int enqueue_step(lb_wave *h, int nst)
 {
     const int64_t t = h->t;
-    sync_counter(h, t);
+    sync_counter(h);
     StepArgs a;
     std::memset(&a, 0, sizeof a);
     a.inst = h->d_inst;
     a.tp = h->d_t;
     plan_measure(h, a, t);
-    emit_step(h, a, t, (int32_t)(t - h->tdev), nst, h->stream);
+    emit_step(h, a, t, (int32_t)(t - h->tdev), h->cur ^ h->bufdev, nst, h->stream);
     HIP_TRY(hipGetLastError());
-    h->t += nst;
+    advance(h, nst, 1);
     return LB_OK;
 }
 
@@ -716,7 +738,7 @@ bool can_fuse(const lb_wave *h)
 int flush_measure(lb_wave *h)
 {
     while (h->red < h->t) {
-        sync_counter(h, h->t);
+        sync_counter(h);
         StepArgs a;
         std::memset(&a, 0, sizeof a);
         a.inst = h->d_inst;
@@ -773,9 +795,9 @@ int replay_steps(lb_wave *h, int k)
         a.n_sb = n_sb;
         a.sb_inst = h->d_sb_inst;
         a.sb_chunk = h->d_sb_chunk;
-        for (int j = 0; j < k; j += nst) emit_step(h, a, t + j, j, nst, h->cap_stream);
+        for (int j = 0; j < k; j += nst) emit_step(h, a, t + j, j, (j / nst) & 1, nst, h->cap_stream);
         hipLaunchKernelGGL(advance_step_kernel, dim3(1), dim3(64), 0, h->cap_stream, h->d_t,
-                           (int64_t)k);
+                           (int64_t)k, (int64_t)(k / nst));
         hipGraph_t graph = nullptr;
         hipError_t e = hipStreamEndCapture(h->cap_stream, &graph);
         if (e != hipSuccess) return fail(LB_EDEVICE, "graph capture: %s", hipGetErrorString(e));
@@ -784,13 +806,11 @@ int replay_steps(lb_wave *h, int k)
         if (e != hipSuccess) return fail(LB_EDEVICE, "graph instantiate: %s", hipGetErrorString(e));
         h->graphs.push_back({k, na, n_red, n_sb, nst, exec});
     }
-    if (h->tdev != t) {
-        hipLaunchKernelGGL(set_step_kernel, dim3(1), dim3(64), 0, h->stream, h->d_t, t);
-        h->tdev = t;
-    }
+    if (h->tdev != t || h->bufdev != h->cur) set_counter(h);
     HIP_TRY(hipGraphLaunch(exec, h->stream));
-    h->t += k;
-    h->tdev += k;
+    advance(h, k, k / nst);
+    h->tdev = h->t;
+    h->bufdev = h->cur;
     if (h->any_surf) {
         h->meas += k;
         h->red += k;
@@ -833,9 +853,9 @@ int zero_state(lb_wave *h)
     int st = zero_region(h, h->lay.off_acc, sizeof(AccDev) * h->n);
     if (st) return st;
     h->t = h->meas = h->red = 0;
+    h->cur = 0;
     h->nan_seen = false;
-    hipLaunchKernelGGL(set_step_kernel, dim3(1), dim3(64), 0, h->stream, h->d_t, (int64_t)0);
-    h->tdev = 0;
+    set_counter(h);
     return LB_OK;
 }
 
@@ -920,6 +940,7 @@ int lb_wave_create(const lb_wave_desc *descs, int32_t n_inst, void *dev_workspac
     h->hinst.resize(n_inst);
     h->scale.resize(n_inst);
     h->task0.assign(n_inst + 1, 0);
+    h->stop_buf.assign(n_inst, 0);
     for (int ii = 0; ii < n_inst; ++ii) {
         const int u = h->order[ii];
         const lb_wave_desc &d = descs[u];
@@ -1209,7 +1230,7 @@ int lb_wave_state_view(const lb_wave *h, int32_t inst, lb_state_view *v)
     if (inst < 0 || inst >= h->n) return fail(LB_EINVAL, "instance out of range");
     const int ii = h->pos[inst];
     const InstPlan &P = h->lay.p[inst];
-    v->offset_bytes = P.off_buf[buf_of(steps_of(h, ii))];
+    v->offset_bytes = P.off_buf[state_buf(h, ii)];
     v->plane_bytes = elem_bytes(h->storage) * (size_t)P.plane;
     v->pitch = P.pitch;
     v->elem_bytes = (int32_t)elem_bytes(h->storage);
@@ -1292,7 +1313,7 @@ int lb_wave_probe_rho(lb_wave *h, int32_t inst, const int64_t *dev_cells, int32_
     const int ii = h->pos[inst];
     const InstPlan &P = h->lay.p[inst];
     const lb_wave_desc &d = h->desc[inst];
-    const void *buf = h->ws + P.off_buf[buf_of(steps_of(h, ii))];
+    const void *buf = h->ws + P.off_buf[state_buf(h, ii)];
     const int64_t ncell = (int64_t)d.nx * d.ny * (d.dim == 3 ? d.nz : 1);
     const int Q = 2 * d.dim + 1;
     const dim3 grid((unsigned)((n_cells + 255) / 256)), blk(256);
