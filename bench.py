@@ -115,8 +115,7 @@ def get_variant(h):
 
 def kernel_name(storage, v):
     if v[3] == 2:
-        return "step2_kernel<{},rows={},nt={}>".format(storage, 4 if storage == "f32" else 2,
-                                                       min(v[2], 1))
+        return "march_kernel<{},nt={}>".format(storage, min(v[2], 1))
     return "step_kernel<3,{},{},{},{}>".format(storage, *v[:3])
 
 
@@ -472,12 +471,12 @@ def main():
     else:
         tune_ms = h.autotune(6)
     variant = get_variant(h)
-    spl = variant[3]
+    spl = h.launch_steps()
     h.set_graph(args.graph)
     h.step(args.warmup)
     if args.graph > 0 and args.steps > 2 * args.graph:
         # the replayed step sequence is captured and instantiated before the clock starts
-        h.step(2 * args.graph + 2)
+        h.step(2 * args.graph + 6)
     h.reset()  # the timed steps start the run from rest
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     torch.cuda.synchronize()
@@ -513,7 +512,7 @@ def main():
     g.close()
     del g
     # algorithmic HBM bytes of one launch: the state read once and written
-    # once (2 Q s per cell), whether the launch advances one step or two
+    # once (2 Q s per cell), however many steps the launch advances
     bytes_per_launch = 2 * Q * s * cells
     achieved = bytes_per_launch / (launch_ms * 1e-3) / 1e9
     traffic = measured_traffic(args.storage, variant)

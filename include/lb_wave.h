@@ -214,8 +214,8 @@ int lb_wave_state_view(const lb_wave *h, int32_t inst, lb_state_view *v);
  *   nontemporal 0: plain loads and stores, 1: non-temporal stores,
  *     2: non-temporal loads and stores.
  * Every variant computes bit-identical results.  lb_wave_autotune times every
- * valid variant, and two steps per launch where allowed, for n_trial steps
- * (rounded up to even) on the handle's own instances, keeps the fastest,
+ * valid variant, and several steps per launch where allowed, for n_trial steps
+ * (rounded up to whole launches) on the handle's own instances, keeps the fastest,
  * then resets the state (lb_wave_reset); best_ms (may be NULL) receives the
  * winning time per step in ms.  set_tile/get_tile change or read
  * cells_per_lane only. */
@@ -226,18 +226,21 @@ int lb_wave_set_tile(lb_wave *h, int32_t cells_per_lane);
 int lb_wave_get_tile(const lb_wave *h, int32_t *cells_per_lane);
 int lb_wave_autotune(lb_wave *h, int32_t n_trial, double *best_ms);
 
-/* Lattice steps per launch: 1 (step_kernel, the default) or 2 (a fused
- * kernel that advances t -> t + 2 with step t's values held on chip, reading
- * and writing the state about once per two steps).  Two steps per launch
- * need every instance 3D with driven x sheets and ny a multiple of the row
- * block, R * 4 / nw rows (R = 4 rows per row group for FP32 and 2 for the
- * other storage types; nw = pitch / 64 wavefronts cover a row up to 256
- * cells; longer rows run in strips of 254 cells, nw = 4); otherwise
- * LB_EINVAL.  Results are bit-identical either way; steps where an instance stops, and odd
- * remainders, run one at a time.  lb_wave_autotune also tries two steps per
- * launch when allowed. */
+/* Lattice steps per launch: 1 (step_kernel, the default) or 2, meaning
+ * several: a fused kernel that advances t -> t + k with the values of the
+ * steps in between held on chip, reading and writing the state about once per
+ * k steps (k = 3, or 2 for FP64 storage; lb_wave_get_launch_steps).  It needs
+ * every instance 3D with driven x sheets and ny a multiple of R * 4 / nw rows
+ * (R = 4 for FP32 and 2 for the other storage types; nw = pitch / 64
+ * wavefronts cover a row up to 256 cells, nw = 4 for longer rows); otherwise
+ * LB_EINVAL.  Results are bit-identical either way; launches are shorter where
+ * an instance stops and for remainders.  lb_wave_autotune also tries several
+ * steps per launch when allowed. */
 int lb_wave_set_steps_per_launch(lb_wave *h, int32_t k);
 int lb_wave_get_steps_per_launch(const lb_wave *h, int32_t *k);
+
+/* Lattice steps that one launch of this handle advances in a long run. */
+int lb_wave_get_launch_steps(const lb_wave *h, int32_t *k);
 
 /* Replay steady steps as captured HIP graphs of `chunk` steps (0 = off,
  * otherwise 2..4096).  A sequence is captured once per launch shape and

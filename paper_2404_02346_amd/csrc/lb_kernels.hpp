@@ -14,6 +14,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace lbw {
 
@@ -43,7 +44,13 @@ template <> struct StoreTraits<_Float16> {
     using R = _Float16;
     using C = float;
     __device__ static inline C to_c(R v) { return (float)v; }
-    __device__ static inline R to_r(C v) { return (_Float16)v; }
+    __device__ static inline R to_r(C v)
+    {
+        // kept apart from the FP32 operation that made v: as one instruction (a multiply-add
+        // with an FP16 result) they would round once instead of twice, in some kernels only
+        asm("" : "+v"(v));
+        return (_Float16)v;
+    }
 };
 template <> struct StoreTraits<bf16> {
     using R = uint16_t;
@@ -142,7 +149,7 @@ struct AccDev {
 // step: one FP32 sphere of 256 x 128 x 128 (117 MB a buffer) stays inside the 256 MB memory-side
 // cache and takes 24.5 us a step, 29.0 with three.
 constexpr int kNumBuf = 2;
-constexpr int kNumSlot = 4;  // moment boxes and partial sums, indexed by step mod 4
+constexpr int kNumSlot = 8;  // moment boxes and partial sums, indexed by step mod 8
 
 __host__ __device__ inline int slot_of(int64_t t) { return (int)(t & (kNumSlot - 1)); }
 
@@ -163,10 +170,10 @@ struct InstDev {
     // measurement
     int32_t mb_lo[3];        // moment box origin (cells whose rho, J the surface reads)
     int32_t mb_n[3];         // moment box extent (0 -> no measurement)
-    void *mom[kNumSlot];     // moment boxes (rho, Jx, Jy, Jz per cell, compute type) by step mod 4
+    void *mom[kNumSlot];     // moment boxes (rho, Jx, Jy, Jz per cell, compute type) by step mod 8
     int32_t n_surf, n_chunks;  // surface elements, 64-element chunks
     const SurfPt *surf;
-    double *part;            // 4 x n_chunks x 4 per-chunk flux sums by step mod 4
+    double *part;            // 8 x n_chunks x 4 per-chunk flux sums by step mod 8
     double c0sq_force;       // c0^2 in the surface integral
     double force_scale;      // -1 / (rho0 * scale^2)
     int64_t avg_start;
@@ -182,17 +189,17 @@ struct SegInfo {
     int32_t xsegs;      // wave tasks per row
     int32_t tpi;        // wave tasks per instance
     int32_t pad;
-    int32_t blk0;       // first block of the run (two-step launch)
-    int32_t bpi;        // blocks per instance (two-step launch)
-    int32_t nyb;        // row blocks per instance (two-step launch)
-    int32_t nsx;        // x strips per row (two-step launch; 1: the row fits one block)
+    int32_t blk0;       // first block of the run (march launch)
+    int32_t bpi;        // blocks per instance (march launch)
+    int32_t nyb;        // row blocks per instance (march launch)
+    int32_t nsx;        // x strips per row (march launch; 1: the row fits one block)
 };
 
 // One launch = [reducer blocks][surface blocks][lattice blocks] (the
-// two-step kernel puts its lattice blocks first), a three-stage pipeline
+// march kernel puts its lattice blocks first), a three-stage pipeline
 // over consecutive steps:
-//  * lattice blocks advance steps t .. t+nst-1 (nst = 1 or 2) and store
-//    rho1, J1 of each f(s) in the moment box of slot s mod 4;
+//  * lattice blocks advance steps t .. t+nst-1 (nst = 1 to 3) and store
+//    rho1, J1 of each f(s) in the moment box of slot s mod 8;
 //  * surface blocks interpolate F(s) for the n_ms steps s = t - meas_off ..
 //    that earlier launches advanced, from their moment boxes, and write one
 //    partial sum per 64 elements into slot s mod 4;
@@ -200,7 +207,7 @@ struct SegInfo {
 //    step order, one block per instance) in a fixed order, scale, trace and
 //    accumulate.
 // Every stage reads what an earlier launch wrote, and the slots written and
-// read by one launch differ mod 4, so no stage waits on another inside a
+// read by one launch differ mod 8, so no stage waits on another inside a
 // launch.  The lattice step of a launch is t = tp[0] + dt and the buffer it reads
 // (tp[1] + dbuf) mod 2: the counter lives in device memory so that a captured
 // sequence of launches can be replayed at any t and from either buffer.
@@ -212,9 +219,8 @@ struct StepArgs {
     int32_t meas_off, n_ms;   // surface stage measures t - meas_off + j, j < n_ms
     int32_t red_off, n_rs;    // reducer stage reduces t - red_off + j, j < n_rs
     int32_t nseg;
-    int32_t ntask;            // lattice tasks (one-step launch) or blocks (two-step launch)
+    int32_t ntask;            // lattice tasks (one-step launch) or blocks (march launch)
     int32_t n_red, n_sb;      // reducer blocks; surface blocks per measured step
-    int32_t zchunk;           // planes per row-group chunk (two-step launch)
     SegInfo seg[kMaxSeg];
     const int32_t *sb_inst;   // per surface block: internal instance
     const int32_t *sb_chunk;  // per surface block: chunk of 64 elements
@@ -239,6 +245,11 @@ __device__ inline int wave_uniform(int v) { return __builtin_amdgcn_readfirstlan
 //   f^new_0    = 2 (1 - dim c^2) rho - f_0,
 // with c = c(x) the local sound speed.
 // ---------------------------------------------------------------------------
+// The multiply-adds are written out: left to the compiler, whether c^2 rho - f is one fused
+// operation or two depends on the code around it, and every kernel has to give the same bits.
+__device__ inline float mul_add(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ inline double mul_add(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 // imposed density rs with the cell's own momentum (eq. imposingfields):
 // f^eq(rs, J) of the pre-collision populations f
 template <int DIM, typename C>
@@ -246,12 +257,37 @@ __device__ inline void impose_rule(const C *f, C c2, C rs, C *out)
 {
     constexpr int Q = 2 * DIM + 1;
     const C h = (C)0.5;
-    out[0] = rs * ((C)1 - (C)DIM * c2);
+    out[0] = rs * mul_add(-(C)DIM, c2, (C)1);
 #pragma unroll
     for (int i = 1; i < Q; i += 2) {
         const C Ja = f[i] - f[i + 1];
-        out[i] = h * (c2 * rs + Ja);
-        out[i + 1] = h * (c2 * rs - Ja);
+        out[i] = h * mul_add(c2, rs, Ja);
+        out[i + 1] = h * mul_add(c2, rs, -Ja);
+    }
+}
+
+// collision away from the sheets
+template <int DIM, typename C>
+__device__ inline void bulk_rule(const C *f, C rho, C c2, C *out)
+{
+    constexpr int Q = 2 * DIM + 1;
+    out[0] = mul_add((C)2 * mul_add(-(C)DIM, c2, (C)1), rho, -f[0]);
+#pragma unroll
+    for (int i = 1; i < Q; i += 2) {
+        out[i] = mul_add(c2, rho, -f[i + 1]);
+        out[i + 1] = mul_add(c2, rho, -f[i]);
+    }
+}
+
+// damped bounce-back of the pre-collision populations (eq. bounce-back)
+template <int DIM, typename C> __device__ inline void wall_rule(const C *f, C phi, C *out)
+{
+    constexpr int Q = 2 * DIM + 1;
+    out[0] = phi * f[0];
+#pragma unroll
+    for (int i = 1; i < Q; i += 2) {
+        out[i] = phi * f[i + 1];
+        out[i + 1] = phi * f[i];
     }
 }
 
@@ -259,26 +295,12 @@ template <int DIM, typename C>
 __device__ inline void cell_rule(const C *f, C rho, C c2, int x, int nx, bool driven, C phi, C rs,
                                  C *out)
 {
-    constexpr int Q = 2 * DIM + 1;
-    if (driven && (x == 0 || x == nx - 1)) {
-        // damped bounce-back of the pre-collision populations (eq. bounce-back)
-        out[0] = phi * f[0];
-#pragma unroll
-        for (int i = 1; i < Q; i += 2) {
-            out[i] = phi * f[i + 1];
-            out[i + 1] = phi * f[i];
-        }
-    } else if (driven && x == 1) {
+    if (driven && (x == 0 || x == nx - 1))
+        wall_rule<DIM, C>(f, phi, out);
+    else if (driven && x == 1)
         impose_rule<DIM, C>(f, c2, rs, out);
-    } else {
-        const C c2rho = c2 * rho;
-        out[0] = (C)2 * ((C)1 - (C)DIM * c2) * rho - f[0];
-#pragma unroll
-        for (int i = 1; i < Q; i += 2) {
-            out[i] = c2rho - f[i + 1];
-            out[i + 1] = c2rho - f[i];
-        }
-    }
+    else
+        bulk_rule<DIM, C>(f, rho, c2, out);
 }
 
 template <int DIM, typename S, int CPL, int XM, int NT>
@@ -459,38 +481,109 @@ __device__ inline void lattice_task(const StepArgs &a, const int64_t t, const in
 }
 
 // ---------------------------------------------------------------------------
-// Two steps per launch (t -> t + 2; D3Q7, driven x sheets, rows of at most
-// 256 cells).  A block covers whole rows: wavefront w moves the cells
-// x = 64 (w % nw) + lane of row group w / nw, with nw = pitch / 64
-// wavefronts per row and 4 / nw row groups (with nw = 3 the fourth
-// wavefront idles but keeps the barriers).  A row group owns R consecutive
-// rows and a chunk of up to zchunk planes (chosen per handle: 64 with 4-row
-// groups, 32 with 2-row groups, or less when so few blocks would leave the
-// chip idle).  It marches through
-// the planes: for plane p it advances step t on its rows plus one halo row
-// on each side (of those only the population moving into the owned rows is
-// kept) and holds the post-collision values in registers; then it finishes
-// step t + 1 on plane p - 1, whose seven incoming populations are now all
-// known: the +x / -x ones shifted across lanes (across wavefronts through
-// LDS), +y / -y from the neighbouring rows, +z / -z from planes p - 2 and p.  Per two
-// steps each plane is read about (R + 2) / R times (the halo rows, and the
-// halo planes at the chunk ends, are read twice) and written once, against
-// two reads and two writes for two one-step launches.
+// Several steps per launch (t -> t + K; D3Q7, driven x sheets).  A block of
+// W wavefronts (4 or 8) owns R rows per row group and a chunk of up to zchunk
+// planes (chosen per handle): wavefront w moves the cells x = 64 (w % nw) + lane of row group
+// w / nw, with nw = pitch / 64 wavefronts per row and W / nw row groups (with
+// nw = 3 one or two wavefronts only help to copy).  It marches
+// through the planes; in iteration i level 1 (step t) is computed on plane i,
+// level 2 (step t + 1) on plane i - 1, .. level K on plane i - K + 1, which
+// is stored.  Level s covers K - s halo rows on each side of the owned rows
+// and K - s halo planes at the chunk ends, so no block waits for another.
+// What a level hands to the next stays in registers, ready to be pulled: a
+// row's rest, +-x and +-y values of one plane and its +z value of the plane
+// before; -z comes straight from the row just computed (the levels of one row
+// are computed one after the other, so no plane is held twice).  The +-x
+// values are shifted across lanes, and across wavefronts through LDS.
+//
+// The populations of plane i + 1 are copied from memory into LDS (16 bytes a
+// lane, without passing through registers) while plane i is computed, and
+// read from there once: neighbouring row groups of a block share their halo
+// rows, and a wavefront has a plane's loads in flight without holding
+// registers for them.
+//
+// What bounds it: in FP32 and FP64 the traffic behind the L2, 2 Q s bytes per
+// cell in K steps plus the halo rows that miss the L2 (16 spheres of 256 x 128 x
+// 128 in FP32, blocks of four wavefronts: 3.0 GB read and 1.9 GB written per
+// launch of three steps against 1.9 and 1.9, at 5.8 TB/s; a copy reaches 6.2);
+// in 16-bit storage the instructions of a plane.  Measured against the kernel
+// before it (two steps, every load through registers), us per step: those 16
+// spheres FP32 384 -> 268, FP16 244 -> 181, one sphere 24.5 -> 20, 16 uneven
+// boxes of 64 to 192 cells a side 307 -> 184, four channels of 1000 x 64 x 64
+// 123 -> 82, four spheres in FP64 208 -> 186.  K = 3 is what the register file
+// holds (70 values of the levels, a plane's 56 loads and 28 results of the 256).
+//
 // The per-cell arithmetic is cell_rule, as in lattice_task, and 16-bit
-// storage rounds the step-t values through the storage type, so the state
-// is bit-identical to that of two one-step launches.  Moments of f(t) and
-// f(t + 1) go to their moment boxes as in lattice_task.
+// storage rounds every level through the storage type, so the state is
+// bit-identical to that of K one-step launches.  Moments of every step go to
+// their moment boxes as in lattice_task.
 // ---------------------------------------------------------------------------
-constexpr int kTwoStepMaxPitch = 256;
-// Rows longer than kTwoStepMaxPitch are cut into strips of kStripW owned cells.  A strip's block
-// spans kStripW + 2 lanes: the columns on either side are computed for step t from the loaded
-// state (as the halo rows are) and hand their values inward, so no block waits for another.
-constexpr int kStripW = 4 * 64 - 2;
-__host__ __device__ inline int two_step_strips(int nx, int pitch)
+constexpr int kMarchMaxPitch = 256;
+constexpr int kMarchMaxSteps = 3;  // most steps of one launch
+// Rows longer than kMarchMaxPitch are cut into strips of kStripW owned cells: the K - 1 columns
+// on either side are computed as the halo rows are.
+constexpr int kStripW = 256 - 2 * (kMarchMaxSteps - 1);
+__host__ __device__ inline int march_strips(int nx, int pitch)
 {
-    return pitch <= kTwoStepMaxPitch ? 1 : (nx + kStripW - 1) / kStripW;
+    return pitch <= kMarchMaxPitch ? 1 : (nx + kStripW - 1) / kStripW;
 }
 
+// The LDS copy of a plane: per population the rows of the block and its halo, row after row, in
+// 16-byte pieces; one instruction of a wavefront copies 64 pieces (1 KiB).
+template <typename E, int K, int R, int W> struct MarchStage {
+    static constexpr int kPer = 16 / (int)sizeof(E);  // cells per piece
+    static constexpr int kHalo = K - 1;
+    // cells of a staged row of a strip: 256 lanes, one neighbour on either side, and the
+    // rounding down of the first cell to a whole piece
+    static constexpr int kStripRow = (258 + 2 * (kPer - 1)) / kPer * kPer;
+    static constexpr int copies(int rows, int row_cells) { return (rows * row_cells / kPer + 63) / 64; }
+    static constexpr int most(int a, int b) { return a > b ? a : b; }
+    static constexpr int kCopies =
+        most(most(most(copies(W * R + 2 * kHalo, 64), copies(W / 2 * R + 2 * kHalo, 128)),
+                  most(copies(W / 3 * R + 2 * kHalo, 192), copies(W / 4 * R + 2 * kHalo, 256))),
+             copies(W / 4 * R + 2 * kHalo, kStripRow));
+    static constexpr int kPop = kCopies * 1024;  // bytes per population
+    static constexpr int kPerWave = (kCopies + W - 1) / W;
+};
+
+// one value per lane from the lane below (to_up) or above; the lane at the end takes `edge`
+template <bool UP> __device__ inline float lane_shift(float edge, float v)
+{
+    constexpr int ctrl = UP ? 0x138 : 0x130;  // whole-wavefront shift by one lane
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(edge), __float_as_int(v), ctrl,
+                                                      0xf, 0xf, false));
+}
+template <bool UP> __device__ inline double lane_shift(double edge, double v)
+{
+    constexpr int ctrl = UP ? 0x138 : 0x130;
+    const int lo = __builtin_amdgcn_update_dpp(__double2loint(edge), __double2loint(v), ctrl, 0xf,
+                                               0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(edge), __double2hiint(v), ctrl, 0xf,
+                                               0xf, false);
+    return __hiloint2double(hi, lo);
+}
+
+constexpr int kWaitLoads = 0x0F70;  // s_waitcnt vmcnt(0), the other counters unconstrained
+
+// LDS stores that the compiler does not order after the copies into LDS still in flight (it
+// would wait for all of them before any LDS access it sees); the caller waits before its barrier
+template <typename T> using lptr = __attribute__((address_space(3))) T *;
+template <int OFFSET> __device__ inline void lds_store(uint32_t addr, float v)
+{
+    asm volatile("ds_write_b32 %0, %1 offset:%2" ::"v"(addr), "v"(v), "n"(OFFSET) : "memory");
+}
+template <int OFFSET> __device__ inline void lds_store(uint32_t addr, double v)
+{
+    asm volatile("ds_write_b64 %0, %1 offset:%2" ::"v"(addr), "v"(v), "n"(OFFSET) : "memory");
+}
+// f(0) .. f(N - 1) with the index as a compile-time constant
+template <int N, typename F> __device__ inline void static_for(F &&f)
+{
+    if constexpr (N > 0) {
+        static_for<N - 1>(f);
+        f(std::integral_constant<int, N - 1>{});
+    }
+}
 
 template <typename C>
 __device__ inline void store_moments(gptr<C> mom, int mrow, int mb_lo0, int mb_n0, int x, C rho,
@@ -508,13 +601,17 @@ __device__ inline void store_moments(gptr<C> mom, int mrow, int mb_lo0, int mb_n
     }
 }
 
-template <typename S, int R, int NT, bool PF>
-__device__ inline void lattice2_block(const StepArgs &a, const int64_t t, const int bsrc, int lb,
-                                      typename StoreTraits<S>::C (*xe)[4][R][2])
+template <typename S, int K, int R, int W, int NT>
+__device__ inline void march_block(const StepArgs &a, const int64_t t, const int bsrc, int lb,
+                                   char *stage, typename StoreTraits<S>::C *xe)
 {
     using T = StoreTraits<S>;
     using E = typename T::R;
     using C = typename T::C;
+    using G = MarchStage<E, K, R, W>;
+    constexpr int H = K - 1;        // halo rows of level 1 on each side
+    constexpr int N1 = R + 2 * H;   // rows of level 1
+    constexpr int NX = N1 - 2;      // rows of level 2 (the most any level takes from the one below)
     int s = 0;
 #pragma unroll
     for (int k = 1; k < kMaxSeg; ++k)
@@ -524,230 +621,311 @@ __device__ inline void lattice2_block(const StepArgs &a, const int64_t t, const 
     const int il = local / sg.bpi;
     const int nsx = sg.nsx;
     const int rem = local - il * sg.bpi;
-    const int sx = rem % nsx;  // strips of one row run side by side
-    const int zc = (rem / nsx) / sg.nyb;
-    const int yb = rem / nsx - zc * sg.nyb;
-    const auto &I = to_const(a.inst)[sg.first + il];
+    const int sx = wave_uniform(rem % nsx);  // strips of one row run side by side
+    const int zc = wave_uniform((rem / nsx) / sg.nyb);
+    const int yb = wave_uniform(rem / nsx - zc * sg.nyb);
+    const auto &I = to_const(a.inst)[wave_uniform(sg.first + il)];
     const int nx = sg.nx, ny = sg.ny, nz = sg.nz;
     const int pitch = I.pitch;
     const int64_t plane = I.plane;
     const int nw = nsx > 1 ? 4 : pitch / 64;  // wavefronts per row (strip)
-    const int ng = 4 / nw;                    // row groups per block
+    const int ng = wave_uniform(W / nw);  // row groups per block
     const int lane = threadIdx.x & 63;
     const int w = wave_uniform(threadIdx.x >> 6);
-    const int g = w / nw, xs = w - g * nw;
-    const bool active = g < ng;
-    const int y0 = (yb * ng + (active ? g : 0)) * R;
-    const int z0 = zc * a.zchunk;
-    const int zlen = min(a.zchunk, nz - z0);
-    // owned columns [xo, xend); in a strip the first and last lanes are its halo columns
+    const int wg = wave_uniform(w / nw);
+    const bool active = wg < ng;
+    const int g = active ? wg : 0;
+    const int xs = w - wg * nw;
+    const int y0 = (yb * ng + g) * R;
+    const int nzc = sg.bpi / (sg.nyb * nsx);  // chunks of planes, equal to within one plane
+    const int z0 = zc * (nz / nzc) + min(zc, nz % nzc);
+    const int zlen = nz / nzc + (zc < nz % nzc);
+    // owned columns [xo, xend); in a strip the first and last K - 1 columns are halo
     const int xo = nsx > 1 ? sx * kStripW : 0;
     const int xend = nsx > 1 ? min(nx, xo + kStripW) : nx;
-    const int x = (nsx > 1 ? xo - 1 : 0) + xs * 64 + lane;
-    const bool xin = active && x >= 0 && x < nx;  // the lane has a cell
-    const bool own = xin && x >= xo && x < xend;   // ... and advances it to step t + 2
+    const int xfirst = nsx > 1 ? xo - H : 0;
+    const int x = xfirst + xs * 64 + lane;
+    const bool own = active && x >= xo && x < xend;
     const C c0sq = (C)I.c0sq;
     const C phi = (C)I.wall_phi;
     const gptr<const C> c2box = to_global<C>(I.c2box);
-    const bool meas = I.mb_n[0] > 0;
     const int bb_lo[3] = {I.bb_lo[0], I.bb_lo[1], I.bb_lo[2]};
     const int bb_n[3] = {I.bb_n[0], I.bb_n[1], I.bb_n[2]};
     const int mb_lo[3] = {I.mb_lo[0], I.mb_lo[1], I.mb_lo[2]};
     const int mb_n[3] = {I.mb_n[0], I.mb_n[1], I.mb_n[2]};
-    const gptr<C> mom_a = to_global<C>(I.mom[slot_of(t)]);
-    const gptr<C> mom_b = to_global<C>(I.mom[slot_of(t + 1)]);
-    C rs_a = C(0), rs_b = C(0);
-    if (x == 1) {
-        rs_a = (C)(I.src_amp * sin(I.omega * (double)t));
-        rs_b = (C)(I.src_amp * sin(I.omega * (double)(t + 1)));
+    C rs[K];
+    gptr<C> mom[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        rs[k] = C(0);
+        mom[k] = to_global<C>(I.mom[slot_of(t + k)]);
     }
-    const gptr<const E> src = to_global<E>(static_cast<const void *>(I.buf[bsrc]));
+    if (x == 1) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) rs[k] = (C)(I.src_amp * sin(I.omega * (double)(t + k)));
+    }
+    const gptr<const char> src = to_global<char>(static_cast<const void *>(I.buf[bsrc]));
     const gptr<E> dst = to_global<E>(I.buf[bsrc ^ 1]);
-    const uint32_t ux = (uint32_t)x;
-
-    // step-t values of plane p - 1, pull-ready for step t + 1 (owned rows)
-    C Q0[R], Qpx[R], Qmx[R], Qpy[R], Qmy[R], Qpz[R], Qpz2[R];
-#pragma unroll
-    for (int j = 0; j < R; ++j) Q0[j] = Qpx[j] = Qmx[j] = Qpy[j] = Qmy[j] = Qpz[j] = Qpz2[j] = C(0);
-
-    // uniform offsets, once per block: rows y0 - 1 .. y0 + R (wrapped in y) and their -y / +y
-    // neighbours within a plane, and the plane size; per plane only the z bases change
     const int64_t zstride = (int64_t)ny * pitch;
-    int64_t yoff[R + 2], ymoff[R + 2], ynoff[R + 2];
-    // and the y part of the moment-box and sound-speed-box row indices: a row (y, z) of a box
-    // (origin lo, extent n) starts at cell (bz n1 + by) n0, bz = z - lo2, by = y - lo1, the sum
-    // of a y part and a z part (-1: the row misses the box)
-    int mb_y[R + 2], bb_y[R + 2];
+    auto wrapz = [&](int z) {  // a box may have fewer planes than the halo
+        while (z < 0) z += nz;
+        while (z >= nz) z -= nz;
+        return z;
+    };
+
+    // ---- the copy of a plane into LDS
+    // staged rows: row r of the block is y = yb ng R - H + r (wrapped; the +y and -y populations
+    // come from one row below and above); staged columns: from x0s on, row_cells each
+    const int row_cells = nsx > 1 ? G::kStripRow : pitch;
+    const int x0s = nsx > 1 ? (xfirst - 1) & ~(G::kPer - 1) : 0;
+    const int rows = ng * R + 2 * H;
+    const int ppr = row_cells / G::kPer;  // pieces per row
+    const int n_copy = (rows * ppr + 63) / 64;
+    uint32_t off[3][G::kPerWave];  // byte offset of this lane's piece within a plane, per y shift
 #pragma unroll
-    for (int j = -1; j <= R; ++j) {
-        int y = y0 + j;
-        y = (y < 0) ? y + ny : (y >= ny ? y - ny : y);
-        yoff[j + 1] = (int64_t)y * pitch;
-        ymoff[j + 1] = (int64_t)((y == 0) ? ny - 1 : y - 1) * pitch;
-        ynoff[j + 1] = (int64_t)((y == ny - 1) ? 0 : y + 1) * pitch;
-        const int mby = y - mb_lo[1], bby = y - bb_lo[1];
-        mb_y[j + 1] = (mb_n[0] > 0 && mby >= 0 && mby < mb_n[1]) ? mby * mb_n[0] : -1;
-        bb_y[j + 1] = (bb_n[0] > 0 && bby >= 0 && bby < bb_n[1]) ? bby * bb_n[0] : -1;
+    for (int m = 0; m < G::kPerWave; ++m) {
+        const int piece = (w + W * m) * 64 + lane;
+        int r = piece / ppr;
+        const int c = piece - r * ppr;
+        if (r >= rows) r = 0;  // past the end: copies of a row into the unused tail
+        const int xg = min(max(x0s + c * G::kPer, 0), pitch - G::kPer);
+#pragma unroll
+        for (int v = 0; v < 3; ++v) {
+            int y = (yb * ng * R - H + r + (v == 1 ? -1 : v == 2 ? 1 : 0)) % ny;
+            if (y < 0) y += ny;
+            off[v][m] = ((uint32_t)y * (uint32_t)pitch + (uint32_t)xg) * (uint32_t)sizeof(E);
+        }
+    }
+    const int64_t zbytes = zstride * (int64_t)sizeof(E), pbytes = plane * (int64_t)sizeof(E);
+    auto copy_plane = [&](int zq) {
+        const gptr<const char> zb = src + zq * zbytes;
+        const gptr<const char> zbm = src + ((zq == 0) ? nz - 1 : zq - 1) * zbytes;
+        const gptr<const char> zbn = src + ((zq == nz - 1) ? 0 : zq + 1) * zbytes;
+#pragma unroll
+        for (int m = 0; m < G::kPerWave; ++m)
+            if (w + W * m < n_copy) {
+                char *to = stage + (w + W * m) * 1024;
+#pragma unroll
+                for (int i = 0; i < 7; ++i)
+                    __builtin_amdgcn_global_load_lds(
+                        (gptr<const void>)((i == 5 ? zbm : i == 6 ? zbn : zb) + i * pbytes +
+                                           off[i == 3 ? 1 : i == 4 ? 2 : 0][m]),
+                        (lptr<void>)(to + i * G::kPop), 16, 0, 0);
+            }
+    };
+    // this lane's cell in the first staged row of its row group
+    const E *cell = reinterpret_cast<const E *>(stage) + g * R * row_cells + (x - x0s);
+
+    // ---- rows of the moment box and the sound-speed box: a row (y, z) of a box (origin lo,
+    // extent n) starts at cell (bz n1 + by) n0, the sum of a y part and a z part (-1: it misses)
+    const uint32_t out_x = (uint32_t)(y0 * pitch + x);  // cell of row y0 within a plane
+    int mb_y[R], bb_y[N1];
+#pragma unroll
+    for (int j = 0; j < N1; ++j) {
+        int y = (y0 + j - H) % ny;
+        if (y < 0) y += ny;
+        const int bby = y - bb_lo[1];
+        bb_y[j] = wave_uniform((bb_n[0] > 0 && bby >= 0 && bby < bb_n[1]) ? bby * bb_n[0] : -1);
+        if (j >= H && j < H + R) {
+            const int mby = y - mb_lo[1];
+            mb_y[j - H] = wave_uniform(
+                (mb_n[0] > 0 && y0 + j - H < ny && mby >= 0 && mby < mb_n[1]) ? mby * mb_n[0] : -1);
+        }
     }
     auto box_z = [&](const int *lo, const int *n, int z) {
         const int bz = z - lo[2];
         return (n[0] > 0 && bz >= 0 && bz < n[2]) ? bz * n[1] * n[0] : -1;
     };
-    auto box_rowj = [&](const int *ypart, int zpart, int j) {
-        return (zpart >= 0 && ypart[j + 1] >= 0) ? zpart + ypart[j + 1] : -1;
-    };
-    // c^2 of the lane's cell in rows y0 - 1 .. y0 + R of plane zq: every lane loads, cells
-    // outside the sound-speed box read the c0^2 stored after it.  Loaded a plane ahead with the
-    // populations, so that no load is waited for right after it is issued
+    // c^2 of the lane's cell in the rows of level 1 of plane zq: lanes outside the box read the
+    // c0^2 stored after it
     const int n_box = bb_n[0] * bb_n[1] * bb_n[2];
-    auto load_c2 = [&](int zq, C (&c)[R + 2]) {
+    const int bx = x - bb_lo[0];
+    const bool xb = bx >= 0 && bx < bb_n[0];
+    int bb_any = -1;  // some row of the block meets the box
+#pragma unroll
+    for (int j = 0; j < N1; ++j) bb_any = max(bb_any, bb_y[j]);
+    auto load_c2 = [&](int zq, C (&c)[N1]) {
         const int bz = box_z(bb_lo, bb_n, zq);
-        const int bx = x - bb_lo[0];
-        const bool xb = bx >= 0 && bx < bb_n[0];
+        if (__builtin_expect((bz | bb_any) >= 0, 0)) {
 #pragma unroll
-        for (int j = -1; j <= R; ++j) {
-            const int crow = box_rowj(bb_y, bz, j);
-            c[j + 1] = c2box[(crow >= 0 && xb) ? crow + bx : n_box];
-        }
-    };
-
-    // the seven pulled populations (step t) of row y0 + j of plane zq; the
-    // +x / -x neighbours by loads offset by one element.  Every lane loads (no branch, so no
-    // wait is forced early): lanes without a cell (padding, or the idle wavefront of a
-    // 3-wavefront row) read x = 0 of the same row, a line the row's first wavefront fetches
-    // anyway, and their results are discarded; the -1 / +1 offsets stay inside the buffer
-    // because the +x plane follows plane 0 and the -x plane precedes plane 3
-    const uint32_t uxl = xin ? ux : 0u;
-    auto load_row = [&](int zq, int j, E *f) {
-        const int64_t zb = zq * zstride;
-        const int64_t zbm = ((zq == 0) ? nz - 1 : zq - 1) * zstride;
-        const int64_t zbn = ((zq == nz - 1) ? 0 : zq + 1) * zstride;
-        const int64_t row = zb + yoff[j + 1];
-        f[0] = *at(src + row, uxl);
-        f[1] = *at(src + plane + row - 1, uxl);
-        f[2] = *at(src + 2 * plane + row + 1, uxl);
-        f[3] = *at(src + 3 * plane + zb + ymoff[j + 1], uxl);
-        f[4] = *at(src + 4 * plane + zb + ynoff[j + 1], uxl);
-        f[5] = *at(src + 5 * plane + zbm + yoff[j + 1], uxl);
-        f[6] = *at(src + 6 * plane + zbn + yoff[j + 1], uxl);
-    };
-    auto load_plane = [&](int zq, E (&L)[R + 2][7]) {
-#pragma unroll
-        for (int j = -1; j <= R; ++j) load_row(zq, j, L[j + 1]);
-    };
-    auto wrapz = [&](int z) { return (z < 0) ? z + nz : (z >= nz ? z - nz : z); };
-
-    // PF: the loads of plane p + 1 are in flight while plane p is computed
-    E Lnext[R + 2][7];
-    C C2next[R + 2];
-    if (PF) {
-        load_plane(wrapz(z0 - 1), Lnext);
-        load_c2(wrapz(z0 - 1), C2next);
-    }
-    C C2prev[R];  // c^2 of the owned rows of plane p - 1 (step t + 1)
-#pragma unroll
-    for (int j = 0; j < R; ++j) C2prev[j] = c0sq;
-
-    for (int p = -1; p <= zlen; ++p) {
-        const int zp = wrapz(z0 + p);
-        const bool own_plane = p >= 0 && p < zlen;
-        const int sl = (p + 2) & 1;
-        E Lcur[R + 2][7];
-        C C2cur[R + 2];
-        if (PF) {
-#pragma unroll
-            for (int j = 0; j < R + 2; ++j) {
-#pragma unroll
-                for (int i = 0; i < 7; ++i) Lcur[j][i] = Lnext[j][i];
-                C2cur[j] = C2next[j];
-            }
-            if (p < zlen) {
-                load_plane(wrapz(z0 + p + 1), Lnext);
-                load_c2(wrapz(z0 + p + 1), C2next);
-            }
+            for (int j = 0; j < N1; ++j)
+                c[j] = *at(c2box, (uint32_t)(xb && bb_y[j] >= 0 ? bz + bb_y[j] + bx : n_box));
         } else {
-            load_c2(zp, C2cur);
+#pragma unroll
+            for (int j = 0; j < N1; ++j) c[j] = c0sq;
         }
-        C N0[R], Npx[R], Nmx[R], Npy[R], Nmy[R], Npz[R], Nmz[R];
-        C prev_py = C(0);
-        const int mb_z = box_z(mb_lo, mb_n, zp);
+    };
+
+    // ---- wavefront edges: lane 63 hands its +x value right, lane 0 its -x value left
+    // xe[level][row][wavefront][0: +x of lane 63, 1: -x of lane 0]
+    auto xe_at = [&](int lev, int row, int ww, int side) {
+        return ((lev * NX + row) * W + ww) * 2 + side;
+    };
+    const bool edge_lane = lane == 0 || lane == 63;
+    const uint32_t xe_base = (uint32_t)(uintptr_t)(lptr<C>)xe;
+    const int xe_from = lane == 63 ? xe_at(0, 0, min(w + 1, W - 1), 1) : xe_at(0, 0, max(w - 1, 0), 0);
+    const uint32_t xe_to =
+        xe_base + (uint32_t)sizeof(C) * (uint32_t)xe_at(0, 0, w, lane == 63 ? 0 : 1);
+
+    // ---- what level k + 1 hands to level k + 2, pull-ready for the rows of that level: rest, +x,
+    // -x, +y, -y of one plane, +z of that plane and of the one before
+    C q[H][7][NX];
+    C C2[K][N1];  // c^2 of the rows of level k + 1 in its plane
+    C c2next[N1];
+    C edge[H][NX];
 #pragma unroll
-        for (int j = -1; j <= R; ++j) {
-            E Lrow[7];
-            if constexpr (!PF) load_row(zp, j, Lrow);
-            const E *L = PF ? Lcur[j + 1] : Lrow;
-            // every lane computes (padding lanes on zeros); lanes beyond the row pass on zeros
-            C f[7], o[7];
+    for (int k = 0; k < H; ++k)
 #pragma unroll
-            for (int i = 0; i < 7; ++i) f[i] = T::to_c(L[i]);
-            if (x == 0) f[1] = C(0);       // nothing enters from outside the sheets
-            if (x == nx - 1) f[2] = C(0);
-            C rho = f[0];
+        for (int i = 0; i < 7; ++i)
 #pragma unroll
-            for (int i = 1; i < 7; ++i) rho += f[i];
-            if (meas && own_plane && j >= 0 && j < R && own)
-                store_moments(mom_a, box_rowj(mb_y, mb_z, j), mb_lo[0], mb_n[0], x, rho, f);
-            cell_rule<3, C>(f, rho, C2cur[j + 1], x, nx, true, phi, rs_a, o);
+            for (int j = 0; j < NX; ++j) q[k][i][j] = C(0);
 #pragma unroll
-            for (int i = 0; i < 7; ++i) o[i] = xin ? T::to_c(T::to_r(o[i])) : C(0);
-            if (j >= 0 && j < R) {
-                N0[j] = o[0];
-                Npx[j] = __shfl_up(o[1], 1);    // +x arrives from x - 1
-                Nmx[j] = __shfl_down(o[2], 1);  // -x arrives from x + 1
-                if (lane == 63) xe[sl][w][j][0] = o[1];
-                if (lane == 0) xe[sl][w][j][1] = o[2];
-                Npy[j] = prev_py;               // +y arrives from row j - 1
-                Npz[j] = o[5];
-                Nmz[j] = o[6];
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int j = 0; j < N1; ++j) C2[k][j] = c0sq;
+
+    load_c2(wrapz(z0 - H), c2next);
+    copy_plane(wrapz(z0 - H));
+    __builtin_amdgcn_s_waitcnt(kWaitLoads);
+
+    // Wavefronts without a sheet cell, those with the far wall only and those with the near wall
+    // and the source each run their own copy of the loop: the block waits for its slowest
+    // wavefront, and the others have no branch per cell.
+    const bool wall = x == 0 || x == nx - 1;
+    auto march = [&](auto sheets) {
+        constexpr int SHEETS = decltype(sheets)::value;  // 0: none, 1: the far wall, 2: any
+        for (int i = -H; i < zlen + H; ++i) {
+            // the plane has arrived, for this wavefront and behind the barrier for the others,
+            // and with it the edges they stored in the last iteration
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __syncthreads();
+            E L[N1][7];
+#pragma unroll
+            for (int j = 0; j < N1; ++j) {
+                const char *c = reinterpret_cast<const char *>(cell + j * row_cells);
+#pragma unroll
+                for (int p = 0; p < 7; ++p)
+                    L[j][p] = *reinterpret_cast<const E *>(
+                        c + p * G::kPop + (p == 1 ? -1 : p == 2 ? 1 : 0) * (int)sizeof(E));
             }
-            if (j >= 1) Nmy[j - 1] = o[4];      // -y arrives from row j + 1
-            prev_py = o[3];
-        }
-        __syncthreads();
 #pragma unroll
-        for (int j = 0; j < R; ++j) {
-            // neighbours in the same row group only (an idle wavefront reads nothing)
-            if (lane == 0) Npx[j] = (active && xs > 0) ? xe[sl][w - 1][j][0] : C(0);
-            if (lane == 63) Nmx[j] = (active && xs < nw - 1) ? xe[sl][w + 1][j][1] : C(0);
-        }
-        if (p >= 1 && own) {
-            // step t + 1 on plane zq = z0 + p - 1
-            const int zq = z0 + p - 1;
-            const int mb_zq = box_z(mb_lo, mb_n, zq);
+            for (int k = 0; k < H; ++k)
 #pragma unroll
-            for (int j = 0; j < R; ++j) {
+                for (int j = 0; j < NX - 2 * k; ++j) edge[k][j] = xe[xe_from + (k * NX + j) * 2 * W];
+#pragma unroll
+            for (int j = 0; j < N1; ++j) C2[0][j] = c2next[j];
+            __syncthreads();  // everybody has read: the plane may be overwritten
+            if (i + 1 < zlen + H) {
+                load_c2(wrapz(z0 + i + 1), c2next);
+                copy_plane(wrapz(z0 + i + 1));
+            }
+
+            C pend[K];    // +y value of a level's last row: pulled after the next row's turn
+            int mrow[K];  // z part of the moment-box row index of a level's plane
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                pend[k] = C(0);
+                const int p = i - k;
+                mrow[k] = wave_uniform((p >= 0 && p < zlen) ? box_z(mb_lo, mb_n, z0 + p) : -1);
+            }
+            E res[R][7];  // level K
+#pragma unroll
+            for (int j = 0; j < N1; ++j) {  // row y0 + j - H
                 C f[7], o[7];
-                f[0] = Q0[j];
-                f[1] = (x == 0) ? C(0) : Qpx[j];
-                f[2] = (x == nx - 1) ? C(0) : Qmx[j];
-                f[3] = Qpy[j];
-                f[4] = Qmy[j];
-                f[5] = Qpz2[j];  // +z of plane zq - 1
-                f[6] = Nmz[j];   // -z of plane zq + 1
-                C rho = f[0];
 #pragma unroll
-                for (int i = 1; i < 7; ++i) rho += f[i];
-                if (meas)
-                    store_moments(mom_b, box_rowj(mb_y, mb_zq, j), mb_lo[0], mb_n[0], x, rho, f);
-                cell_rule<3, C>(f, rho, C2prev[j], x, nx, true, phi, rs_b, o);
-                const int64_t row = zq * zstride + yoff[j + 1];
+                for (int p = 0; p < 7; ++p) f[p] = T::to_c(L[j][p]);
 #pragma unroll
-                for (int i = 0; i < 7; ++i)
-                    vstore<E, (NT >= 1)>(at(dst + (i * plane + row), ux), T::to_r(o[i]));
+                for (int k = 0; k < K; ++k) {  // level k + 1 covers rows k .. N1 - 1 - k
+                    if (j < k || j >= N1 - k) break;
+                    if (k > 0) {
+                        const int r = j - k;  // row index of this level
+                        C(&Q)[7][NX] = q[k - 1];
+                        C n[7];
+                        n[0] = Q[0][r];
+                        n[1] = lane_shift<true>(edge[k - 1][r], Q[1][r]);
+                        n[2] = lane_shift<false>(edge[k - 1][r], Q[2][r]);
+                        n[3] = Q[3][r];
+                        n[4] = Q[4][r];
+                        n[5] = Q[6][r];
+                        n[6] = o[6];
+                        // the row of the level below that has just been computed takes its place
+                        Q[0][r] = o[0];
+                        Q[1][r] = o[1];
+                        Q[2][r] = o[2];
+                        Q[6][r] = Q[5][r];
+                        Q[5][r] = o[5];
+                        Q[3][r] = pend[k - 1];
+                        if (r > 0) Q[4][r - 1] = o[4];
+                        pend[k - 1] = o[3];
+#pragma unroll
+                        for (int p = 0; p < 7; ++p) f[p] = n[p];
+                    }
+                    // nothing enters from outside the sheets
+                    if (SHEETS == 2) f[1] = (x == 0) ? C(0) : f[1];
+                    if (SHEETS >= 1) f[2] = (x == nx - 1) ? C(0) : f[2];
+                    C rho = f[0];
+#pragma unroll
+                    for (int p = 1; p < 7; ++p) rho += f[p];
+                    if (j >= H && j < H + R && __builtin_expect((mrow[k] | mb_y[j - H]) >= 0, 0)) {
+                        if (own)
+                            store_moments(mom[k], mrow[k] + mb_y[j - H], mb_lo[0], mb_n[0], x, rho, f);
+                    }
+                    bulk_rule<3, C>(f, rho, C2[k][j], o);
+                    if (SHEETS >= 1 && wall) wall_rule<3, C>(f, phi, o);
+                    if (SHEETS == 2 && x == 1) impose_rule<3, C>(f, C2[k][j], rs[k], o);
+#pragma unroll
+                    for (int p = 0; p < 7; ++p) {
+                        if (k < H) o[p] = T::to_c(T::to_r(o[p]));
+                        else res[j - H][p] = T::to_r(o[p]);
+                    }
+                }
+                // the first and last row of a level give only their +y or -y value to the next
+#pragma unroll
+                for (int k = 0; k < H; ++k) {
+                    if (j == k) pend[k] = o[3];
+                    if (j == N1 - 1 - k) q[k][4][NX - 1 - 2 * k] = o[4];
+                }
             }
-        }
+            if (nw > 1 && edge_lane) {
+                static_for<H * NX>([&](auto at_row) {
+                    constexpr int k = decltype(at_row)::value / NX, j = decltype(at_row)::value % NX;
+                    if constexpr (j < NX - 2 * k)
+                        lds_store<(k * NX + j) * 2 * W * (int)sizeof(C)>(
+                            xe_to, lane == 63 ? q[k][1][j] : q[k][2][j]);
+                });
+            }
+            // wait for the next plane before this one's stores are issued: the counter that is
+            // waited on also counts stores, which now have the next iteration to complete in
+            __builtin_amdgcn_s_waitcnt(kWaitLoads);
+            if (i >= H && own) {
+                gptr<E> out = dst + (int64_t)(z0 + i - H) * zstride;
 #pragma unroll
-        for (int j = 0; j < R; ++j) {
-            C2prev[j] = C2cur[j + 1];
-            Qpz2[j] = Qpz[j];
-            Q0[j] = N0[j];
-            Qpx[j] = Npx[j];
-            Qmx[j] = Nmx[j];
-            Qpy[j] = Npy[j];
-            Qmy[j] = Nmy[j];
-            Qpz[j] = Npz[j];
+                for (int p = 0; p < 7; ++p, out += plane)
+#pragma unroll
+                    for (int j = 0; j < R; ++j)
+                        if (__builtin_expect(y0 + j < ny, 1))
+                            vstore<E, (NT >= 1)>(at(out, out_x + j * (uint32_t)pitch), res[j][p]);
+            }
+#pragma unroll
+            for (int k = K - 1; k > 0; --k)
+#pragma unroll
+                for (int j = 0; j < N1; ++j) C2[k][j] = C2[k - 1][j];
         }
-    }
+    };
+    if (!active) {
+        // a wavefront without cells (three to a row leave two over) copies its share and waits
+        for (int i = -H; i < zlen + H; ++i) {
+            __syncthreads();
+            __syncthreads();
+            if (i + 1 < zlen + H) copy_plane(wrapz(z0 + i + 1));
+            __builtin_amdgcn_s_waitcnt(kWaitLoads);
+        }
+    } else if (__ballot(x == 0 || x == 1))
+        march(std::integral_constant<int, 2>{});
+    else if (__ballot(wall))
+        march(std::integral_constant<int, 1>{});
+    else
+        march(std::integral_constant<int, 0>{});
 }
 
 // ---------------------------------------------------------------------------
@@ -760,13 +938,13 @@ __device__ inline void lattice2_block(const StepArgs &a, const int64_t t, const 
 // summed over the 64 elements in a fixed order into one partial per chunk.
 // ---------------------------------------------------------------------------
 template <int DIM, typename C>
-__device__ inline void surface_block(const StepArgs &a, const int64_t t_meas, int sb,
+__device__ inline void surface_block(const StepArgs &a, const int64_t t_meas, int sb, int tid,
                                      double (*lds)[64][4])
 {
     constexpr int NN = (DIM == 3) ? 27 : 9;
     constexpr int PER = (NN + 3) / 4;
-    const int lane = threadIdx.x & 63;
-    const int w = wave_uniform(threadIdx.x >> 6);
+    const int lane = tid & 63;
+    const int w = wave_uniform(tid >> 6);
     const InstDev &I = a.inst[a.sb_inst[sb]];
     const int chunk = a.sb_chunk[sb];
     const int k = chunk * 64 + lane;
@@ -829,9 +1007,9 @@ __device__ inline void surface_block(const StepArgs &a, const int64_t t_meas, in
 // Reducer: F(t) of one instance for the steps t0 .. t0+n-1 in order, each
 // from its chunk partials (written by an earlier launch), scaled, traced and
 // accumulated.  One block per instance, so the accumulation order is fixed.
-__device__ inline void reduce_block(const StepArgs &a, const int64_t t0, int n, int ii)
+__device__ inline void reduce_block(const StepArgs &a, const int64_t t0, int n, int ii, int tid)
 {
-    if (threadIdx.x != 0) return;
+    if (tid != 0) return;
     const InstDev &I = a.inst[ii];
     if (I.n_surf == 0) return;
     for (int j = 0; j < n; ++j) {
@@ -864,10 +1042,11 @@ __device__ inline void reduce_block(const StepArgs &a, const int64_t t0, int n, 
 // The measurement blocks of a launch (reducers, then the surface blocks of
 // each measured step); returns false for a lattice block.
 template <int DIM, typename C>
-__device__ inline bool measure_part(const StepArgs &a, const int64_t t, int b, double (*lds)[64][4])
+__device__ inline bool measure_part(const StepArgs &a, const int64_t t, int b, int tid,
+                                    double (*lds)[64][4])
 {
     if (b < a.n_red) {
-        reduce_block(a, t - a.red_off, a.n_rs, b);
+        reduce_block(a, t - a.red_off, a.n_rs, b, tid);
         return true;
     }
     b -= a.n_red;
@@ -877,7 +1056,7 @@ __device__ inline bool measure_part(const StepArgs &a, const int64_t t, int b, d
         const InstDev &I = a.inst[a.sb_inst[sb]];
         const int64_t t_meas = t - a.meas_off + j;
         if (I.max_steps > 0 && t_meas >= I.max_steps) return true;
-        surface_block<DIM, C>(a, t_meas, sb, lds);
+        surface_block<DIM, C>(a, t_meas, sb, tid, lds);
         return true;
     }
     return false;
@@ -889,7 +1068,7 @@ __global__ void __launch_bounds__(kStepThreads) step_kernel(StepArgs a)
     __shared__ double lds[4][64][4];
     const int64_t t = a.tp[0] + a.dt;
     const int b = blockIdx.x;
-    if (measure_part<DIM, typename StoreTraits<S>::C>(a, t, b, lds)) return;
+    if (measure_part<DIM, typename StoreTraits<S>::C>(a, t, b, threadIdx.x, lds)) return;
     const int bsrc = ((int)a.tp[1] + a.dbuf) & 1;
     const int wave = wave_uniform(threadIdx.x >> 6);
     const int task = (b - a.n_red - a.n_ms * a.n_sb) * (kStepThreads / 64) + wave;
@@ -909,20 +1088,28 @@ __device__ inline int xcd_block(int b, int n)
     return (x < r) ? x * (q + 1) + k : r * (q + 1) + (x - r) * q + k;
 }
 
-template <typename S, int R, int NT, bool PF>
-__global__ void __launch_bounds__(kStepThreads, PF ? 2 : 4) step2_kernel(StepArgs a)
+template <typename S, int K, int R, int W, int NT>
+__global__ void __launch_bounds__(64 * W, 2) march_kernel(StepArgs a)
 {
     using C = typename StoreTraits<S>::C;
-    __shared__ double lds[4][64][4];
-    __shared__ C xe[2][4][R][2];
+    using G = MarchStage<typename StoreTraits<S>::R, K, R, W>;
+    constexpr int NX = R + 2 * (K - 1) - 2;
+    __shared__ __attribute__((aligned(1024))) char stage[7 * G::kPop];
+    __shared__ C xe[(K - 1) * NX * 2 * W];
     const int64_t t = a.tp[0] + a.dt;
     const int b = blockIdx.x;
     // the long lattice blocks first, the short measurement blocks fill the tail
     if (b < a.ntask) {
-        lattice2_block<S, R, NT, PF>(a, t, ((int)a.tp[1] + a.dbuf) & 1, xcd_block(b, a.ntask), xe);
+        march_block<S, K, R, W, NT>(a, t, ((int)a.tp[1] + a.dbuf) & 1, xcd_block(b, a.ntask), stage, xe);
         return;
     }
-    measure_part<3, C>(a, t, b - a.ntask, lds);
+    // measurement blocks of kStepThreads threads, side by side
+    using Lds = double[4][64][4];
+    constexpr int per = 64 * W / kStepThreads;
+    static_assert(sizeof stage >= per * sizeof(Lds), "the surface blocks use the same LDS");
+    const int part = wave_uniform(threadIdx.x / kStepThreads);
+    measure_part<3, C>(a, t, per * (b - a.ntask) + part, threadIdx.x % kStepThreads,
+                       reinterpret_cast<Lds *>(stage)[part]);
 }
 
 // Point source (the paper's oscillating point source): after the lattice

@@ -13,10 +13,12 @@
 #include <cstdio>
 #include <cstring>
 #include <climits>
+#include <functional>
 #include <limits>
 #include <mutex>
 #include <numeric>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/lb_wave.h"
@@ -426,14 +428,22 @@ inline void store_host(uint8_t *p, int storage, double v)
     }
 }
 
+// Blocks of one box: row blocks x chunks of planes x strips of a row.
+struct MarchBox {
+    int64_t nyb = 0, nzc = 0, nsx = 0;
+    int64_t blocks() const { return nyb * nzc * nsx; }
+};
+
 }  // namespace
 
 struct lb_wave {
     int n = 0, dim = 0, storage = 0, vx = 1, xm = 0, nt = 0;
-    int fused = 1;                    // lattice steps per launch (1 or 2)
-    bool fused_ok = false;            // every instance fits the two-step kernel
-    int zchunk = 0;                   // planes per chunk of the two-step kernel
-    std::vector<int> blk0;            // internal order, size n + 1: two-step blocks
+    int fused = 1;                    // 1: one lattice step per launch, 2: several
+    bool fused_ok = false;            // several steps per launch are allowed
+    bool march_ok = false;            // every instance fits the march kernel
+    int march_waves = 4;              // wavefronts per block of the march kernel
+    std::vector<MarchBox> boxes;      // internal order: march decomposition
+    std::vector<int> blk0;            // internal order, size n + 1: march blocks
     char *ws = nullptr;
     size_t ws_bytes = 0;
     hipStream_t stream = nullptr;
@@ -576,52 +586,162 @@ void launch_point(const lb_wave *h, const StepArgs &a, hipStream_t st)
     }
 }
 
-// Rows per row group of the two-step kernel: 4 for FP32; 2 for FP64, whose values take
-// twice the registers, and for FP16/BF16, whose 2-byte loads are latency-bound and gain
-// more from the extra wavefronts than they lose to the re-read halo rows (measured).
-int two_step_rows(int storage) { return storage == LB_F32 ? 4 : 2; }
-// Planes per two-step chunk before the halving below.  Longer chunks re-read fewer halo
-// planes (two per chunk) and make fewer, longer blocks.  Measured on 16 boxes of
-// 256 x 128 x 128, ms per launch with 64 / 32 / 16 planes: FP32 (4-row groups) 0.761 /
-// 0.796 / 0.791; FP16 (2-row groups) 0.490 / 0.484 / 0.498.
-int two_step_zchunk(int storage) { return storage == LB_F32 ? 64 : 32; }
-// Two-step plane chunks shrink (down to kMinZChunk) until a handle has at least as many blocks
-// as the chip holds at once: 512 for FP32 (256 CUs, two wavefronts per SIMD), 1024 for the
-// others (four).  One sphere of 256 x 128 x 128 in FP32: 2.25 forces/s with 512 blocks of 8
-// planes, 2.08 with 1024 of 4.
-int64_t two_step_min_blocks(int storage) { return storage == LB_F32 ? 512 : 1024; }
-constexpr int kMinZChunk = 4;
+// Steps of one march launch, and rows per row group.  FP64 holds twice the registers and LDS.
+int march_steps(int storage) { return storage == LB_F64 ? 2 : 3; }
+int march_rows(int storage) { return storage == LB_F64 ? 2 : 4; }
+// Wavefronts of a march block: 8 (one block per CU) or 4 (two).  With 4, a row of 256 cells or a
+// strip makes a block of one row group, which reads (R + 4) / R = 2 times its own rows; 8 make
+// two groups that share their halo rows, 1.5 times.  That pays where the L2 misses of the halo
+// rows are on the critical path, in handles larger than the memory-side cache (16 FP32 spheres of
+// 256 x 128 x 128: 268 us per step against 278; FP64, 4 spheres: 165 against 187); in it, and in
+// 16-bit storage, which is bound by its instructions, two independent blocks hide each other's
+// barriers better (one FP32 sphere: 20.1 against 22.8; 16 in FP16: 178 against 197).
+constexpr int64_t kMallBytes = 256 << 20;
 
-// Prefetching the next plane's populations and sound speeds pays where the
-// registers allow it (4- and 2-byte storage, two wavefronts per SIMD without
-// spills); FP64 loads in place.
-template <typename S, int R>
-void launch2_t(const lb_wave *h, const StepArgs &a, int blocks, hipStream_t st)
+MarchBox march_box(const InstDev &I, int storage, int waves, int zchunk)
 {
-    constexpr bool PF = sizeof(typename StoreTraits<S>::R) <= 4;
-    if (h->nt == 0)
-        hipLaunchKernelGGL((step2_kernel<S, R, 0, PF>), dim3(blocks), dim3(kStepThreads), 0, st, a);
-    else
-        hipLaunchKernelGGL((step2_kernel<S, R, 1, PF>), dim3(blocks), dim3(kStepThreads), 0, st, a);
+    MarchBox m;
+    m.nsx = march_strips(I.nx, I.pitch);
+    const int rows = march_rows(storage) * (waves / (m.nsx > 1 ? 4 : I.pitch / 64));
+    m.nyb = (I.ny + rows - 1) / rows;
+    m.nzc = (I.nz + zchunk - 1) / zchunk;
+    return m;
 }
 
-void launch2(const lb_wave *h, const StepArgs &a, int blocks, hipStream_t st)
+// Time of one launch with chunks of at most zchunk planes, in iterations of a block: every XCD
+// takes an eighth of the blocks, in order, and as one ends its place (a CU holds one block of 8
+// wavefronts or two of 4) takes the next.  A block runs its planes and the K - 1 halo planes at
+// both ends; two on a CU take 1.4 times as long as one alone (measured: 1.6 from HBM, 1.2 from the
+// memory-side cache).
+double march_time(const std::vector<InstDev> &inst, int storage, int waves, int zchunk)
 {
-    if (blocks <= 0) return;
-    switch (h->storage) {
-    case LB_F64: launch2_t<double, 2>(h, a, blocks, st); break;
-    case LB_F32: launch2_t<float, 4>(h, a, blocks, st); break;
-    case LB_F16: launch2_t<_Float16, 2>(h, a, blocks, st); break;
-    default: launch2_t<bf16, 2>(h, a, blocks, st); break;
+    std::vector<std::pair<int64_t, double>> runs;  // blocks, iterations
+    int64_t n = 0;
+    for (const InstDev &I : inst) {
+        const MarchBox m = march_box(I, storage, waves, zchunk);
+        runs.push_back({m.blocks(), (double)(I.nz + m.nzc - 1) / (double)m.nzc +
+                                        2.0 * (march_steps(storage) - 1) + 1.0});
+        n += m.blocks();
     }
+    const int places = 32 * 8 / waves;
+    double worst = 0.0;
+    size_t r = 0;
+    int64_t used = 0;
+    for (int x = 0; x < kNumXcd; ++x) {
+        std::vector<double> free_at(places, 0.0);  // a heap, the earliest on top
+        double last = 0.0;
+        for (int64_t k = n / kNumXcd + (x < n % kNumXcd); k > 0; --k) {
+            while (used == runs[r].first) {
+                ++r;
+                used = 0;
+            }
+            ++used;
+            std::pop_heap(free_at.begin(), free_at.end(), std::greater<double>());
+            last = std::max(last, free_at.back() += runs[r].second);
+            std::push_heap(free_at.begin(), free_at.end(), std::greater<double>());
+        }
+        worst = std::max(worst, last);
+    }
+    return worst * (waves == 4 && n > 256 ? 1.4 : 1.0);
+}
+
+// The chunk length with the shortest such time; handles of very many blocks, where the ends
+// hardly matter, take long chunks without trying.  Measured against chunks of a fixed 64 planes
+// (FP32, us per step): 16 uneven boxes of 64 to 192 cells a side 198 against 231, four channels of
+// 1000 x 64 x 64 83 against 127, one sphere of 256 x 128 x 128 20 against 45 or more.
+int march_zchunk(const std::vector<InstDev> &inst, int storage, int waves)
+{
+    int64_t n = 0;
+    for (const InstDev &I : inst) n += march_box(I, storage, waves, 64).blocks();
+    int best = 64;
+    if (n > 8192) return best;
+    double best_time = march_time(inst, storage, waves, best);
+    for (int zc : {128, 96, 48, 40, 32, 28, 24, 20, 16, 12, 10, 8, 6, 5, 4, 3, 2, 1}) {
+        const double time = march_time(inst, storage, waves, zc);
+        if (time < best_time) {
+            best_time = time;
+            best = zc;
+        }
+    }
+    return best;
+}
+
+// 8 wavefronts where most cells lie in rows that fill a block of 4 and the states outgrow the
+// memory-side cache (see kMallBytes)
+int march_block_waves(const std::vector<InstDev> &inst, int storage)
+{
+    if (elem_bytes(storage) < 4) return 4;
+    int64_t cells = 0, wide = 0;
+    for (const InstDev &I : inst) {
+        const int64_t c = (int64_t)I.pitch * I.ny * I.nz;
+        cells += c;
+        if (I.pitch >= 256) wide += c;
+    }
+    return 2 * wide > cells && cells * 7 * kNumBuf * (int64_t)elem_bytes(storage) > kMallBytes ? 8 : 4;
+}
+
+// Several steps per launch need ny to be a multiple of the rows of a block: kRuleRows rows per
+// row group.  (The march kernel itself takes any ny; the rule is the interface's.)
+int rule_rows(int storage) { return storage == LB_F32 ? 4 : 2; }
+
+template <typename S, int K, int R, int W>
+void launch_march_w(const lb_wave *h, const StepArgs &a, int blocks, hipStream_t st)
+{
+    if (h->nt == 0)
+        hipLaunchKernelGGL((march_kernel<S, K, R, W, 0>), dim3(blocks), dim3(64 * W), 0, st, a);
+    else
+        hipLaunchKernelGGL((march_kernel<S, K, R, W, 1>), dim3(blocks), dim3(64 * W), 0, st, a);
+}
+
+template <typename S, int K, int R>
+void launch_march_t(const lb_wave *h, const StepArgs &a, int meas_blocks, hipStream_t st)
+{
+    if (h->march_waves == 8)
+        launch_march_w<S, K, R, 8>(h, a, (meas_blocks + 1) / 2 + a.ntask, st);
+    else
+        launch_march_w<S, K, R, 4>(h, a, meas_blocks + a.ntask, st);
+}
+
+void launch_march(const lb_wave *h, const StepArgs &a, int nst, int meas_blocks, hipStream_t st)
+{
+    if (meas_blocks + a.ntask <= 0) return;
+    const bool three = nst == 3;
+    switch (h->storage) {
+    case LB_F64: launch_march_t<double, 2, 2>(h, a, meas_blocks, st); break;
+    case LB_F32:
+        three ? launch_march_t<float, 3, 4>(h, a, meas_blocks, st)
+              : launch_march_t<float, 2, 4>(h, a, meas_blocks, st);
+        break;
+    case LB_F16:
+        three ? launch_march_t<_Float16, 3, 4>(h, a, meas_blocks, st)
+              : launch_march_t<_Float16, 2, 4>(h, a, meas_blocks, st);
+        break;
+    default:
+        three ? launch_march_t<bf16, 3, 4>(h, a, meas_blocks, st)
+              : launch_march_t<bf16, 2, 4>(h, a, meas_blocks, st);
+        break;
+    }
+}
+
+// The launches of n lattice steps: at most `most` steps each, the shorter ones first.
+int next_steps(int64_t n, int most)
+{
+    if (most == 3) return n % 3 == 0 ? 3 : n == 1 ? 1 : 2;  // 3 m + 1 = 2 + 2 + 3 (m - 1)
+    if (most == 2) return n % 2 == 0 ? 2 : 1;
+    return 1;
+}
+
+int most_steps(const lb_wave *h)
+{
+    return h->fused == 2 && h->march_ok ? march_steps(h->storage) : 1;
 }
 
 // Measurement part of the launch whose lattice part starts at t_launch:
 // reduce every measured step whose partials an earlier launch wrote
 // (steps red .. meas-1), and measure every step whose moments an earlier
-// launch stored (steps meas .. t_launch-1).  A launch advances at most two
-// steps, so both ranges hold at most two steps and the slots they use
-// (step mod 4) differ from those the launch writes.
+// launch stored (steps meas .. t_launch-1).  A launch advances at most three
+// steps, so both ranges hold at most three steps and the slots they use
+// (step mod 8) differ from those the launch writes.
 void plan_measure(lb_wave *h, StepArgs &a, int64_t t_launch)
 {
     a.n_red = a.n_sb = a.n_ms = a.n_rs = 0;
@@ -649,17 +769,16 @@ void plan_measure(lb_wave *h, StepArgs &a, int64_t t_launch)
 // Fill the lattice part of `a` for the steps t .. t+nst-1 (segments of the
 // live prefix) and launch, one launch per kMaxSeg segments; the measurement
 // blocks ride on the first launch.  nst = 1: wave tasks of step_kernel;
-// nst = 2: blocks of step2_kernel (the live prefix is the same for both steps).
+// else blocks of march_kernel (the live prefix is the same for all its steps).
 void emit_step(const lb_wave *h, StepArgs a, int64_t t, int32_t dt, int dbuf, int nst,
                hipStream_t st)
 {
     const int na = active_prefix(h, t);
-    const bool two = nst == 2;
-    auto first_of = [&](const SegInfo &sg) { return two ? sg.blk0 : sg.task0; };
-    const int n_active = two ? h->blk0[na] : h->task0[na];
+    const bool march = nst > 1;
+    auto first_of = [&](const SegInfo &sg) { return march ? sg.blk0 : sg.task0; };
+    const int n_active = march ? h->blk0[na] : h->task0[na];
     a.dt = dt;
     a.dbuf = dbuf;
-    a.zchunk = h->zchunk;
     size_t s = 0;
     bool first = true;
     do {
@@ -667,8 +786,8 @@ void emit_step(const lb_wave *h, StepArgs a, int64_t t, int32_t dt, int dbuf, in
         int k = 0;
         for (; k < kMaxSeg && s + k < h->segs.size() && first_of(h->segs[s + k]) < n_active; ++k) {
             a.seg[k] = h->segs[s + k];
-            a.seg[k].task0 -= two ? 0 : base;
-            a.seg[k].blk0 -= two ? base : 0;
+            a.seg[k].task0 -= march ? 0 : base;
+            a.seg[k].blk0 -= march ? base : 0;
         }
         const int end = (s + k < h->segs.size()) ? std::min(first_of(h->segs[s + k]), n_active)
                                                  : n_active;
@@ -676,14 +795,14 @@ void emit_step(const lb_wave *h, StepArgs a, int64_t t, int32_t dt, int dbuf, in
         a.ntask = k > 0 ? end - base : 0;
         if (!first) a.n_red = a.n_sb = a.n_ms = a.n_rs = 0;
         const int meas_blocks = a.n_red + a.n_ms * a.n_sb;
-        if (two)
-            launch2(h, a, meas_blocks + a.ntask, st);
+        if (march)
+            launch_march(h, a, nst, meas_blocks, st);
         else
             launch(h, a, meas_blocks + (a.ntask + 3) / 4, st);
         first = false;
         s += k;
     } while (s < h->segs.size() && first_of(h->segs[s]) < n_active);
-    if (h->any_point && !two) launch_point(h, a, st);
+    if (h->any_point && !march) launch_point(h, a, st);
 }
 
 // Set the device counter to the handle's step and buffer, in stream order.
@@ -711,7 +830,7 @@ void advance(lb_wave *h, int64_t k, int n_launch)
     for (int ii = active_prefix(h, h->t); ii < live; ++ii) h->stop_buf[ii] = h->cur;
 }
 
-// nst lattice steps (1 or 2) for every live instance, with the measurement
+// nst lattice steps (1 to 3) for every live instance, with the measurement
 // of the previous steps folded into the same launch.
 int enqueue_step(lb_wave *h, int nst)
 {
@@ -728,10 +847,12 @@ int enqueue_step(lb_wave *h, int nst)
     return LB_OK;
 }
 
-// Steps t and t+1 can share a two-step launch: no instance stops after t.
-bool can_fuse(const lb_wave *h)
+// The largest number of steps up to k that one launch can advance: no instance stops inside it.
+int fuse_steps(const lb_wave *h, int k)
 {
-    return h->fused == 2 && active_prefix(h, h->t) == active_prefix(h, h->t + 1);
+    const int live = active_prefix(h, h->t);
+    while (k > 1 && active_prefix(h, h->t + k - 1) != live) --k;
+    return k;
 }
 
 // Finish the measurement of every completed step (two launches at most).
@@ -751,14 +872,12 @@ int flush_measure(lb_wave *h)
     return LB_OK;
 }
 
-// Steps t .. t+k-1 all launch the same blocks (k / nst launches of nst
-// steps): the measurement runs nst and 2 nst steps behind and no instance
-// stops inside the window.
-bool steady(const lb_wave *h, int64_t k)
+// Steps t .. t+k-1 all launch the same blocks, nst steps at a time: the
+// measurement runs nst and 2 nst steps behind and no instance stops inside
+// the window.
+bool steady(const lb_wave *h, int k, int nst)
 {
     const int64_t t = h->t;
-    const int nst = h->fused;
-    if (k % nst) return false;
     if (h->any_surf && (t < 2 * nst || h->meas != t - nst || h->red != t - 2 * nst)) return false;
     for (const InstDev &I : h->hinst) {
         const int64_t ms = I.max_steps;
@@ -767,12 +886,11 @@ bool steady(const lb_wave *h, int64_t k)
     return true;
 }
 
-// Replay k steady steps as one captured graph (captured once per launch
-// shape on a private stream, launched on the handle's stream).
-int replay_steps(lb_wave *h, int k)
+// Replay k steady steps, nst at a time, as one captured graph (captured once
+// per launch shape on a private stream, launched on the handle's stream).
+int replay_steps(lb_wave *h, int k, int nst)
 {
     const int64_t t = h->t;
-    const int nst = h->fused;
     const int na = active_prefix(h, t);
     const int n_red = h->any_surf ? prefix_alive(h, t - 2 * nst) : 0;
     const int n_sb = h->any_surf ? h->sb_first[prefix_alive(h, t - nst)] : 0;
@@ -795,7 +913,8 @@ int replay_steps(lb_wave *h, int k)
         a.n_sb = n_sb;
         a.sb_inst = h->d_sb_inst;
         a.sb_chunk = h->d_sb_chunk;
-        for (int j = 0; j < k; j += nst) emit_step(h, a, t + j, j, (j / nst) & 1, nst, h->cap_stream);
+        for (int j = 0; j < k; j += nst)
+            emit_step(h, a, t + j, j, (j / nst) & 1, nst, h->cap_stream);
         hipLaunchKernelGGL(advance_step_kernel, dim3(1), dim3(64), 0, h->cap_stream, h->d_t,
                            (int64_t)k, (int64_t)(k / nst));
         hipGraph_t graph = nullptr;
@@ -1051,40 +1170,31 @@ int lb_wave_create(const lb_wave_desc *descs, int32_t n_inst, void *dev_workspac
         host_blobs.push_back(std::move(blob));
         blob_off.push_back(L.off_sbtab);
     }
-    // two-step decomposition: row groups of R rows, 4 / nw groups per block,
-    // chunks of zchunk planes: the longest chunk (fewest re-read halo planes)
-    // that still fills the chip (two_step_min_blocks)
+    // march decomposition: row blocks, chunks of planes, strips
     {
-        const int R = two_step_rows(h->storage);
-        auto blocks_for = [&](int zc, std::vector<int> *b0) {
-            bool ok = (h->dim == 3);
-            if (b0) b0->assign(n_inst + 1, 0);
+        h->fused_ok = h->dim == 3 && !h->any_point;
+        bool fits = true;
+        for (const InstDev &I : h->hinst) {
+            const int groups = I.pitch > kMarchMaxPitch ? 1 : 4 / (I.pitch / 64);
+            if (I.xbc != LB_XBC_DRIVEN || I.ny % (rule_rows(h->storage) * groups)) h->fused_ok = false;
+            // lane offsets inside one plane are 32-bit byte counts
+            if ((int64_t)I.ny * I.pitch * (int64_t)elem_bytes(h->storage) > (int64_t)UINT32_MAX)
+                fits = false;
+        }
+        h->boxes.resize(n_inst);
+        h->blk0.assign(n_inst + 1, 0);
+        if (h->fused_ok && fits) {
+            h->march_waves = march_block_waves(h->hinst, h->storage);
+            const int zchunk = march_zchunk(h->hinst, h->storage, h->march_waves);
             int64_t total = 0;
-            for (int ii = 0; ii < n_inst; ++ii) {
-                const InstDev &I = h->hinst[ii];
-                int bpi = 0;
-                if (I.xbc == 0) {
-                    const int nsx = two_step_strips(I.nx, I.pitch);
-                    const int ng = nsx > 1 ? 1 : 4 / (I.pitch / 64);
-                    if (I.ny % (R * ng) == 0)
-                        bpi = (I.ny / (R * ng)) * ((I.nz + zc - 1) / zc) * nsx;
-                }
-                if (bpi == 0) ok = false;
-                total += bpi;
-                if (b0) (*b0)[ii + 1] = (*b0)[ii] + bpi;
+            for (int ii = 0; ii < n_inst && total < INT32_MAX / 2; ++ii) {
+                h->boxes[ii] = march_box(h->hinst[ii], h->storage, h->march_waves, zchunk);
+                total += h->boxes[ii].blocks();
+                h->blk0[ii + 1] = (int)std::min<int64_t>(total, INT32_MAX);
             }
-            return ok ? total : (int64_t)-1;
-        };
-        h->zchunk = two_step_zchunk(h->storage);
-        const int64_t min_blocks = two_step_min_blocks(h->storage);
-        while (h->zchunk > kMinZChunk && blocks_for(h->zchunk, nullptr) >= 0 &&
-               blocks_for(h->zchunk, nullptr) < min_blocks)
-            h->zchunk /= 2;
-        // (blocks_for also sizes blk0, which the segments below read in every case)
-        const bool fits = blocks_for(h->zchunk, &h->blk0) >= 0 &&
-                          h->blk0[n_inst] < std::numeric_limits<int32_t>::max() / 2;
-        h->fused_ok = fits && !h->any_point;
-        if (!h->fused_ok) std::fill(h->blk0.begin(), h->blk0.end(), 0);
+            h->march_ok = total < INT32_MAX / 2;
+        }
+        if (!h->march_ok) std::fill(h->blk0.begin(), h->blk0.end(), 0);
     }
     // segments: maximal runs of equal shape in internal order
     for (int ii = 0; ii < n_inst; ++ii) {
@@ -1102,11 +1212,8 @@ int lb_wave_create(const lb_wave_desc *descs, int32_t n_inst, void *dev_workspac
             sg.tpi = sg.xsegs * I.ny * I.nz;
             sg.blk0 = h->blk0[ii];
             sg.bpi = h->blk0[ii + 1] - h->blk0[ii];
-            sg.nsx = two_step_strips(I.nx, I.pitch);
-            if (h->fused_ok) {
-                const int ng = sg.nsx > 1 ? 1 : 4 / (I.pitch / 64);
-                sg.nyb = I.ny / (two_step_rows(h->storage) * ng);
-            }
+            sg.nsx = (int)h->boxes[ii].nsx;
+            sg.nyb = (int)h->boxes[ii].nyb;
             h->segs.push_back(sg);
         }
     }
@@ -1137,17 +1244,19 @@ int lb_wave_step_n(lb_wave *h, int64_t n_steps)
     if (h->nan_seen) return fail(LB_ENAN, "a previous force was not finite");
     int64_t left = n_steps;
     while (left > 0) {
-        const int k = h->graph_chunk;
+        // a replayed sequence holds launches of nst steps only: the chunk rounded down to them
+        const int most = most_steps(h), nst = std::min(most, std::max(h->graph_chunk, 1));
+        const int k = h->graph_chunk / nst * nst;
         int st;
-        if (k >= 2 && left >= k && steady(h, k)) {
-            st = replay_steps(h, k);
+        if (k >= 2 && left >= k && steady(h, k, nst)) {
+            st = replay_steps(h, k, nst);
             left -= k;
-        } else if (left >= 2 && can_fuse(h)) {
-            st = enqueue_step(h, 2);
-            left -= 2;
         } else {
-            st = enqueue_step(h, 1);
-            left -= 1;
+            // before the first replay launches of its size fill the measurement pipeline
+            int n = k >= 2 && left >= k ? nst : next_steps(left, most);
+            n = fuse_steps(h, n);
+            st = enqueue_step(h, n);
+            left -= n;
         }
         if (st != LB_OK) return st;
     }
@@ -1159,7 +1268,7 @@ int lb_wave_set_steps_per_launch(lb_wave *h, int32_t k)
     if (!h) return fail(LB_EINVAL, "handle is NULL");
     if (k != 1 && k != 2) return fail(LB_EINVAL, "steps per launch must be 1 or 2");
     if (k == 2 && !h->fused_ok)
-        return fail(LB_EINVAL, "two steps per launch need 3D instances with driven x sheets "
+        return fail(LB_EINVAL, "several steps per launch need 3D instances with driven x sheets "
                                "and ny a multiple of the row block");
     if (k != h->fused) drop_graphs(h);
     h->fused = k;
@@ -1170,6 +1279,13 @@ int lb_wave_get_steps_per_launch(const lb_wave *h, int32_t *k)
 {
     if (!h || !k) return fail(LB_EINVAL, "NULL argument");
     *k = h->fused;
+    return LB_OK;
+}
+
+int lb_wave_get_launch_steps(const lb_wave *h, int32_t *k)
+{
+    if (!h || !k) return fail(LB_EINVAL, "NULL argument");
+    *k = most_steps(h);
     return LB_OK;
 }
 
@@ -1399,9 +1515,11 @@ int lb_wave_autotune(lb_wave *h, int32_t n_trial, double *best_ms)
     double best = 1e300;
     int bv[4] = {1, 0, 0, 1};  // cells per lane, x mode, nontemporal, steps per launch
     const int xm_max = elem_bytes(h->storage) >= 4 ? 1 : 0;
-    const int trial = n_trial + (n_trial & 1);  // even, so two-step launches cover it
     auto time_it = [&](double *per) -> int {
-        int st = lb_wave_step_n(h, 2);  // warm-up
+        const int nst = most_steps(h);
+        const int whole = std::max(2, nst);  // even, or whole launches of three steps
+        const int trial = (n_trial + whole - 1) / whole * whole;
+        int st = lb_wave_step_n(h, whole);  // warm-up
         if (st) return st;
         HIP_TRY(hipEventRecord(e0, h->stream));
         st = lb_wave_step_n(h, trial);
