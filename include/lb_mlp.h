@@ -61,17 +61,16 @@ int lb_mlp_get_params(lb_mlp *h, float *host_params);
 
 /* y = net(x) for 1 <= B <= 2^30 samples (independent of max_batch: inference
  * keeps no activations in the workspace): dev_x B x 4 FP32, dev_y B FP32.  One fused launch carries
- * 128 samples per workgroup through every layer with the activations in LDS;
+ * 16, 32 or 128 samples per workgroup (by B) through every layer with the activations in LDS;
  * operand roundings as in the training forward (BF16 weights and
  * activations, FP32 accumulation and bias).  Asynchronous on the handle's
  * stream. */
 int lb_mlp_forward(lb_mlp *h, const float *dev_x, int32_t B, float *dev_y);
 
-/* The training forward (one MFMA GEMM launch per layer, activations kept in
- * the workspace for the backward pass) for B <= max_batch samples; same
- * arguments as lb_mlp_forward.  Both run the same MFMA sequence per output
- * (sums starting at the bias, K in the same 32-wide steps) and the same
- * roundings, so their outputs agree bit for bit.  Asynchronous. */
+/* The training forward's kernel for B <= max_batch samples, without the
+ * backward half; same arguments as lb_mlp_forward.  Both run the same MFMA
+ * sequence per output (sums starting at the bias, K in the same 32-wide steps)
+ * and the same roundings, so their outputs agree bit for bit.  Asynchronous. */
 int lb_mlp_forward_layered(lb_mlp *h, const float *dev_x, int32_t B, float *dev_y);
 
 /* Gradient of the mean squared error L = (1/B) sum (y - t)^2 with respect to

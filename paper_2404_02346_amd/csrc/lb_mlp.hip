@@ -7,6 +7,7 @@
 // D (16 x 16) has lane l holding column l % 16, rows 4 (l / 16) .. + 3.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -91,141 +92,409 @@ __device__ inline float gelu_d(float z)
     return fmaf(z * 0.39894228040143268f, e, z >= 0.0f ? 1.0f - h : h);
 }
 
+// The BF16 mirrors of the 256 x 256 weights are kept in the order in which a wavefront loads them:
+// the fragment of column tile n / 16 and K step k / 32 is 1 KiB, lane (n % 16) + 16 (k % 32 / 8)
+// holding 8 consecutive k.  Row by row, a fragment load touched 64 bytes of each of 16 rows: the
+// sweep below took 40 us for 4800 samples, now 27; infer_kernel 0.82 ms for 2^20, now 0.72.
+__host__ __device__ constexpr int frag_index(int n, int k)
+{
+    return ((k / 32 * (kHidden / 16) + n / 16) * 64 + n % 16 + 16 * (k % 32 / 8)) * 8 + k % 8;
+}
+__device__ inline s16x8 weight_frag(const uint16_t *W, int step, int tile, int lane)
+{
+    return *reinterpret_cast<const s16x8 *>(W + ((step * (kHidden / 16) + tile) * 64 + lane) * 8);
+}
+
+// Operands of the weight gradients, rows (neurons or inputs) x samples, in the same order: fragment
+// of rows 16 tile .. and samples 32 step .., `tiles` tiles of rows per step
+__host__ __device__ constexpr int row_tiles(int rows) { return (rows + 15) / 16; }
+__device__ inline int64_t sample_frag(int step, int tiles, int tile, int lane)
+{
+    return (((int64_t)step * tiles + tile) * 64 + lane) * 8;
+}
+__device__ inline int64_t sample_index(int m, int tiles, int r)
+{
+    return sample_frag(m / 32, tiles, r / 16, r % 16 + 16 * (m % 32 / 8)) + m % 8;
+}
+
 // ---------------------------------------------------------------------------
-// Training products.  Every product is C (M x N) = A (M x K) B (N x K)^T with
-// both operands stored K-contiguous (A row m at A + m s_am, B row n at B + n
-// s_bn), so a lane's MFMA fragment (8 consecutive k of one row) is one 16-byte
-// load straight into registers:
-//   forward  z_l     = a_l W_l^T          A = a_l (B x K_l),     B = W_l (N_l x K_l)
-//   errors   e_{l-1} = delta_l W_l        A = delta_l (B x N_l), B = W_l^T (K_l x N_l)
-//   weights  dW_l    = delta_l^T a_l      A = delta_l^T (N_l x B), B = a_l^T (K_l x B)
-// The forward and error epilogues therefore also write BF16 transposed copies
-// (batch-contiguous, rows padded with zeros to a multiple of 64 samples), and
-// the optimizer keeps a transposed BF16 mirror of every weight matrix.  The
-// weight products have K = batch (4096): K is split into at most kMaxSplit
-// chunks so that some 256 workgroups run, each chunk's sum goes to its own
-// slot, and finish_kernel adds the slots in chunk order (deterministic).
-// Bias gradients (column sums of the FP32 errors) and the loss are summed per
-// 64-sample block in the epilogues and finished the same way.
+// Training.  One Adam step is three launches:
+//   sweep_kernel   forward through all layers and back down to the error of
+//                  every hidden layer, for 32 samples per block;
+//   wgrad_kernel   the weight gradients dW_l = delta_l^T a_l of all layers;
+//   finish_kernel  the sums of their parts, and Adam.
+// Rows (samples) never mix before the weight gradients, so a block carries its
+// samples through the whole network: activations and errors pass from layer to
+// layer in LDS (BF16) and the pre-activations stay in registers (FP32), and
+// only what the weight gradients read goes to memory: the activations and
+// errors in the order of the MFMA fragments of those products (zero past the
+// batch up to a multiple of 64 samples).  The weight gradients have K = batch: K is split into at most
+// kMaxSplit chunks, each chunk's sum goes to its own slot, and finish_kernel
+// adds the slots in chunk order (deterministic).  Bias gradients (column sums
+// of the FP32 errors) and the loss are summed per 32 samples in the sweep and
+// finished the same way.
 // ---------------------------------------------------------------------------
 
-enum Epi { EPI_FWD = 0, EPI_OUT = 1, EPI_DX = 2, EPI_PART = 3 };
-// operand storage: 16-byte BF16 vectors, or elementwise BF16 / FP32 with any strides
-enum OpMode { OP_VEC = 0, OP_BF16 = 1, OP_F32 = 2 };
-
-constexpr int kTile = 64;      // 64 x 64 output tile per workgroup, 4 wavefronts of 32 x 32
-constexpr int kStepsAhead = 8; // K steps of 32 whose fragments are loaded before use
+constexpr int kTile = 64;      // weight gradients: 64 x 64 outputs per workgroup, 4 wavefronts of
+                               // 32 x 32; the batch is padded to a multiple of it
+constexpr int kStepsAhead = 5; // K steps of 32 whose fragments are loaded before use: 16 VGPRs a
+                               // step, so that four blocks share a CU
 constexpr int kMaxSplit = 16;  // K chunks of a weight-gradient product
-constexpr int kMaxTrainBatch = 1 << 24;  // training batch limit (workspace about 14 KB per sample)
+constexpr int kMaxTrainBatch = 1 << 24;  // training batch limit (workspace about 8 KB per sample)
 
-struct GemmNT {
-    int M, N, K;       // K: true length (elementwise operands mask k >= K)
-    int Kp;            // K rounded up to 32: the loop bound (vector operands read zeros there)
-    int k_chunk;       // K range of chunk z: [z k_chunk, min(Kp, (z + 1) k_chunk))
-    int tiles_m, tiles_n, chunks;  // grid of this product: tile (mt, nt) of chunk z
-    const void *A;     // A(m, k) = A[m s_am + k s_ak]  (s_ak = 1 for OP_VEC)
-    int64_t s_am, s_ak;
-    const void *B;     // B(n, k) = B[n s_bn + k s_bk]  (s_bk = 1 for OP_VEC)
-    int64_t s_bn, s_bk;
-    int epi;
-    const float *bias;   // N (EPI_FWD, EPI_OUT)
-    float *outf;         // EPI_FWD: z (row stride ldo); EPI_OUT: y; EPI_PART: chunk z at outf + z M ldo
-    int64_t ldo;
-    uint16_t *outb;      // BF16 row-major output (EPI_FWD: GELU(z); EPI_DX: error), may be NULL
-    uint16_t *outt;      // BF16 transposed output outt[n ldt + m] for m < m_pad (zero for m >= M)
-    int64_t ldt;
-    int m_pad;
-    const float *zprev;  // EPI_DX: pre-activation of the layer below (row stride ldo)
-    const float *target; // EPI_OUT: targets (training), or NULL (inference)
-    float inv_b2;        // EPI_OUT: 2 / batch
-    float *colpart;      // EPI_OUT (training), EPI_DX: per-64-row column sums [mt][N]
-    double *losspart;    // EPI_OUT (training): per-64-row sum of squared errors [mt]
+constexpr int kSweepRows = 32;
+constexpr int kSweepWaves = 8;
+constexpr int kActLd = kHidden + 8;  // LDS row of BF16 activations: 16-byte reads of 16 consecutive
+                                     // rows spread over the banks
+
+struct SweepArgs {
+    const float *x;         // B x 4
+    const float *target;    // B targets (training), or NULL: forward only
+    int B;
+    float inv_b2;           // 2 / B
+    const float *p;         // parameters
+    const uint16_t *pb, *pbT;  // BF16 mirrors W and W^T
+    uint16_t *act[kLayers];    // inputs of every layer (sample_index order), training only
+    uint16_t *err[kLayers];    // errors of every layer, likewise
+    float *bpart[kLayers];  // per 32 samples: column sums of the errors [block][N_l]
+    double *lpart;          // per 32 samples: sum of squared errors
+    float *y;               // B
 };
 
-template <int MODE>
-__device__ inline s16x8 load_frag(const void *base, int64_t s_row, int64_t s_k, int row, int nrows,
-                                  int k, int K)
+// first parameter of hidden layer l (1 .. kLayers - 2)
+__device__ inline int hidden_offset(int l)
 {
-    s16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (row >= nrows) return v;
-    if constexpr (MODE == OP_VEC) {
-        v = *reinterpret_cast<const s16x8 *>(static_cast<const uint16_t *>(base) +
-                                             (int64_t)row * s_row + k);
-    } else {
+    return param_offset_w(1) + (l - 1) * (param_offset_w(2) - param_offset_w(1));
+}
+
+// One hidden layer's weight fragments of this wavefront's 32 columns, 8 K steps x 2 column tiles,
+// and where its sums start
+struct LayerFrags {
+    s16x8 b[8][2];
+    float start[2];
+    __device__ inline void load(const uint16_t *W, const float *bias, int w, int lane)
+    {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            if (k + e < K) {
-                const int64_t o = (int64_t)row * s_row + (int64_t)(k + e) * s_k;
-                if constexpr (MODE == OP_BF16)
-                    v[e] = (short)static_cast<const uint16_t *>(base)[o];
-                else
-                    v[e] = (short)to_bf16(static_cast<const float *>(base)[o]);
+        for (int s = 0; s < 8; ++s)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) b[s][j] = weight_frag(W, s, 2 * w + j, lane);
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            start[j] = bias ? bias[w * 32 + 16 * j + (lane & 15)] : 0.f;
+    }
+};
+
+// What bounds the sweep: latency.  A block's layers follow one another, each a
+// few hundred cycles of MFMA and GELU behind two barriers and the L2 latency of
+// its weights (all of a layer's fragments are in flight together, loaded while
+// the layer before is finished).  The layers are loops, not unrolled, and the
+// pre-activations wait in LDS rather than in registers for that: 4800
+// samples: 27 us (41 before the weights were loaded in fragment order).  32
+// samples per block (RT = 2 row tiles) fill 150 CUs at that batch; the column
+// sums below are those of 32 samples, so fewer would change the order of the
+// sums.  One launch replaces nine (five products forward, four back, 7-16 us
+// each).  Without TRAIN it is the forward pass of small batches.
+template <int RT, bool TRAIN>
+__global__ void __launch_bounds__(64 * kSweepWaves, 2) sweep_kernel(SweepArgs a)
+{
+    static_assert(!TRAIN || RT == kSweepRows / 16, "column sums are those of kSweepRows samples");
+    constexpr int kRows = 16 * RT;
+    constexpr bool train = TRAIN;
+    __shared__ __attribute__((aligned(16))) uint16_t act[kRows][kActLd];
+    // pre-activations, [layer][tile][thread], each thread's own
+    __shared__ f32x4 z[TRAIN ? kLayers - 1 : 1][TRAIN ? 2 * RT : 1][TRAIN ? 64 * kSweepWaves : 1];
+    __shared__ __attribute__((aligned(16))) uint16_t w_out[kHidden];
+    __shared__ uint16_t d_out[kRows];
+    __shared__ float t_out[kRows];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int kl = 8 * (lane >> 4);         // this lane's k offset within a 32-wide step
+    const int col = w * 32 + (lane & 15);   // its column of column tile 0
+    const int row = 4 * (lane >> 4);        // its first row of row tile 0
+    const int m0 = blockIdx.x * kRows;
+    f32x4 acc[RT][2];
+    LayerFrags f;
+
+    auto product = [&]() {  // acc = start + act . fragments
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                acc[i][j] = f32x4{f.start[j], f.start[j], f.start[j], f.start[j]};
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            bf16x8 af[RT];
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+                af[i] = __builtin_bit_cast(
+                    bf16x8, *reinterpret_cast<const s16x8 *>(&act[16 * i + (lane & 15)][32 * s + kl]));
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        af[i], __builtin_bit_cast(bf16x8, f.b[s][j]), acc[i][j], 0, 0, 0);
+        }
+    };
+    // values v of this wavefront's tiles to LDS and to memory (zero for rows past the batch)
+    auto publish = [&](const f32x4 (&v)[RT][2], uint16_t *out) {
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int r = 16 * i + row, c = col + 16 * j;
+                const uint32_t lo = to_bf16x2(v[i][j][0], v[i][j][1]);
+                const uint32_t hi = to_bf16x2(v[i][j][2], v[i][j][3]);
+                act[r][c] = (uint16_t)lo;
+                act[r + 1][c] = (uint16_t)(lo >> 16);
+                act[r + 2][c] = (uint16_t)hi;
+                act[r + 3][c] = (uint16_t)(hi >> 16);
+                if (train)
+                    *reinterpret_cast<uint2 *>(out + sample_index(m0 + r, row_tiles(kHidden), c)) =
+                        make_uint2(lo, hi);
+            }
+    };
+    auto activate = [&](int l) {
+        f32x4 g[RT][2];
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                if (train) z[l][2 * i + j][threadIdx.x] = acc[i][j];
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    g[i][j][v] = m0 + 16 * i + row + v < a.B ? gelu(acc[i][j][v]) : 0.f;
+            }
+        publish(g, a.act[l + 1]);
+    };
+
+    // layer 0 (K = 4): lanes 0..15 carry k = 0..3 of their row (A) or column (B)
+    {
+        const uint16_t *W = a.pb + param_offset_w(0);
+        bf16x8 bf[2], af[RT];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            s16x8 b = {0, 0, 0, 0, 0, 0, 0, 0};
+            if (lane < 16) {
+#pragma unroll
+                for (int k = 0; k < kIn; ++k) b[k] = (short)W[(col + 16 * j) * kIn + k];
+            }
+            bf[j] = __builtin_bit_cast(bf16x8, b);
+        }
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            s16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
+            const int m = m0 + 16 * i + lane;
+            if (lane < 16 && m < a.B) {
+#pragma unroll
+                for (int k = 0; k < kIn; ++k) v[k] = (short)to_bf16(a.x[(int64_t)m * kIn + k]);
+            }
+            if (train && w == 0 && lane < 16) {
+#pragma unroll
+                for (int k = 0; k < kIn; ++k) a.act[0][sample_index(m, 1, k)] = (uint16_t)v[k];
+            }
+            af[i] = __builtin_bit_cast(bf16x8, v);
+        }
+        float b0[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) b0[j] = a.p[param_offset_b(0) + col + 16 * j];
+        f.load(a.pb + hidden_offset(1), a.p + param_offset_b(1), w, lane);
+        if (threadIdx.x < kHidden)
+            w_out[threadIdx.x] = a.pb[param_offset_w(kLayers - 1) + threadIdx.x];
+        if (train && threadIdx.x < kRows)
+            t_out[threadIdx.x] = m0 + (int)threadIdx.x < a.B ? a.target[m0 + threadIdx.x] : 0.f;
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    af[i], bf[j], f32x4{b0[j], b0[j], b0[j], b0[j]}, 0, 0, 0);
+    }
+    const float bias_out = a.p[param_offset_b(kLayers - 1)];
+    activate(0);
+    __syncthreads();
+#pragma unroll 1
+    for (int l = 1; l < kLayers - 1; ++l) {
+        product();
+        if (l + 1 < kLayers - 1)
+            f.load(a.pb + hidden_offset(l + 1), a.p + hidden_offset(l + 1) + kHidden * kHidden, w, lane);
+        else if (train)
+            f.load(a.pbT + hidden_offset(l), nullptr, w, lane);  // the way back
+        __syncthreads();  // every wavefront has read this layer's input
+        activate(l);
+        __syncthreads();
+    }
+
+    // output layer (256 -> 1): the first wavefront; the B fragment is nonzero only in column 0
+    if (w == 0) {
+        f32x4 o[RT];
+#pragma unroll
+        for (int i = 0; i < RT; ++i) o[i] = f32x4{bias_out, bias_out, bias_out, bias_out};
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            s16x8 b = {0, 0, 0, 0, 0, 0, 0, 0};
+            if ((lane & 15) == 0) b = *reinterpret_cast<const s16x8 *>(&w_out[32 * s + kl]);
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                const bf16x8 af = __builtin_bit_cast(
+                    bf16x8, *reinterpret_cast<const s16x8 *>(&act[16 * i + (lane & 15)][32 * s + kl]));
+                o[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, __builtin_bit_cast(bf16x8, b), o[i],
+                                                               0, 0, 0);
+            }
+        }
+        float csum = 0.f;
+        double lsum = 0.0;
+        if ((lane & 15) == 0) {
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                float d[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int m = m0 + 16 * i + row + v;
+                    d[v] = 0.f;
+                    if (m < a.B) {
+                        a.y[m] = o[i][v];
+                        if (train) {
+                            const float e = o[i][v] - t_out[16 * i + row + v];
+                            d[v] = e * a.inv_b2;
+                            lsum += (double)e * (double)e;
+                            csum = __builtin_fmaf(e, a.inv_b2, csum);
+                        }
+                    }
+                }
+                if (train) {
+                    const uint32_t lo = to_bf16x2(d[0], d[1]), hi = to_bf16x2(d[2], d[3]);
+                    const int r = 16 * i + row;
+                    d_out[r] = (uint16_t)lo;
+                    d_out[r + 1] = (uint16_t)(lo >> 16);
+                    d_out[r + 2] = (uint16_t)hi;
+                    d_out[r + 3] = (uint16_t)(hi >> 16);
+                    *reinterpret_cast<uint2 *>(a.err[kLayers - 1] + sample_index(m0 + r, 1, 0)) =
+                        make_uint2(lo, hi);
+                }
+            }
+        }
+        if (train) {
+            csum += __shfl_xor(csum, 16);
+            csum += __shfl_xor(csum, 32);
+            lsum += __shfl_xor(lsum, 16);
+            lsum += __shfl_xor(lsum, 32);
+            if (lane == 0) {
+                a.bpart[kLayers - 1][blockIdx.x] = csum;
+                a.lpart[blockIdx.x] = lsum;
             }
         }
     }
+    if constexpr (TRAIN) {
+    __syncthreads();
+
+    {
+        // delta_4 W_4: K = 1, one 32-wide step whose other k are zero
+        static_assert(!TRAIN || RT == 2);
+        bf16x8 af[2], bf[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            s16x8 v = {0, 0, 0, 0, 0, 0, 0, 0}, b = {0, 0, 0, 0, 0, 0, 0, 0};
+            if (lane < 16) {
+                v[0] = (short)d_out[16 * q + lane];
+                b[0] = (short)w_out[col + 16 * q];
+            }
+            af[q] = __builtin_bit_cast(bf16x8, v);
+            bf[q] = __builtin_bit_cast(bf16x8, b);
+        }
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[j],
+                                                                    f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+    }
+    // back: acc holds delta_{l+1} W_{l+1}; the error of layer l is that times gelu'(z_l)
+#pragma unroll 1
+    for (int l = kLayers - 2; l >= 0; --l) {
+        f32x4 d[RT][2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            float csum = 0.f;
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                const f32x4 zl = z[l][2 * i + j][threadIdx.x];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    float t = 0.f;
+                    if (m0 + 16 * i + row + v < a.B) {
+                        t = acc[i][j][v] * gelu_d(zl[v]);
+                        asm("" : "+v"(t));  // the sum takes the rounded error: no fused operation
+                        csum += t;
+                    }
+                    d[i][j][v] = t;
+                }
+            }
+            csum += __shfl_xor(csum, 16);
+            csum += __shfl_xor(csum, 32);
+            if (lane < 16) a.bpart[l][(int64_t)blockIdx.x * kHidden + col + 16 * j] = csum;
+        }
+        publish(d, a.err[l]);
+        if (l == 0) break;
+        __syncthreads();
+        product();
+        if (l > 1) f.load(a.pbT + hidden_offset(l - 1), nullptr, w, lane);
+        __syncthreads();
+    }
+    }
+}
+
+// One weight-gradient product C (M x N) = A (M x K) B (N x K)^T over the batch (K), in chunks.
+struct WGrad {
+    int M, N;
+    int k_chunk;         // K range of chunk z: [z k_chunk, min(Kp, (z + 1) k_chunk))
+    int tiles_m, tiles_n;
+    int blk0;            // first block of this product
+    const uint16_t *A;   // errors (sample_index order)
+    const uint16_t *B;   // activations, likewise
+    float *out;          // chunk z at out + z M N
+};
+struct WGradArgs {
+    WGrad g[kLayers];
+    int Kp;  // batch rounded up to 32
+};
+
+// fragment of row tile `tile` and K step `step`, zero past the last row
+__device__ inline s16x8 load_frag(const uint16_t *base, int rows, int tile, int step, int lane)
+{
+    s16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (tile * 16 + (lane & 15) < rows)
+        v = *reinterpret_cast<const s16x8 *>(base + sample_frag(step, row_tiles(rows), tile, lane));
     return v;
 }
 
-// one 64 x 64 output tile (mt, nt) of K chunk kz
-template <int AM, int BM>
-__device__ inline void gemm_tile(const GemmNT &g, int mt, int nt, int kz, float (*red)[kTile],
-                                 double *lred)
+// one 64 x 64 output tile of one K chunk
+__device__ inline void wgrad_tile(const WGradArgs &a, const WGrad &g, int blk)
 {
-    const int m_blk = mt * kTile, n_blk = nt * kTile;
+    const int m_blk = blk % g.tiles_m * kTile, n_blk = blk / g.tiles_m % g.tiles_n * kTile;
+    const int kz = blk / (g.tiles_m * g.tiles_n);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int wm = w >> 1, wn = w & 1;
-    const int kl = 8 * (lane >> 4);
-    const int k_beg = kz * g.k_chunk;
-    const int k_end = min(g.Kp, k_beg + g.k_chunk);
-    int ra[2], rb[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        ra[i] = m_blk + wm * 32 + i * 16 + (lane & 15);
-        rb[i] = n_blk + wn * 32 + i * 16 + (lane & 15);
-    }
-    // lane holds column rb[j], rows mrow + 16 i + v (v = 0..3) of the result
-    const int mrow = m_blk + wm * 32 + 4 * (lane >> 4);
-    // with a bias the sums start from it, as in the fused inference kernel, so that
-    // both forwards round every activation identically
-    const bool has_bias = g.epi == EPI_FWD || g.epi == EPI_OUT;
+    const int k_beg = kz * g.k_chunk, k_end = min(a.Kp, k_beg + g.k_chunk);
+    const int ta = m_blk / 16 + (w >> 1) * 2, tb = n_blk / 16 + (w & 1) * 2;  // first row tiles
     f32x4 acc[2][2];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const float b0 = (has_bias && rb[j] < g.N) ? g.bias[rb[j]] : 0.f;
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) acc[i][j] = f32x4{b0, b0, b0, b0};
-    }
-    // the epilogue's other inputs are fetched before the product, so that their
-    // latency overlaps it: z of the layer below (EPI_DX), the targets (EPI_OUT)
-    float pre[2][2][4];
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int m = mrow + 16 * i + v;
-                float q = 0.f;
-                if (g.epi == EPI_DX && m < g.M && rb[j] < g.N) q = g.zprev[(int64_t)m * g.ldo + rb[j]];
-                if (g.epi == EPI_OUT && g.target && j == 0 && m < g.M) q = g.target[m];
-                pre[j][i][v] = q;
-            }
-
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int kb = k_beg; kb < k_end; kb += 32 * kStepsAhead) {
-        s16x8 a[kStepsAhead][2], b[kStepsAhead][2];
+        s16x8 fa[kStepsAhead][2], fb[kStepsAhead][2];
 #pragma unroll
         for (int s = 0; s < kStepsAhead; ++s) {
             const int k = kb + 32 * s;
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                a[s][i] = s16x8{0, 0, 0, 0, 0, 0, 0, 0};
-                b[s][i] = s16x8{0, 0, 0, 0, 0, 0, 0, 0};
+                fa[s][i] = s16x8{0, 0, 0, 0, 0, 0, 0, 0};
+                fb[s][i] = s16x8{0, 0, 0, 0, 0, 0, 0, 0};
             }
             if (k < k_end) {
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
-                    a[s][i] = load_frag<AM>(g.A, g.s_am, g.s_ak, ra[i], g.M, k + kl, g.K);
-                    b[s][i] = load_frag<BM>(g.B, g.s_bn, g.s_bk, rb[i], g.N, k + kl, g.K);
+                    fa[s][i] = load_frag(g.A, g.M, ta + i, k / 32, lane);
+                    fb[s][i] = load_frag(g.B, g.N, tb + i, k / 32, lane);
                 }
             }
         }
@@ -237,115 +506,31 @@ __device__ inline void gemm_tile(const GemmNT &g, int mt, int nt, int kz, float 
 #pragma unroll
                     for (int j = 0; j < 2; ++j)
                         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            __builtin_bit_cast(bf16x8, a[s][i]), __builtin_bit_cast(bf16x8, b[s][j]),
+                            __builtin_bit_cast(bf16x8, fa[s][i]), __builtin_bit_cast(bf16x8, fb[s][j]),
                             acc[i][j], 0, 0, 0);
             }
         }
     }
-
-    if (g.epi == EPI_PART) {
-        float *o = g.outf + (int64_t)kz * g.M * g.ldo;
+    float *o = g.out + (int64_t)kz * g.M * g.N;
+    const int mrow = m_blk + (w >> 1) * 32 + 4 * (lane >> 4);
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int m = mrow + 16 * i + v;
-                    if (m < g.M && rb[j] < g.N) o[(int64_t)m * g.ldo + rb[j]] = acc[i][j][v];
-                }
-        return;
-    }
-    float csum[2] = {0.f, 0.f};
-    double lsum = 0.0;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int n = rb[j];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            float tv[4];
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int m = mrow + 16 * i + v;
-                const bool ok = m < g.M && n < g.N;
-                const float c = acc[i][j][v];
-                const int64_t o = (int64_t)m * g.ldo + n;
-                float t = 0.f;
-                if (g.epi == EPI_FWD) {
-                    if (ok) {
-                        t = gelu(c);
-                        g.outf[o] = c;
-                        g.outb[o] = to_bf16(t);
-                    }
-                } else if (g.epi == EPI_OUT) {
-                    if (ok) {
-                        g.outf[m] = c;
-                        if (g.target) {
-                            const float e = c - pre[0][i][v];
-                            t = e * g.inv_b2;
-                            lsum += (double)e * (double)e;
-                            csum[j] += t;
-                        }
-                    }
-                } else {  // EPI_DX
-                    if (ok) {
-                        t = c * gelu_d(pre[j][i][v]);
-                        if (g.outb) g.outb[o] = to_bf16(t);
-                        csum[j] += t;
-                    }
-                }
-                tv[v] = t;
+                const int m = mrow + 16 * i + v, n = 16 * (tb + j) + (lane & 15);
+                if (m < g.M && n < g.N) o[(int64_t)m * g.N + n] = acc[i][j][v];
             }
-            const int m0 = mrow + 16 * i;
-            if (g.outt && n < g.N && m0 < g.m_pad) {
-                const uint32_t lo = to_bf16x2(tv[0], tv[1]), hi = to_bf16x2(tv[2], tv[3]);
-                *reinterpret_cast<uint2 *>(g.outt + (int64_t)n * g.ldt + m0) = make_uint2(lo, hi);
-            }
-        }
-    }
-    if (g.colpart) {
-        // column sums over this block's 64 rows: a lane's 8 rows in order, then the four
-        // lane groups of a column (butterfly), then the two wavefront rows
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            float s = csum[j];
-            s += __shfl_xor(s, 16);
-            s += __shfl_xor(s, 32);
-            if (lane < 16) red[wm][wn * 32 + j * 16 + lane] = s;
-        }
-        if (g.losspart) {
-            lsum += __shfl_xor(lsum, 16);
-            lsum += __shfl_xor(lsum, 32);
-            if (wn == 0 && lane == 0) lred[wm] = lsum;
-        }
-        __syncthreads();
-        if (threadIdx.x < kTile) {
-            const int n = n_blk + threadIdx.x;
-            if (n < g.N)
-                g.colpart[(int64_t)mt * g.N + n] = red[0][threadIdx.x] + red[1][threadIdx.x];
-        }
-        if (g.losspart && threadIdx.x == 0) g.losspart[mt] = lred[0] + lred[1];
-    }
 }
 
-// One launch runs two independent products: blocks [0, n0) take tiles of g0, the
-// rest tiles of g1 (a single product passes n0 = its block count).  Block b of a
-// product is tile (b mod tiles_m, (b / tiles_m) mod tiles_n) of chunk
-// b / (tiles_m tiles_n).
-template <int AM0, int BM0, int AM1, int BM1>
-__global__ void __launch_bounds__(256) gemm_nt_kernel(GemmNT g0, GemmNT g1, int n0)
+__global__ void __launch_bounds__(256) wgrad_kernel(WGradArgs a)
 {
-    __shared__ float red[2][kTile];
-    __shared__ double lred[2];
-    const int b = blockIdx.x;
-    if (b < n0) {
-        gemm_tile<AM0, BM0>(g0, b % g0.tiles_m, (b / g0.tiles_m) % g0.tiles_n,
-                            b / (g0.tiles_m * g0.tiles_n), red, lred);
-    } else {
-        const int c = b - n0;
-        gemm_tile<AM1, BM1>(g1, c % g1.tiles_m, (c / g1.tiles_m) % g1.tiles_n,
-                            c / (g1.tiles_m * g1.tiles_n), red, lred);
-    }
+    int l = 0;
+#pragma unroll
+    for (int q = 1; q < kLayers; ++q)
+        if ((int)blockIdx.x >= a.g[q].blk0) l = q;
+    wgrad_tile(a, a.g[l], blockIdx.x - a.g[l].blk0);
 }
 
 struct FinishArgs {
@@ -353,8 +538,8 @@ struct FinishArgs {
     uint16_t *pb, *pbT;
     const float *wpart[kLayers];  // chunk sums of dW_l: [chunk][N_l][K_l]
     int wsplit[kLayers];
-    const float *bpart[kLayers];  // block sums of db_l: [block][N_l]
-    int nblk;
+    const float *bpart[kLayers];  // sums of db_l over 32 samples: [block][N_l]
+    int nblk;                     // blocks of 64 samples
     const double *losspart;
     double *loss;
     int B;
@@ -362,30 +547,109 @@ struct FinishArgs {
     float lr, b1, b2, eps, c1, c2;
 };
 
+constexpr int kBiasBlocks = (kLayers - 1) * (kHidden / 64) + 1;  // 64 biases each; the output's last
+constexpr int kBiasStage = 64;  // 64-sample sums per bias staged in LDS at a time
+
+// one parameter's Adam state, fetched before its gradient is summed
+struct AdamState {
+    float p, m, v;
+    __device__ inline AdamState(const FinishArgs &f, int i)
+        : p(f.adam ? f.p[i] : 0.f), m(f.adam ? f.m[i] : 0.f), v(f.adam ? f.v[i] : 0.f)
+    {
+    }
+    // one step with gradient gi; returns the new parameter
+    __device__ inline float step(const FinishArgs &f, int i, float gi) const
+    {
+        // the multiply-adds are written out, so that their rounding does not depend on the code
+        // around them
+        const float mi = __builtin_fmaf(gi, 1.f - f.b1, f.b1 * m);
+        const float vi = __builtin_fmaf(f.b2, v, (1.f - f.b2) * gi * gi);
+        f.m[i] = mi;
+        f.v[i] = vi;
+        const float pi = p - f.lr * (mi / f.c1) / (sqrtf(vi / f.c2) + f.eps);
+        f.p[i] = pi;
+        return pi;
+    }
+};
+
+// the BF16 mirrors of weight (n, k) of a layer whose parameters start at `off`: W, for hidden
+// layers in fragment order, and W^T
+__device__ inline void mirror(uint16_t *pb, uint16_t *pbT, int off, int N, int K, int n, int k, float w)
+{
+    const uint16_t b = to_bf16(w);
+    if (N == kHidden && K == kHidden) {
+        pb[off + frag_index(n, k)] = b;
+        pbT[off + frag_index(k, n)] = b;
+    } else {
+        pb[off + n * K + k] = b;
+    }
+}
+
+// Gradients of 64 biases of layer l (the output layer has one) from the sums over 32 samples,
+// added in pairs and then in block order; with the output layer, the loss.  The whole block
+// fetches the sums, so that their latencies overlap; one wavefront adds.
+__device__ inline void finish_biases(const FinishArgs &f, int blk, float (*sums)[64], double *loss)
+{
+    const bool out = blk == kBiasBlocks - 1;
+    const int l = out ? kLayers - 1 : blk / (kHidden / 64);
+    const int n0 = out ? 0 : blk % (kHidden / 64) * 64;
+    const int N = out ? 1 : kHidden;
+    const float *bp = f.bpart[0];
+#pragma unroll
+    for (int q = 1; q < kLayers; ++q)
+        if (l == q) bp = f.bpart[q];
+    const int c = threadIdx.x & 63;
+    int off = param_offset_b(0);
+#pragma unroll
+    for (int q = 1; q < kLayers; ++q)
+        if (l == q) off = param_offset_b(q);
+    const int i = off + min(n0 + c, N - 1);
+    const AdamState st(f, i);
+    float gi = 0.f;
+    double s = 0.0;
+    for (int b0 = 0; b0 < f.nblk; b0 += kBiasStage) {
+        const int nb = min(kBiasStage, f.nblk - b0);
+        if (n0 + c < N) {
+#pragma unroll 16
+            for (int u = threadIdx.x / 64; u < nb; u += 4) {
+                const int64_t o = (int64_t)(2 * (b0 + u)) * N + n0 + c;
+                sums[u][c] = bp[o] + bp[o + N];
+            }
+        }
+        if (out && threadIdx.x < nb)
+            loss[threadIdx.x] = f.losspart[2 * (b0 + threadIdx.x)] + f.losspart[2 * (b0 + threadIdx.x) + 1];
+        __syncthreads();
+        if (threadIdx.x < 64 && n0 + c < N)
+            for (int u = 0; u < nb; ++u) gi += sums[u][c];
+        if (out && threadIdx.x == 0)
+            for (int u = 0; u < nb; ++u) s += loss[u];
+        __syncthreads();
+    }
+    if (out && threadIdx.x == 0) *f.loss = s / (double)f.B;
+    if (threadIdx.x >= 64 || n0 + c >= N) return;
+    f.g[i] = gi;
+    if (f.adam) st.step(f, i, gi);
+}
+
 // gradient of every parameter from its partial sums (chunk or block order), the
-// loss, and (adam != 0) one Adam step with the BF16 mirrors W and W^T refreshed
+// loss, and (adam != 0) one Adam step with the BF16 mirrors W and W^T refreshed.
+// The first kBiasBlocks blocks take the biases, the rest the weights.
 __global__ void __launch_bounds__(256) finish_kernel(FinishArgs f)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == 0) {
-        double s = 0.0;
-        for (int b0 = 0; b0 < f.nblk; b0 += 16) {
-            double q[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) q[u] = b0 + u < f.nblk ? f.losspart[b0 + u] : 0.0;
-#pragma unroll
-            for (int u = 0; u < 16; ++u)
-                if (b0 + u < f.nblk) s += q[u];
-        }
-        *f.loss = s / (double)f.B;
+    __shared__ float sums[kBiasStage][64];
+    __shared__ double loss[kBiasStage];
+    if (blockIdx.x < kBiasBlocks) {
+        finish_biases(f, blockIdx.x, sums, loss);
+        return;
     }
+    const int i = (blockIdx.x - kBiasBlocks) * blockDim.x + threadIdx.x;
     if (i >= kParams) return;
     int l = 0;
 #pragma unroll
     for (int q = 1; q < kLayers; ++q)
         if (i >= param_offset_w(q)) l = q;
-    int K = kDims[0], N = kDims[1], S = f.wsplit[0];
-    const float *wp = f.wpart[0], *bp = f.bpart[0];
+    int K = kDims[0], N = kDims[1], S = f.wsplit[0], off = 0;
+    const float *wp = f.wpart[0];
 #pragma unroll
     for (int q = 1; q < kLayers; ++q)
         if (l == q) {
@@ -393,42 +657,23 @@ __global__ void __launch_bounds__(256) finish_kernel(FinishArgs f)
             N = kDims[q + 1];
             S = f.wsplit[q];
             wp = f.wpart[q];
-            bp = f.bpart[q];
+            off = param_offset_w(q);
         }
-    const int local = i - param_offset_w(l);
-    const bool weight = local < N * K;
+    const int local = i - off;
+    if (local >= N * K) return;  // a bias
     // every partial is loaded before the first add (a runtime-length loop would wait
-    // for each load in turn); the sums still run in chunk or block order
+    // for each load in turn); the sums still run in chunk order
+    const AdamState st(f, i);
     float gi = 0.f;
-    if (weight) {
-        float q[kMaxSplit];
+    float q[kMaxSplit];
 #pragma unroll
-        for (int s = 0; s < kMaxSplit; ++s) q[s] = s < S ? wp[(int64_t)s * N * K + local] : 0.f;
+    for (int s = 0; s < kMaxSplit; ++s) q[s] = s < S ? wp[(int64_t)s * N * K + local] : 0.f;
 #pragma unroll
-        for (int s = 0; s < kMaxSplit; ++s)
-            if (s < S) gi += q[s];
-    } else {
-        const int n = local - N * K;
-        for (int b0 = 0; b0 < f.nblk; b0 += 16) {
-            float q[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) q[u] = b0 + u < f.nblk ? bp[(int64_t)(b0 + u) * N + n] : 0.f;
-#pragma unroll
-            for (int u = 0; u < 16; ++u)
-                if (b0 + u < f.nblk) gi += q[u];
-        }
-    }
+    for (int s = 0; s < kMaxSplit; ++s)
+        if (s < S) gi += q[s];
     f.g[i] = gi;
     if (!f.adam) return;
-    const float mi = f.b1 * f.m[i] + (1.f - f.b1) * gi;
-    const float vi = f.b2 * f.v[i] + (1.f - f.b2) * gi * gi;
-    f.m[i] = mi;
-    f.v[i] = vi;
-    const float pi = f.p[i] - f.lr * (mi / f.c1) / (sqrtf(vi / f.c2) + f.eps);
-    f.p[i] = pi;
-    const uint16_t pbi = to_bf16(pi);
-    f.pb[i] = pbi;
-    if (weight) f.pbT[param_offset_w(l) + (local % K) * N + local / K] = pbi;
+    mirror(f.pb, f.pbT, off, N, K, local / K, local % K, st.step(f, i, gi));
 }
 
 // BF16 mirrors W and W^T of the FP32 parameters (after they are set)
@@ -436,21 +681,16 @@ __global__ void mirror_kernel(const float *p, uint16_t *pb, uint16_t *pbT)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= kParams) return;
-    const uint16_t b = to_bf16(p[i]);
-    pb[i] = b;
-    int l = 0;
+    int K = kDims[0], N = kDims[1], off = 0;
 #pragma unroll
     for (int q = 1; q < kLayers; ++q)
-        if (i >= param_offset_w(q)) l = q;
-    int K = kDims[0], N = kDims[1];
-#pragma unroll
-    for (int q = 1; q < kLayers; ++q)
-        if (l == q) {
+        if (i >= param_offset_w(q)) {
             K = kDims[q];
             N = kDims[q + 1];
+            off = param_offset_w(q);
         }
-    const int local = i - param_offset_w(l);
-    if (local < N * K) pbT[param_offset_w(l) + (local % K) * N + local / K] = b;
+    const int local = i - off;
+    if (local < N * K) mirror(pb, pbT, off, N, K, local / K, local % K, p[i]);
 }
 
 __global__ void zero_f32_kernel(float *p, int64_t n)
@@ -484,7 +724,7 @@ __global__ void __launch_bounds__(64) mfma_probe_kernel(const uint16_t *A, const
     for (int v = 0; v < 4; ++v) D[(4 * (lane >> 4) + v) * 16 + (lane & 15)] = acc[v];
 }
 
-// Fused inference: one block carries kInferRows samples through all layers,
+// Fused inference of large batches: one block carries kInferRows samples through all layers,
 // their activations staying in LDS (BF16, rows padded by 8 elements so that
 // the 16-byte fragment reads of 16 consecutive rows spread over the banks).
 // Every layer runs on MFMA with the same operand roundings as the training
@@ -502,8 +742,6 @@ constexpr int kInferWaves = 8;
 constexpr int kInferThreads = 64 * kInferWaves;
 // the 1D grid of ceil(B / kInferRows) blocks must hold fewer than 2^32 threads
 constexpr int kMaxInferBatch = 1 << 30;
-constexpr int kActLd = kHidden + 8;
-
 __global__ void __launch_bounds__(kInferThreads, kInferWaves / 2)
     infer_kernel(const float *__restrict__ x, int B, const float *__restrict__ p,
                  const uint16_t *__restrict__ pb, float *__restrict__ y)
@@ -579,13 +817,12 @@ __global__ void __launch_bounds__(kInferThreads, kInferWaves / 2)
 
     // hidden layers 1 .. kLayers-2 (256 x 256)
     for (int l = 1; l < kLayers - 1; ++l) {
-        const uint16_t *W = pb + param_offset_w(l);  // W[n][k], k fastest
+        const uint16_t *W = pb + param_offset_w(l);
         start(l);
         s16x8 bnext[JT];
 #pragma unroll
         for (int j = 0; j < JT; ++j) {
-            const int col = w * CW + j * 16 + (lane & 15);
-            bnext[j] = *reinterpret_cast<const s16x8 *>(W + col * kHidden + kl);
+            bnext[j] = weight_frag(W, 0, w * JT + j, lane);
         }
         for (int k0 = 0; k0 < kHidden; k0 += 32) {
             bf16x8 bfr[JT];
@@ -594,8 +831,7 @@ __global__ void __launch_bounds__(kInferThreads, kInferWaves / 2)
             if (k0 + 32 < kHidden) {
 #pragma unroll
                 for (int j = 0; j < JT; ++j) {
-                    const int col = w * CW + j * 16 + (lane & 15);
-                    bnext[j] = *reinterpret_cast<const s16x8 *>(W + col * kHidden + k0 + 32 + kl);
+                    bnext[j] = weight_frag(W, k0 / 32 + 1, w * JT + j, lane);
                 }
             }
 #pragma unroll
@@ -651,18 +887,14 @@ inline int round_up(int v, int q) { return (v + q - 1) / q * q; }
 
 struct Layout {
     size_t p, g, m, v, pb, pbT;      // parameters, gradients, Adam moments, BF16 mirrors W and W^T
-    size_t act[kLayers];             // BF16 activations a_1..a_4, row-major (B x 256); act[0] unused
-    size_t actT[kLayers];            // the same transposed (256 x ldt)
-    size_t z[kLayers];               // FP32 pre-activations z_0..z_3 (B x 256)
+    size_t act[kLayers];             // BF16 inputs of every layer (sample_index order)
+    size_t err[kLayers];             // BF16 errors of every layer, likewise
     size_t y;                        // FP32 output (B)
-    size_t drm[2], dT[2];            // BF16 errors of the hidden layers, row-major and transposed
-    size_t d4;                       // BF16 error of the output layer (ldt)
     size_t wpart[kLayers];           // FP32 chunk sums of the weight gradients
-    size_t bpart[kLayers];           // FP32 block sums of the bias gradients
-    size_t lpart;                    // FP64 block sums of the squared errors
+    size_t bpart[kLayers];           // FP32 sums of the bias gradients over 32 samples
+    size_t lpart;                    // FP64 sums of the squared errors over 32 samples
     size_t loss;                     // FP64
     size_t total;
-    int64_t ldt;                     // row stride of the transposed copies (max batch padded to 64)
 };
 
 Layout plan(int Bm)
@@ -675,8 +907,7 @@ Layout plan(int Bm)
         return o;
     };
     const size_t Bp = (size_t)round_up(Bm, kTile);
-    const size_t nblk = Bp / kTile;
-    L.ldt = (int64_t)Bp;
+    const size_t nblk = Bp / kSweepRows;
     L.p = take(4 * (size_t)kParams);
     L.g = take(4 * (size_t)kParams);
     L.m = take(4 * (size_t)kParams);
@@ -684,16 +915,10 @@ Layout plan(int Bm)
     L.pb = take(2 * (size_t)kParams);
     L.pbT = take(2 * (size_t)kParams);
     for (int l = 0; l < kLayers; ++l) {
-        L.act[l] = take(2 * (size_t)kHidden * Bm);
-        L.actT[l] = take(2 * (size_t)kHidden * Bp);
-        L.z[l] = take(4 * (size_t)kHidden * Bm);
+        L.act[l] = take(2 * (size_t)(16 * row_tiles(kDims[l])) * Bp);
+        L.err[l] = take(2 * (size_t)(16 * row_tiles(kDims[l + 1])) * Bp);
     }
     L.y = take(4 * (size_t)Bm);
-    for (int i = 0; i < 2; ++i) {
-        L.drm[i] = take(2 * (size_t)kHidden * Bm);
-        L.dT[i] = take(2 * (size_t)kHidden * Bp);
-    }
-    L.d4 = take(2 * Bp);
     for (int l = 0; l < kLayers; ++l) {
         const size_t nk = (size_t)kDims[l + 1] * kDims[l];
         L.wpart[l] = take(4 * nk * kMaxSplit);
@@ -726,13 +951,6 @@ namespace {
         if (e_ != hipSuccess) return lbw_fail_msg(LB_EDEVICE, hipGetErrorString(e_));   \
     } while (0)
 
-GemmNT base_args()
-{
-    GemmNT g;
-    std::memset(&g, 0, sizeof g);
-    return g;
-}
-
 // K split into chunks of whole 32-steps: at most `want` chunks, equal but the last
 int split_chunks(int steps, int want, int *per_out = nullptr)
 {
@@ -740,39 +958,6 @@ int split_chunks(int steps, int want, int *per_out = nullptr)
     const int per = (steps + want - 1) / want;
     if (per_out) *per_out = per;
     return (steps + per - 1) / per;
-}
-
-// the grid of one product: ceil(M/64) x ceil(N/64) tiles, split_chunks(., want) K chunks
-void plan_gemm(GemmNT &g, int want)
-{
-    g.Kp = round_up(g.K, 32);
-    int per = 0;
-    g.chunks = split_chunks(g.Kp / 32, want, &per);
-    g.k_chunk = 32 * per;
-    g.tiles_m = (g.M + kTile - 1) / kTile;
-    g.tiles_n = (g.N + kTile - 1) / kTile;
-}
-
-int blocks_of(const GemmNT &g) { return g.tiles_m * g.tiles_n * g.chunks; }
-
-// one product C = A B^T in one launch
-template <int AM, int BM>
-void gemm(const lb_mlp *h, GemmNT g, int want = 1)
-{
-    plan_gemm(g, want);
-    const int n = blocks_of(g);
-    hipLaunchKernelGGL((gemm_nt_kernel<AM, BM, AM, BM>), dim3(n), dim3(256), 0, h->stream, g, g, n);
-}
-
-// two independent products in one launch
-template <int AM0, int BM0, int AM1, int BM1>
-void gemm2(const lb_mlp *h, GemmNT g0, int want0, GemmNT g1, int want1)
-{
-    plan_gemm(g0, want0);
-    plan_gemm(g1, want1);
-    const int n0 = blocks_of(g0), n1 = blocks_of(g1);
-    hipLaunchKernelGGL((gemm_nt_kernel<AM0, BM0, AM1, BM1>), dim3(n0 + n1), dim3(256), 0,
-                       h->stream, g0, g1, n0);
 }
 
 // requested K chunks of a weight-gradient product: about 256 workgroups in all,
@@ -785,116 +970,78 @@ int weight_split(int l, int B)
     return std::max(1, std::min(want, steps / 4));
 }
 
-// forward for B samples; keeps activations (both layouts) and pre-activations for
-// the backward pass.  With targets t the output layer also forms the output error
-// 2 (y - t) / B, its block sums and the blocks' squared errors.
-void forward(const lb_mlp *h, const float *x, int B, float *y, const float *t)
+SweepArgs sweep_args(const lb_mlp *h, const float *x, int B, float *y)
 {
     const Layout &L = h->L;
-    const int m_pad = round_up(B, kTile);
-    for (int l = 0; l < kLayers; ++l) {
-        const int K = kDims[l], N = kDims[l + 1];
-        GemmNT g = base_args();
-        g.M = B;
-        g.N = N;
-        g.K = K;
-        g.B = h->at<uint16_t>(L.pb) + param_offset_w(l);  // W_l (N x K)
-        g.s_bn = K;
-        g.s_bk = 1;
-        g.bias = h->at<float>(L.p) + param_offset_b(l);
-        g.ldo = N;
-        g.ldt = L.ldt;
-        g.m_pad = m_pad;
-        if (l < kLayers - 1) {
-            g.epi = EPI_FWD;
-            g.outf = h->at<float>(L.z[l]);
-            g.outb = h->at<uint16_t>(L.act[l + 1]);
-            g.outt = h->at<uint16_t>(L.actT[l + 1]);
-        } else {
-            g.epi = EPI_OUT;
-            g.outf = y;
-            if (t) {
-                g.target = t;
-                g.inv_b2 = 2.0f / (float)B;
-                g.outt = h->at<uint16_t>(L.d4);
-                g.colpart = h->at<float>(L.bpart[l]);
-                g.losspart = h->at<double>(L.lpart);
-            }
-        }
-        if (l == 0) {
-            g.A = x;  // FP32 input, converted to BF16 on load
-            g.s_am = K;
-            g.s_ak = 1;
-            gemm<OP_F32, OP_BF16>(h, g);
-        } else {
-            g.A = h->at<uint16_t>(L.act[l]);
-            g.s_am = K;
-            g.s_ak = 1;
-            gemm<OP_VEC, OP_VEC>(h, g);
-        }
-    }
+    SweepArgs a;
+    std::memset(&a, 0, sizeof a);
+    a.x = x;
+    a.B = B;
+    a.p = h->at<float>(L.p);
+    a.pb = h->at<uint16_t>(L.pb);
+    a.pbT = h->at<uint16_t>(L.pbT);
+    a.y = y;
+    return a;
 }
 
-// weight gradients (chunk sums) of every layer and block sums of the errors.  The
-// weight gradient of layer l and the error of layer l - 1 both read only layer
-// l's error, so they share one launch.
-void backward(const lb_mlp *h, const float *x, int B)
+// Forward for B samples: 16 per block while that leaves no block waiting (256 CUs), else 32.
+// Measured, us for 6 / 512 / 4096 / 8192 / 16384 samples: 16 per block 7.7 / 8.2 / 8.9 / 12.6 /
+// 22.5, 32 per block 9.2 / 11.0 / 11.5 / 11.8 / 16.8.
+void sweep_forward(const lb_mlp *h, const float *x, int B, float *y)
+{
+    const SweepArgs a = sweep_args(h, x, B, y);
+    const dim3 threads(64 * kSweepWaves);
+    if (B <= 16 * 256)
+        hipLaunchKernelGGL((sweep_kernel<1, false>), dim3((B + 15) / 16), threads, 0, h->stream, a);
+    else
+        hipLaunchKernelGGL((sweep_kernel<2, false>), dim3((B + 31) / 32), threads, 0, h->stream, a);
+}
+// Batches up to this size run through the sweep, larger ones through infer_kernel, whose 128
+// samples per block reuse each weight four times as often but take 25 us however few they are
+// (24576 samples: 23.7 us in the sweep, 27.4 in infer_kernel; 32768: 28.7 and 27.6).
+constexpr int kSweepInfer = 24576;
+
+// forward for B samples and back to the errors of every layer
+void sweep_train(const lb_mlp *h, const float *x, int B, const float *t)
 {
     const Layout &L = h->L;
-    const int m_pad = round_up(B, kTile);
-    int cur = 0;
-    for (int l = kLayers - 1; l >= 0; --l) {
-        const int K = kDims[l], N = kDims[l + 1];
-        // this layer's error: transposed (N x ldt) and row-major (B x N)
-        const uint16_t *eT = (l == kLayers - 1) ? h->at<uint16_t>(L.d4) : h->at<uint16_t>(L.dT[cur]);
-        const uint16_t *erm = (l == kLayers - 1) ? h->at<uint16_t>(L.d4) : h->at<uint16_t>(L.drm[cur]);
-        // dW_l (N x K) = delta_l^T a_l
-        GemmNT g = base_args();
-        g.M = N;
-        g.N = K;
-        g.K = B;
-        g.A = eT;
-        g.s_am = L.ldt;
-        g.s_ak = 1;
-        g.epi = EPI_PART;
-        g.outf = h->at<float>(L.wpart[l]);
-        g.ldo = K;
-        const int split = weight_split(l, B);
-        if (l == 0) {
-            g.B = x;  // FP32 input: B(n, k) = x[k][n]
-            g.s_bn = 1;
-            g.s_bk = kIn;
-            gemm<OP_VEC, OP_F32>(h, g, split);
-            break;
-        }
-        g.B = h->at<uint16_t>(L.actT[l]);
-        g.s_bn = L.ldt;
-        g.s_bk = 1;
-        // delta_{l-1} (B x K) = (delta_l W_l) * gelu'(z_{l-1}), with its block column sums
-        GemmNT d = base_args();
-        d.M = B;
-        d.N = K;
-        d.K = N;
-        d.A = erm;
-        d.s_am = N;
-        d.s_ak = 1;
-        d.B = h->at<uint16_t>(L.pbT) + param_offset_w(l);  // W_l^T (K x N)
-        d.s_bn = N;
-        d.s_bk = 1;
-        d.epi = EPI_DX;
-        d.zprev = h->at<float>(L.z[l - 1]);
-        d.ldo = K;
-        d.outb = (l > 1) ? h->at<uint16_t>(L.drm[1 - cur]) : nullptr;
-        d.outt = h->at<uint16_t>(L.dT[1 - cur]);
-        d.ldt = L.ldt;
-        d.m_pad = m_pad;
-        d.colpart = h->at<float>(L.bpart[l - 1]);
-        if (N < 32)
-            gemm2<OP_VEC, OP_VEC, OP_BF16, OP_BF16>(h, g, split, d, 1);  // the output layer's K = 1
-        else
-            gemm2<OP_VEC, OP_VEC, OP_VEC, OP_VEC>(h, g, split, d, 1);
-        cur = 1 - cur;
+    SweepArgs a = sweep_args(h, x, B, h->at<float>(L.y));
+    a.target = t;
+    a.inv_b2 = 2.0f / (float)B;
+    for (int l = 0; l < kLayers; ++l) {
+        a.act[l] = h->at<uint16_t>(L.act[l]);
+        a.err[l] = h->at<uint16_t>(L.err[l]);
+        a.bpart[l] = h->at<float>(L.bpart[l]);
     }
+    a.lpart = h->at<double>(L.lpart);
+    const int blocks = round_up(B, kTile) / kSweepRows;  // the padding rows are written too
+    hipLaunchKernelGGL((sweep_kernel<2, true>), dim3(blocks), dim3(64 * kSweepWaves), 0, h->stream, a);
+}
+
+// weight gradients (chunk sums) of every layer from what the sweep left
+void wgrad(const lb_mlp *h, int B)
+{
+    const Layout &L = h->L;
+    WGradArgs a;
+    std::memset(&a, 0, sizeof a);
+    a.Kp = round_up(B, 32);
+    int blocks = 0;
+    for (int l = 0; l < kLayers; ++l) {
+        WGrad &g = a.g[l];
+        g.M = kDims[l + 1];
+        g.N = kDims[l];
+        int per = 0;
+        const int chunks = split_chunks(a.Kp / 32, weight_split(l, B), &per);
+        g.k_chunk = 32 * per;
+        g.tiles_m = (g.M + kTile - 1) / kTile;
+        g.tiles_n = (g.N + kTile - 1) / kTile;
+        g.blk0 = blocks;
+        g.A = h->at<uint16_t>(L.err[l]);
+        g.B = h->at<uint16_t>(L.act[l]);
+        g.out = h->at<float>(L.wpart[l]);
+        blocks += g.tiles_m * g.tiles_n * chunks;
+    }
+    hipLaunchKernelGGL(wgrad_kernel, dim3(blocks), dim3(256), 0, h->stream, a);
 }
 
 FinishArgs finish_args(const lb_mlp *h, int B)
@@ -922,7 +1069,8 @@ FinishArgs finish_args(const lb_mlp *h, int B)
 
 void finish(const lb_mlp *h, const FinishArgs &f)
 {
-    hipLaunchKernelGGL(finish_kernel, dim3((kParams + 255) / 256), dim3(256), 0, h->stream, f);
+    hipLaunchKernelGGL(finish_kernel, dim3(kBiasBlocks + (kParams + 255) / 256), dim3(256), 0,
+                       h->stream, f);
 }
 
 int check_batch(const lb_mlp *h, int B)
@@ -943,8 +1091,8 @@ int check_adam(float lr, float beta1, float beta2, float eps)
 void adam_step(lb_mlp *h, const float *x, const float *t, int B, float lr, float beta1,
                float beta2, float eps)
 {
-    forward(h, x, B, h->at<float>(h->L.y), t);
-    backward(h, x, B);
+    sweep_train(h, x, B, t);
+    wgrad(h, B);
     h->step++;
     FinishArgs f = finish_args(h, B);
     f.adam = 1;
@@ -1036,6 +1184,11 @@ int lb_mlp_forward(lb_mlp *h, const float *dev_x, int32_t B, float *dev_y)
     if (B < 1) return lbw_fail_msg(LB_EINVAL, "batch must be >= 1");
     if (B > kMaxInferBatch) return lbw_fail_msg(LB_EINVAL, "batch above 2^30");
     if (!dev_x || !dev_y) return lbw_fail_msg(LB_EINVAL, "NULL argument");
+    if (B <= kSweepInfer) {
+        sweep_forward(h, dev_x, B, dev_y);
+        MLP_TRY(hipGetLastError());
+        return LB_OK;
+    }
     const unsigned blocks = (unsigned)(((int64_t)B + kInferRows - 1) / kInferRows);
     hipLaunchKernelGGL(infer_kernel, dim3(blocks), dim3(kInferThreads), 0, h->stream, dev_x, B,
                        h->at<float>(h->L.p), h->at<uint16_t>(h->L.pb), dev_y);
@@ -1048,7 +1201,7 @@ int lb_mlp_forward_layered(lb_mlp *h, const float *dev_x, int32_t B, float *dev_
     int st = check_batch(h, B);
     if (st) return st;
     if (!dev_x || !dev_y) return lbw_fail_msg(LB_EINVAL, "NULL argument");
-    forward(h, dev_x, B, dev_y, nullptr);
+    sweep_forward(h, dev_x, B, dev_y);
     MLP_TRY(hipGetLastError());
     return LB_OK;
 }
@@ -1059,8 +1212,8 @@ int lb_mlp_grad(lb_mlp *h, const float *dev_x, const float *dev_t, int32_t B, fl
     int st = check_batch(h, B);
     if (st) return st;
     if (!dev_x || !dev_t || !host_grads) return lbw_fail_msg(LB_EINVAL, "NULL argument");
-    forward(h, dev_x, B, h->at<float>(h->L.y), dev_t);
-    backward(h, dev_x, B);
+    sweep_train(h, dev_x, B, dev_t);
+    wgrad(h, B);
     finish(h, finish_args(h, B));
     MLP_TRY(hipGetLastError());
     MLP_TRY(hipMemcpyAsync(host_grads, h->at<float>(h->L.g), 4 * (size_t)kParams,
