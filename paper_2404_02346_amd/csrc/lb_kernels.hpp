@@ -1235,87 +1235,132 @@ __global__ void __launch_bounds__(256) copy_kernel(const word16 *__restrict__ sr
 
 // ---------------------------------------------------------------------------
 // Empty driven cavity: the x-only field of the empty box is the 3-population
-// 1D lattice (rest weight 1 - c0^2, moving weights c0^2/2), here run by one
-// workgroup with the lattice in registers and the +/- populations exchanged
-// through LDS.  Accumulates sum rho cos(w t) and sum rho sin(w t) per cell
-// over the last n_fit steps.
+// 1D lattice (rest weight 1 - c0^2, moving weights c0^2/2), run by one
+// workgroup with the lattice in registers, CPL cells to a lane.  Accumulates
+// sum rho cos(w t) and sum rho sin(w t) per cell over the last n_fit steps.
+//
+// What bounds it: the chain of one step after another (15360 for 30 periods of
+// 256 cells), so a step has no barrier, no LDS access and no branch per cell:
+//  * up to 64 CPL cells one wavefront does it all, the moving populations
+//    passing from lane to lane in registers.  Wider boxes take a wavefront per
+//    kCavOwn cells, each also computing kCavHalo cells on either side, and the
+//    wavefronts exchange their cells through LDS every kCavHalo steps;
+//  * bulk, wall and padding cells share one rule with per-cell coefficients,
+//    out = a rho + b f with a = 0 on the walls (b = Phi there, -1 in the bulk)
+//    and both 0 in the padding, which so stays empty; the added product is exact;
+//  * the drive's sines are evaluated 64 steps at a time, one per lane.
+// ns per step for 64 / 128 / 256 / 300 / 1000 / 2048 cells: 100 / 119 / 158 / 181 / 289 / 406
+// (602 / 601 / 597 / 625 / 707 / 826 with 1024 threads, two barriers a step and a sine per thread).
 // ---------------------------------------------------------------------------
-constexpr int kCavThreads = 1024;
 constexpr int kCavMaxNx = 2048;
-constexpr int kCavPer = kCavMaxNx / kCavThreads;
+constexpr int kCavHalo = 16;                      // divides 64
+constexpr int kCavOwn = 64 * 4 - 2 * kCavHalo;    // CPL = 4
+constexpr int kCavMaxWaves = (kCavMaxNx + kCavOwn - 1) / kCavOwn;
 
-__global__ void __launch_bounds__(kCavThreads)
+// the value v of lane k
+__device__ inline double lane_value(double v, int k)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), k),
+                            __builtin_amdgcn_readlane(__double2loint(v), k));
+}
+
+template <int CPL, bool MANY>
+__global__ void __launch_bounds__(MANY ? 64 * kCavMaxWaves : 64)
 cavity_kernel(int nx, double c0sq, double omega, double rho_a, double phi, int64_t n_total,
               int64_t n_fit, double *lockin /* 2*nx: cos sums, sin sums */)
 {
-    __shared__ double gp[kCavMaxNx];
-    __shared__ double gm[kCavMaxNx];
-    double g0[kCavPer], sc[kCavPer], ss[kCavPer];
-    double np_[kCavPer], nm_[kCavPer];
+    static_assert(!MANY || CPL == 4, "kCavOwn is for 4 cells to a lane");
+    __shared__ double cells[MANY ? 3 : 1][MANY ? kCavMaxNx : 1];
+    const int lane = threadIdx.x & 63, w = wave_uniform(threadIdx.x >> 6);
+    const int x0 = (MANY ? w * kCavOwn - kCavHalo : 0) + lane * CPL;  // its first cell
+    double g0[CPL], np[CPL], nm[CPL], sc[CPL], ss[CPL];
+    double a0[CPL], ac[CPL], b[CPL];
 #pragma unroll
-    for (int j = 0; j < kCavPer; ++j) {
-        g0[j] = 0.0;
-        sc[j] = 0.0;
-        ss[j] = 0.0;
-        np_[j] = 0.0;  // post-collision +x population of the cell
-        nm_[j] = 0.0;  // post-collision -x population of the cell
+    for (int c = 0; c < CPL; ++c) {
+        const int x = x0 + c;
+        g0[c] = np[c] = nm[c] = sc[c] = ss[c] = 0.0;
+        const bool in = x >= 0 && x < nx, wall = x == 0 || x == nx - 1;
+        a0[c] = in && !wall ? 2.0 * (1.0 - c0sq) : 0.0;
+        ac[c] = in && !wall ? c0sq : 0.0;
+        b[c] = !in ? 0.0 : wall ? phi : -1.0;
     }
-    for (int64_t t = 0; t < n_total; ++t) {
-        // publish last step's post-collision moving populations
+    const double rest = 1.0 - c0sq;
+    constexpr int kSrc = 1 % CPL;  // the source is x = 1: this cell of one lane
+    const bool src = x0 + kSrc == 1;
+    auto own = [&](int x) {
+        return x >= 0 && x < nx && (!MANY || (x >= w * kCavOwn && x < (w + 1) * kCavOwn));
+    };
+    for (int64_t t0 = 0; t0 < n_total; t0 += 64) {
+        const double arg = omega * (double)(t0 + lane);
+        const double rs_all = rho_a * sin(arg);
+        double cw_all = 0.0, sw_all = 0.0;
+        if (t0 + 64 > n_total - n_fit) sincos(arg, &sw_all, &cw_all);
+        const int n = (int)min((int64_t)64, n_total - t0);
+#pragma unroll 1
+        for (int k0 = 0; k0 < n; k0 += MANY ? kCavHalo : 64) {
+            if (MANY) {  // every wavefront's own cells to the others' halos
+                __syncthreads();
 #pragma unroll
-        for (int j = 0; j < kCavPer; ++j) {
-            const int x = threadIdx.x + j * kCavThreads;
-            if (x < nx) {
-                gp[x] = np_[j];
-                gm[x] = nm_[j];
+                for (int c = 0; c < CPL; ++c)
+                    if (own(x0 + c)) {
+                        cells[0][x0 + c] = g0[c];
+                        cells[1][x0 + c] = np[c];
+                        cells[2][x0 + c] = nm[c];
+                    }
+                __syncthreads();
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) {
+                    const int x = x0 + c;
+                    if (x >= 0 && x < nx && !own(x)) {
+                        g0[c] = cells[0][x];
+                        np[c] = cells[1][x];
+                        nm[c] = cells[2][x];
+                    }
+                }
+            }
+            const int k1 = MANY ? min(n, k0 + kCavHalo) : n;
+#pragma unroll 1
+            for (int k = k0; k < k1; ++k) {
+                double ap[CPL], am[CPL], rho[CPL];
+                ap[0] = lane_shift<true>(0.0, np[CPL - 1]);
+                am[CPL - 1] = lane_shift<false>(0.0, nm[0]);
+#pragma unroll
+                for (int c = 1; c < CPL; ++c) {
+                    ap[c] = np[c - 1];
+                    am[c - 1] = nm[c];
+                }
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) rho[c] = g0[c] + ap[c] + am[c];
+                if (t0 + k >= n_total - n_fit) {
+                    const double cw = lane_value(cw_all, k), sw = lane_value(sw_all, k);
+#pragma unroll
+                    for (int c = 0; c < CPL; ++c) {
+                        sc[c] = mul_add(rho[c], cw, sc[c]);
+                        ss[c] = mul_add(rho[c], sw, ss[c]);
+                    }
+                }
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) {
+                    g0[c] = mul_add(a0[c], rho[c], b[c] * g0[c]);
+                    np[c] = mul_add(ac[c], rho[c], b[c] * am[c]);
+                    nm[c] = mul_add(ac[c], rho[c], b[c] * ap[c]);
+                }
+                const double rs = lane_value(rs_all, k);
+                const double J = ap[kSrc] - am[kSrc];
+                const double s0 = rs * rest;
+                const double sp = 0.5 * mul_add(c0sq, rs, J), sm = 0.5 * mul_add(c0sq, rs, -J);
+                g0[kSrc] = src ? s0 : g0[kSrc];
+                np[kSrc] = src ? sp : np[kSrc];
+                nm[kSrc] = src ? sm : nm[kSrc];
             }
         }
-        __syncthreads();
-        double ap[kCavPer], am[kCavPer];
-#pragma unroll
-        for (int j = 0; j < kCavPer; ++j) {
-            const int x = threadIdx.x + j * kCavThreads;
-            ap[j] = (x < nx && x > 0) ? gp[x - 1] : 0.0;
-            am[j] = (x < nx - 1) ? gm[x + 1] : 0.0;
-        }
-        __syncthreads();
-        const bool fit = t >= n_total - n_fit;
-        double cw = 0.0, sw = 0.0;
-        if (fit) sincos(omega * (double)t, &sw, &cw);
-        const double rs = rho_a * sin(omega * (double)t);
-#pragma unroll
-        for (int j = 0; j < kCavPer; ++j) {
-            const int x = threadIdx.x + j * kCavThreads;
-            if (x >= nx) continue;
-            const double rho = g0[j] + ap[j] + am[j];
-            if (fit) {
-                sc[j] += rho * cw;
-                ss[j] += rho * sw;
-            }
-            if (x == 0 || x == nx - 1) {
-                g0[j] = phi * g0[j];
-                np_[j] = phi * am[j];
-                nm_[j] = phi * ap[j];
-            } else if (x == 1) {
-                const double J = ap[j] - am[j];
-                g0[j] = rs * (1.0 - c0sq);
-                np_[j] = 0.5 * (c0sq * rs + J);
-                nm_[j] = 0.5 * (c0sq * rs - J);
-            } else {
-                g0[j] = 2.0 * (1.0 - c0sq) * rho - g0[j];
-                np_[j] = c0sq * rho - am[j];
-                nm_[j] = c0sq * rho - ap[j];
-            }
-        }
     }
 #pragma unroll
-    for (int j = 0; j < kCavPer; ++j) {
-        const int x = threadIdx.x + j * kCavThreads;
-        if (x < nx) {
-            lockin[x] = sc[j];
-            lockin[nx + x] = ss[j];
+    for (int c = 0; c < CPL; ++c)
+        if (own(x0 + c)) {
+            lockin[x0 + c] = sc[c];
+            lockin[nx + x0 + c] = ss[c];
         }
-    }
 }
 
 }  // namespace lbw

@@ -1669,6 +1669,24 @@ int cavity_fit(int32_t nx, int64_t m, double k, const double *lock, double *out,
     return LB_OK;
 }
 
+// One wavefront holds up to 256 cells, 4 to a lane; fewer to a lane shorten a step.
+void launch_cavity(int nx, double c0sq, double omega, double rho_a, double phi, int64_t n_total,
+                   int64_t n_fit, double *lock, hipStream_t s)
+{
+    const auto go = [&](auto kernel, int waves) {
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(64 * waves), 0, s, nx, c0sq, omega, rho_a, phi,
+                           n_total, n_fit, lock);
+    };
+    if (nx <= 64)
+        go(cavity_kernel<1, false>, 1);
+    else if (nx <= 128)
+        go(cavity_kernel<2, false>, 1);
+    else if (nx <= 256)
+        go(cavity_kernel<4, false>, 1);
+    else
+        go(cavity_kernel<4, true>, (nx + kCavOwn - 1) / kCavOwn);
+}
+
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 double *g_scratch[kMaxDevices] = {};
@@ -1707,8 +1725,7 @@ int lb_cavity_calibrate(int32_t nx, double c0, double omega, double rho_a, doubl
         return fail(LB_ENOMEM, "workspace too small");
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     double *d_lock = static_cast<double *>(dev_workspace);
-    hipLaunchKernelGGL(cavity_kernel, dim3(1), dim3(kCavThreads), 0, s, nx, c0 * c0, omega,
-                       rho_a, wall_phi, n_total, m, d_lock);
+    launch_cavity(nx, c0 * c0, omega, rho_a, wall_phi, n_total, m, d_lock, s);
     HIP_TRY(hipGetLastError());
     std::vector<double> lock(2 * (size_t)nx);
     HIP_TRY(hipMemcpyAsync(lock.data(), d_lock, sizeof(double) * 2 * nx, hipMemcpyDeviceToHost, s));
@@ -1728,8 +1745,7 @@ int lb_cavity_calibrate_noalloc(int32_t nx, double c0, double omega, double rho_
     if ((st = cavity_scratch(&d_lock))) return st;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     // the kernel writes every one of the 2 nx sums, so nothing needs clearing first
-    hipLaunchKernelGGL(cavity_kernel, dim3(1), dim3(kCavThreads), 0, s, nx, c0 * c0, omega,
-                       rho_a, wall_phi, n_total, m, d_lock);
+    launch_cavity(nx, c0 * c0, omega, rho_a, wall_phi, n_total, m, d_lock, s);
     HIP_TRY(hipGetLastError());
     double lock[2 * kCavMaxNx];  // host copy on the stack (no heap allocation)
     HIP_TRY(hipMemcpyAsync(lock, d_lock, sizeof(double) * 2 * nx, hipMemcpyDeviceToHost, s));
