@@ -149,9 +149,11 @@ struct AccDev {
 // step: one FP32 sphere of 256 x 128 x 128 (117 MB a buffer) stays inside the 256 MB memory-side
 // cache and takes 24.5 us a step, 29.0 with three.
 constexpr int kNumBuf = 2;
-constexpr int kNumSlot = 8;  // moment boxes and partial sums, indexed by step mod 8
-
-__host__ __device__ inline int slot_of(int64_t t) { return (int)(t & (kNumSlot - 1)); }
+// Moment boxes and partial sums, indexed by step mod InstDev::slots: a launch writes those of its
+// steps while the ones of the launch before are read, so twice the most steps of a launch, rounded
+// up to a power of two.
+constexpr int kNumSlot = 8;
+constexpr int kResidentSteps = 64;  // most steps of a resident launch (2D)
 
 struct InstDev {
     int32_t dim, nx, ny, nz;
@@ -170,10 +172,13 @@ struct InstDev {
     // measurement
     int32_t mb_lo[3];        // moment box origin (cells whose rho, J the surface reads)
     int32_t mb_n[3];         // moment box extent (0 -> no measurement)
-    void *mom[kNumSlot];     // moment boxes (rho, Jx, Jy, Jz per cell, compute type) by step mod 8
+    char *mom;               // moment boxes (rho, Jx, Jy, Jz per cell, compute type) by slot
+    int64_t mom_bytes;       // bytes from one to the next
+    int32_t slots;           // moment boxes and partial sums
+    int32_t resident;        // configuration of the resident kernel (2D)
     int32_t n_surf, n_chunks;  // surface elements, 64-element chunks
     const SurfPt *surf;
-    double *part;            // 8 x n_chunks x 4 per-chunk flux sums by step mod 8
+    double *part;            // slots x n_chunks x 4 per-chunk flux sums
     double c0sq_force;       // c0^2 in the surface integral
     double force_scale;      // -1 / (rho0 * scale^2)
     int64_t avg_start;
@@ -181,6 +186,16 @@ struct InstDev {
     double *trace;           // trace_cap x 3
     int64_t trace_cap;
 };
+
+// slot of step t, and the moment box there
+template <typename I> __device__ inline int slot_of(const I &inst, int64_t t)
+{
+    return (int)(t & (inst.slots - 1));
+}
+template <typename I> __device__ inline char *mom_of(const I &inst, int64_t t)
+{
+    return inst.mom + slot_of(inst, t) * inst.mom_bytes;
+}
 
 struct SegInfo {
     int32_t task0;      // first wave task of the run (one-step launch)
@@ -198,8 +213,8 @@ struct SegInfo {
 // One launch = [reducer blocks][surface blocks][lattice blocks] (the
 // march kernel puts its lattice blocks first), a three-stage pipeline
 // over consecutive steps:
-//  * lattice blocks advance steps t .. t+nst-1 (nst = 1 to 3) and store
-//    rho1, J1 of each f(s) in the moment box of slot s mod 8;
+//  * lattice blocks advance steps t .. t+nst-1 (nst = 1 to 3, in 2D up to 64) and
+//    store rho1, J1 of each f(s) in the moment box of its slot;
 //  * surface blocks interpolate F(s) for the n_ms steps s = t - meas_off ..
 //    that earlier launches advanced, from their moment boxes, and write one
 //    partial sum per 64 elements into slot s mod 4;
@@ -207,7 +222,7 @@ struct SegInfo {
 //    step order, one block per instance) in a fixed order, scale, trace and
 //    accumulate.
 // Every stage reads what an earlier launch wrote, and the slots written and
-// read by one launch differ mod 8, so no stage waits on another inside a
+// read by one launch differ, so no stage waits on another inside a
 // launch.  The lattice step of a launch is t = tp[0] + dt and the buffer it reads
 // (tp[1] + dbuf) mod 2: the counter lives in device memory so that a captured
 // sequence of launches can be replayed at any t and from either buffer.
@@ -221,6 +236,7 @@ struct StepArgs {
     int32_t nseg;
     int32_t ntask;            // lattice tasks (one-step launch) or blocks (march launch)
     int32_t n_red, n_sb;      // reducer blocks; surface blocks per measured step
+    int32_t nst;              // steps of a resident launch
     SegInfo seg[kMaxSeg];
     const int32_t *sb_inst;   // per surface block: internal instance
     const int32_t *sb_chunk;  // per surface block: chunk of 64 elements
@@ -339,7 +355,7 @@ __device__ inline void lattice_task(const StepArgs &a, const int64_t t, const in
     const int mb_lo0 = I.mb_lo[0], mb_lo1 = I.mb_lo[1], mb_lo2 = I.mb_lo[2];
     const int mb_n0 = I.mb_n[0], mb_n1 = I.mb_n[1], mb_n2 = I.mb_n[2];
     const gptr<const C> c2box = to_global<C>(I.c2box);
-    const gptr<C> mom = to_global<C>(I.mom[slot_of(t)]);
+    const gptr<C> mom = to_global<C>(mom_of(I, t));
     const C phi = (C)I.wall_phi;
     const double src_amp = I.src_amp, omega = I.omega;
     const gptr<const R> src = to_global<R>(static_cast<const void *>(I.buf[bsrc]));
@@ -563,6 +579,28 @@ template <bool UP> __device__ inline double lane_shift(double edge, double v)
     return __hiloint2double(hi, lo);
 }
 
+// v of lane n as a value of the whole wavefront
+__device__ inline float lane_value(float v, int n)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), n));
+}
+__device__ inline double lane_value(double v, int n)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), n),
+                            __builtin_amdgcn_readlane(__double2loint(v), n));
+}
+// the shift of 64 lanes around the end
+template <bool UP> __device__ inline float lane_rotate(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), UP ? 0x13C : 0x134, 0xf, 0xf, true));
+}
+template <bool UP> __device__ inline double lane_rotate(double v)
+{
+    constexpr int ctrl = UP ? 0x13C : 0x134;
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), ctrl, 0xf, 0xf, true),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), ctrl, 0xf, 0xf, true));
+}
+
 constexpr int kWaitLoads = 0x0F70;  // s_waitcnt vmcnt(0), the other counters unconstrained
 
 // LDS stores that the compiler does not order after the copies into LDS still in flight (it
@@ -658,7 +696,7 @@ __device__ inline void march_block(const StepArgs &a, const int64_t t, const int
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         rs[k] = C(0);
-        mom[k] = to_global<C>(I.mom[slot_of(t + k)]);
+        mom[k] = to_global<C>(mom_of(I, t + k));
     }
     if (x == 1) {
 #pragma unroll
@@ -949,8 +987,11 @@ __device__ inline void surface_block(const StepArgs &a, const int64_t t_meas, in
     const int chunk = a.sb_chunk[sb];
     const int k = chunk * 64 + lane;
     const bool live = k < I.n_surf;
-    const gptr<const C> mom = to_global<C>(static_cast<const void *>(I.mom[slot_of(t_meas)]));
+    const gptr<const C> mom = to_global<C>(static_cast<const void *>(mom_of(I, t_meas)));
+    // in 2D several steps at once come from the resident kernel, which writes column by column
     const int mbx = I.mb_n[0], mby = I.mb_n[1];
+    const bool columns = DIM == 2 && a.n_ms > 1;
+    const int sx = columns ? mby : 1, sy = columns ? 1 : mbx;
 
     double rI = 0.0, Jx = 0.0, Jy = 0.0, Jz = 0.0;
     if (live) {
@@ -961,7 +1002,7 @@ __device__ inline void surface_block(const StepArgs &a, const int64_t t_meas, in
             if (n < NN) {
                 const int dx = n % 3, dy = (n / 3) % 3, dz = n / 9;
                 const gptr<const C> m =
-                    mom + 4 * (((int64_t)P.bz[dz] * mby + P.by[dy]) * mbx + P.bx[dx]);
+                    mom + 4 * ((int64_t)P.bz[dz] * mby * mbx + P.by[dy] * sy + P.bx[dx] * sx);
                 const double wt = P.w[dx] * P.w[3 + dy] * P.w[6 + dz];
                 rI += wt * (double)m[0];
                 Jx += wt * (double)m[1];
@@ -997,45 +1038,61 @@ __device__ inline void surface_block(const StepArgs &a, const int64_t t_meas, in
         fz += __shfl_xor(fz, off);
     }
     if (lane == 0) {
-        double *o = I.part + (slot_of(t_meas) * I.n_chunks + chunk) * 4;
+        double *o = I.part + (slot_of(I, t_meas) * I.n_chunks + chunk) * 4;
         o[0] = fx;
         o[1] = fy;
         o[2] = fz;
     }
 }
 
-// Reducer: F(t) of one instance for the steps t0 .. t0+n-1 in order, each
+// Reducer: F(t) of one instance for the steps t0 .. t0+n-1 (n <= 64), each
 // from its chunk partials (written by an earlier launch), scaled, traced and
-// accumulated.  One block per instance, so the accumulation order is fixed.
+// accumulated.  One wavefront per instance, a step to a lane; the sums over the
+// chunks and the accumulation over the steps run in a fixed order.
 __device__ inline void reduce_block(const StepArgs &a, const int64_t t0, int n, int ii, int tid)
 {
-    if (tid != 0) return;
+    if (tid >= 64) return;
     const InstDev &I = a.inst[ii];
     if (I.n_surf == 0) return;
-    for (int j = 0; j < n; ++j) {
-        const int64_t t = t0 + j;
-        if (I.max_steps > 0 && t >= I.max_steps) return;
-        const double *p = I.part + slot_of(t) * I.n_chunks * 4;
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+    if (I.max_steps > 0) n = (int)min((int64_t)n, I.max_steps - t0);
+    const int64_t t = t0 + tid;
+    double F[3] = {0.0, 0.0, 0.0};
+    if (tid < n) {
+        const double *p = I.part + slot_of(I, t) * I.n_chunks * 4;
         for (int c = 0; c < I.n_chunks; ++c) {
-            s0 += p[4 * c];
-            s1 += p[4 * c + 1];
-            s2 += p[4 * c + 2];
+            F[0] += p[4 * c];
+            F[1] += p[4 * c + 1];
+            F[2] += p[4 * c + 2];
         }
-        const double F[3] = {s0 * I.force_scale, s1 * I.force_scale, s2 * I.force_scale};
+#pragma unroll
+        for (int i = 0; i < 3; ++i) F[i] *= I.force_scale;
         if (t < I.trace_cap) {
             I.trace[3 * t + 0] = F[0];
             I.trace[3 * t + 1] = F[1];
             I.trace[3 * t + 2] = F[2];
         }
-        if (t >= I.avg_start) {
-            AccDev *acc = I.acc;
-            acc->sum[0] += F[0];
-            acc->sum[1] += F[1];
-            acc->sum[2] += F[2];
-            acc->n += 1;
-            if (!(isfinite(F[0]) && isfinite(F[1]) && isfinite(F[2]))) acc->nan = 1;
+    }
+    AccDev *acc = I.acc;
+    double sum[3] = {acc->sum[0], acc->sum[1], acc->sum[2]};
+    int64_t count = acc->n;
+    bool bad = acc->nan != 0;
+    for (int j = 0; j < n; ++j) {
+        double G[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) G[i] = __shfl(F[i], j);
+        if (t0 + j < I.avg_start) continue;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            sum[i] += G[i];
+            bad |= !isfinite(G[i]);
         }
+        ++count;
+    }
+    if (tid == 0) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) acc->sum[i] = sum[i];
+        acc->n = count;
+        acc->nan = bad;
     }
 }
 
@@ -1110,6 +1167,237 @@ __global__ void __launch_bounds__(64 * W, 2) march_kernel(StepArgs a)
     const int part = wave_uniform(threadIdx.x / kStepThreads);
     measure_part<3, C>(a, t, per * (b - a.ntask) + part, threadIdx.x % kStepThreads,
                        reinterpret_cast<Lds *>(stage)[part]);
+}
+
+// ---------------------------------------------------------------------------
+// Up to kResidentSteps steps per launch in 2D (D2Q5, driven x sheets): one block
+// holds a whole box in registers.  Wavefront w owns a share of the columns, lane
+// l the cells y = l and l + 64 of each.  A step reads nothing but its neighbours'
+// values: +-y from the next lane, +-x from the next column's registers, and at a
+// wavefront's first and last column through LDS, with one barrier.  Columns
+// rather than rows, because the wall and source columns, which have a rule of
+// their own, are then whole wavefronts and no lane masks.  The moments of every
+// step go to memory, where the surface blocks of the next launch interpolate
+// them, all steps side by side on the other CUs.
+//
+// What bounds it: the instruction rate of one CU (about 110 FP64 instructions and
+// 32 lane moves of a wavefront per step at 128 x 64 cells).  There, in us per step,
+// one box and 32 at once: 1.7 and 1.8 in FP64 (4.0 and 7.0 with a launch per step),
+// 1.2 for one in FP32 (3.9).  Rows instead of columns: 3.1 and 5.0 in FP64.  c^2 of
+// FP64 from LDS: kept in registers, which then spill, 2.3 and 2.6.
+// ---------------------------------------------------------------------------
+constexpr int kResidentWaves = 16;
+// configuration CX << 8 | RY (columns of a wavefront, cells of a lane in a column) of a box, 0 if it
+// does not fit: eight cells of a lane are what the registers of 16 wavefronts hold in FP64
+__host__ __device__ inline int resident_config(int nx, int ny)
+{
+    const int cols = (nx + kResidentWaves - 1) / kResidentWaves;
+    const int cx = cols <= 4 ? 4 : 8, ry = ny <= 64 ? 1 : 2;
+    return cols <= 8 && ny <= 128 && cx * ry <= 8 ? cx << 8 | ry : 0;
+}
+
+// FULL: every wavefront owns CX columns and every lane RY cells of each; the other form takes any box
+template <typename S, int CX, int RY, bool FULL>
+__device__ inline void resident_box(const StepArgs &a, int box, const int64_t t, const int bsrc,
+                                    typename StoreTraits<S>::C *edges, typename StoreTraits<S>::C *c2lds,
+                                    const typename StoreTraits<S>::C *drive)
+{
+    using T = StoreTraits<S>;
+    using E = typename T::R;
+    using C = typename T::C;
+    using V = typename VecT<E, CX>::type;
+    constexpr int W = kResidentWaves;
+    const auto &I = to_const(a.inst)[box];
+    const int nx = FULL ? W * CX : I.nx, ny = FULL ? 64 * RY : I.ny, pitch = I.pitch;
+    const int lane = threadIdx.x & 63, w = wave_uniform(threadIdx.x >> 6);
+    const int cols = FULL ? CX : nx / W + (w < nx % W);  // an equal share, some one column more
+    const int x0 = FULL ? w * CX : w * (nx / W) + min(w, nx % W);
+    const int last = min(nx, W) - 1;                     // the last wavefront that has columns
+    const int end = ny - 64 * (RY - 1) - 1;              // the lane of the last row
+    const int nst = I.max_steps > 0 ? (int)min((int64_t)a.nst, I.max_steps - t) : a.nst;
+    const int64_t plane = I.plane;
+    const gptr<const E> src = to_global<E>(static_cast<const void *>(I.buf[bsrc]));
+    const gptr<E> dst = to_global<E>(I.buf[bsrc ^ 1]);
+    const C phi = (C)I.wall_phi;
+
+    // post-collision values, and c^2, which in FP64 the registers have no room for
+    constexpr bool kLds = sizeof(C) == 8;
+    C q[5][CX][RY], c2[kLds ? 1 : CX][kLds ? 1 : RY];
+    C *const c2own = c2lds + w * (CX * RY * 64) + lane;
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+        const int y = lane + 64 * r;
+        const bool in = FULL || y < ny;
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+            const int64_t at = i * plane + (int64_t)y * pitch + x0;
+            if constexpr (FULL) {
+                const V v = *(gptr<const V>)(src + at);
+#pragma unroll
+                for (int c = 0; c < CX; ++c) q[i][c][r] = T::to_c(vget<E, CX>(v, c));
+            } else {
+#pragma unroll
+                for (int c = 0; c < CX; ++c) q[i][c][r] = in && c < cols ? T::to_c(src[at + c]) : C(0);
+            }
+        }
+        const gptr<const C> c2box = to_global<C>(I.c2box);
+        const int bb_n0 = I.bb_n[0], by = y - I.bb_lo[1];
+        const bool inside = in && by >= 0 && by < I.bb_n[1];
+#pragma unroll
+        for (int c = 0; c < CX; ++c) {
+            const int bx = x0 + c - I.bb_lo[0];
+            const C v = inside && c < cols && bx >= 0 && bx < bb_n0 ? c2box[by * bb_n0 + bx] : (C)I.c0sq;
+            if constexpr (kLds)
+                c2own[(c * RY + r) * 64] = v;
+            else
+                c2[c][r] = v;
+        }
+    }
+
+    // edges[parity][wavefront][0: -x values of its first column, 1: +x values of its last][y]
+    auto edge = [&](int parity, int ww, int side) {
+        return edges + ((parity * W + ww) * 2 + side) * (64 * RY) + lane;
+    };
+    auto publish = [&](int parity) {
+#pragma unroll
+        for (int c = 0; c < CX; ++c)
+#pragma unroll
+            for (int r = 0; r < RY; ++r) {
+                if (c == 0 && (FULL || cols > 0)) edge(parity, w, 0)[64 * r] = q[2][0][r];
+                if (FULL ? c == CX - 1 : c == cols - 1) edge(parity, w, 1)[64 * r] = q[1][c][r];
+            }
+    };
+    publish(0);
+    __syncthreads();
+    for (int k = 0; k < nst; ++k) {
+        C prev[RY], beyond[RY];  // +x of the column before, -x of the column after the last
+#pragma unroll
+        for (int r = 0; r < RY; ++r) {
+            prev[r] = w > 0 ? edge(k & 1, w - 1, 1)[64 * r] : C(0);
+            beyond[r] = w < last ? edge(k & 1, w + 1, 0)[64 * r] : C(0);
+        }
+        const C rs = drive[k];
+        // evaluated in every step: kept for all columns, what depends on it overflows the registers
+        int mx0 = x0 - I.mb_lo[0], my0 = lane - I.mb_lo[1];
+        asm volatile("" : "+s"(mx0), "+v"(my0));
+        const int mb_n1 = I.mb_n[1], columns_measured = mb_n1 > 0 ? I.mb_n[0] : 0;
+        const gptr<C> mom = to_global<C>(mom_of(I, t + k));
+#pragma unroll
+        for (int c = 0; c < CX; ++c) {
+            if (!FULL && c >= cols) break;
+            const bool edge_col = FULL ? c == CX - 1 : c == cols - 1;
+            C f[RY][5], rho[RY];
+#pragma unroll
+            for (int r = 0; r < RY; ++r) {
+                f[r][0] = q[0][c][r];
+                f[r][1] = prev[r];
+                prev[r] = q[1][c][r];
+                f[r][2] = edge_col || c == CX - 1 ? beyond[r] : q[2][c < CX - 1 ? c + 1 : c][r];
+                if constexpr (FULL && RY == 1) {
+                    f[r][3] = lane_rotate<true>(q[3][c][r]);
+                    f[r][4] = lane_rotate<false>(q[4][c][r]);
+                } else {
+                    const C up = r > 0 ? lane_value(q[3][c][r > 0 ? r - 1 : 0], 63)
+                                       : lane_value(q[3][c][RY - 1], end);
+                    const C down = lane_value(q[4][c][r < RY - 1 ? r + 1 : 0], 0);
+                    f[r][3] = lane_shift<true>(up, q[3][c][r]);
+                    f[r][4] = lane_shift<false>(down, q[4][c][r]);
+                    if (!FULL && r == RY - 1) f[r][4] = lane == end ? down : f[r][4];
+                }
+                rho[r] = f[r][0];
+#pragma unroll
+                for (int i = 1; i < 5; ++i) rho[r] += f[r][i];
+            }
+            if ((uint32_t)(mx0 + c) < (uint32_t)columns_measured) {
+#pragma unroll
+                for (int r = 0; r < RY; ++r) {
+                    const int by = my0 + 64 * r;
+                    if ((uint32_t)by < (uint32_t)mb_n1) {
+                        using V4 = typename VecT<C, 4>::type;
+                        V4 mv;
+                        mv[0] = rho[r];
+                        mv[1] = f[r][1] - f[r][2];
+                        mv[2] = f[r][3] - f[r][4];
+                        mv[3] = C(0);
+                        *(gptr<V4>)(mom + 4 * ((mx0 + c) * mb_n1 + by)) = mv;
+                    }
+                }
+            }
+            const int x = x0 + c;
+            // full boxes have their sheets in these columns of a wavefront
+            const bool sheet = FULL && c > 1 && c < CX - 1 ? false : x <= 1 || x == nx - 1;
+#pragma unroll
+            for (int r = 0; r < RY; ++r) {
+                C o[5], cc;
+                if constexpr (kLds)
+                    cc = c2own[(c * RY + r) * 64];
+                else
+                    cc = c2[c][r];
+                if (!sheet)
+                    bulk_rule<2, C>(f[r], rho[r], cc, o);
+                else
+                    cell_rule<2, C>(f[r], rho[r], cc, x, nx, true, phi, rs, o);
+#pragma unroll
+                for (int i = 0; i < 5; ++i) q[i][c][r] = T::to_c(T::to_r(o[i]));
+            }
+        }
+        publish((k + 1) & 1);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+        const int y = lane + 64 * r;
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+            const int64_t at = i * plane + (int64_t)y * pitch + x0;
+            if constexpr (FULL) {
+                V v;
+#pragma unroll
+                for (int c = 0; c < CX; ++c) vset<E, CX>(v, c, T::to_r(q[i][c][r]));
+                *(gptr<V>)(dst + at) = v;
+            } else if (y < ny) {
+#pragma unroll
+                for (int c = 0; c < CX; ++c)
+                    if (c < cols) dst[at + c] = T::to_r(q[i][c][r]);
+            }
+        }
+    }
+}
+
+template <typename S> __global__ void __launch_bounds__(64 * kResidentWaves) resident_kernel(StepArgs a)
+{
+    using C = typename StoreTraits<S>::C;
+    constexpr int W = kResidentWaves;
+    __shared__ __attribute__((aligned(16))) C edges[2 * W * 2 * 128];
+    __shared__ C c2lds[sizeof(C) == 8 ? W * 64 * 8 : 1];
+    __shared__ C drive[kResidentSteps];
+    const int64_t t = a.tp[0] + a.dt;
+    const int b = blockIdx.x;
+    if (b >= a.ntask) {
+        // measurement blocks of kStepThreads threads, side by side
+        using Lds = double[4][64][4];
+        constexpr int per = 64 * W / kStepThreads;
+        static_assert(sizeof edges >= per * sizeof(Lds), "the surface blocks use the same LDS");
+        const int part = wave_uniform(threadIdx.x / kStepThreads);
+        measure_part<2, C>(a, t, per * (b - a.ntask) + part, threadIdx.x % kStepThreads,
+                           reinterpret_cast<Lds *>(edges)[part]);
+        return;
+    }
+    const int bsrc = ((int)a.tp[1] + a.dbuf) & 1;
+    const auto &I = to_const(a.inst)[b];
+    if ((int)threadIdx.x < a.nst)
+        drive[threadIdx.x] = (C)(I.src_amp * sin(I.omega * (double)(t + (int)threadIdx.x)));
+    __syncthreads();
+    const int cx = I.resident >> 8, ry = I.resident & 255;
+    const bool full = I.nx == W * cx && I.ny == 64 * ry;
+    if (cx == 8 && full)
+        resident_box<S, 8, 1, true>(a, b, t, bsrc, edges, c2lds, drive);
+    else if (cx == 8)
+        resident_box<S, 8, 1, false>(a, b, t, bsrc, edges, c2lds, drive);
+    else if (ry == 2)
+        resident_box<S, 4, 2, false>(a, b, t, bsrc, edges, c2lds, drive);
+    else
+        resident_box<S, 4, 1, false>(a, b, t, bsrc, edges, c2lds, drive);
 }
 
 // Point source (the paper's oscillating point source): after the lattice
@@ -1258,12 +1546,6 @@ constexpr int kCavOwn = 64 * 4 - 2 * kCavHalo;    // CPL = 4
 constexpr int kCavMaxWaves = (kCavMaxNx + kCavOwn - 1) / kCavOwn;
 
 // the value v of lane k
-__device__ inline double lane_value(double v, int k)
-{
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), k),
-                            __builtin_amdgcn_readlane(__double2loint(v), k));
-}
-
 template <int CPL, bool MANY>
 __global__ void __launch_bounds__(MANY ? 64 * kCavMaxWaves : 64)
 cavity_kernel(int nx, double c0sq, double omega, double rho_a, double phi, int64_t n_total,

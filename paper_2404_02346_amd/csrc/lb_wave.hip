@@ -333,14 +333,28 @@ struct InstPlan {
     int pitch;
     int64_t plane;
     int n_chunks;
-    size_t off_surf, off_part, off_mom[kNumSlot], off_trace, off_box, off_buf[kNumBuf];
+    size_t off_surf, off_part, off_mom, mom_bytes, off_trace, off_box, off_buf[kNumBuf];
 };
 
 struct Layout {
     size_t off_inst, off_acc, off_sbtab, off_tdev, total;
     int n_sb_total;
+    bool resident;  // every box is advanced by the resident kernel
+    int slots;      // moment boxes and partial sums per instance
     std::vector<InstPlan> p;
 };
+
+// The resident kernel takes handles whose boxes are all 2D, driven and small enough: from eight steps
+// on it is the faster one at every size it takes and any number of boxes.  A launch costs the box's
+// way into the registers and back.  128 x 64 cells in FP64, us per step of a call of 1, 4, 8 and 64
+// steps: 28, 8.5, 5.0 and 1.9, with a launch per step 10, 6.5, 5.9 and 4.7; 512 such boxes: 108, 35,
+// 22 and 10, with a launch per step 87, 80, 79 and 78.
+constexpr int kResidentMin = 8;
+int resident_of(const lb_wave_desc &d)
+{
+    if (d.dim != 2 || d.xbc != LB_XBC_DRIVEN || d.src_kind != LB_SRC_SHEET) return 0;
+    return resident_config(d.nx, d.ny);
+}
 
 Layout plan(const lb_wave_desc *descs, int n)
 {
@@ -351,7 +365,12 @@ Layout plan(const lb_wave_desc *descs, int n)
     L.off_acc = off;
     off = align_up(off + sizeof(AccDev) * n);
     L.n_sb_total = 0;
-    for (int i = 0; i < n; ++i) L.n_sb_total += (descs[i].n_surf + 63) / 64;
+    L.resident = true;
+    for (int i = 0; i < n; ++i) {
+        L.n_sb_total += (descs[i].n_surf + 63) / 64;
+        if (!resident_of(descs[i])) L.resident = false;
+    }
+    L.slots = L.resident ? 2 * kResidentSteps : kNumSlot;
     L.off_sbtab = off;
     off = align_up(off + sizeof(int32_t) * 2 * (size_t)L.n_sb_total);
     L.off_tdev = off;
@@ -366,14 +385,13 @@ Layout plan(const lb_wave_desc *descs, int n)
         P.plane = plane_stride((int64_t)P.pitch * d.ny * d.nz, elem_bytes(d.storage));
         P.n_chunks = (d.n_surf + 63) / 64;
         P.mbox = measure_box(d);
-        for (int b = 0; b < kNumSlot; ++b) {
-            P.off_mom[b] = off;
-            off = align_up(off + 4 * compute_bytes(d.storage) * P.mbox.cells());
-        }
+        P.off_mom = off;
+        P.mom_bytes = align_up(4 * compute_bytes(d.storage) * P.mbox.cells());
+        off += P.mom_bytes * L.slots;
         P.off_surf = off;
         off = align_up(off + sizeof(SurfPt) * d.n_surf);
         P.off_part = off;
-        off = align_up(off + sizeof(double) * kNumSlot * 4 * (size_t)P.n_chunks);
+        off = align_up(off + sizeof(double) * L.slots * 4 * (size_t)P.n_chunks);
         P.off_trace = off;
         off = align_up(off + sizeof(double) * 3 * (size_t)d.trace_steps);
         P.off_box = off;  // the box, then one c0^2 sentinel for reads from outside it
@@ -723,6 +741,19 @@ void launch_march(const lb_wave *h, const StepArgs &a, int nst, int meas_blocks,
     }
 }
 
+// nst steps of every live box, one block each, with the measurement of the launches before
+void launch_resident(const lb_wave *h, const StepArgs &a, int meas_blocks, hipStream_t st)
+{
+    const int waves = kResidentWaves, per = 64 * waves / kStepThreads;
+    const dim3 grid(a.ntask + (meas_blocks + per - 1) / per), threads(64 * waves);
+    switch (h->storage) {
+    case LB_F64: hipLaunchKernelGGL(resident_kernel<double>, grid, threads, 0, st, a); break;
+    case LB_F32: hipLaunchKernelGGL(resident_kernel<float>, grid, threads, 0, st, a); break;
+    case LB_F16: hipLaunchKernelGGL(resident_kernel<_Float16>, grid, threads, 0, st, a); break;
+    default: hipLaunchKernelGGL(resident_kernel<bf16>, grid, threads, 0, st, a); break;
+    }
+}
+
 // The launches of n lattice steps: at most `most` steps each, the shorter ones first.
 int next_steps(int64_t n, int most)
 {
@@ -739,9 +770,8 @@ int most_steps(const lb_wave *h)
 // Measurement part of the launch whose lattice part starts at t_launch:
 // reduce every measured step whose partials an earlier launch wrote
 // (steps red .. meas-1), and measure every step whose moments an earlier
-// launch stored (steps meas .. t_launch-1).  A launch advances at most three
-// steps, so both ranges hold at most three steps and the slots they use
-// (step mod 8) differ from those the launch writes.
+// launch stored (steps meas .. t_launch-1).  Both ranges hold the steps of one
+// launch at most, and the slots they use differ from those the launch writes.
 void plan_measure(lb_wave *h, StepArgs &a, int64_t t_launch)
 {
     a.n_red = a.n_sb = a.n_ms = a.n_rs = 0;
@@ -774,6 +804,15 @@ void emit_step(const lb_wave *h, StepArgs a, int64_t t, int32_t dt, int dbuf, in
                hipStream_t st)
 {
     const int na = active_prefix(h, t);
+    if (h->lay.resident && nst > 1) {
+        a.dt = dt;
+        a.dbuf = dbuf;
+        a.nst = nst;
+        a.ntask = na;
+        if (a.n_red + a.n_ms * a.n_sb + na > 0)
+            launch_resident(h, a, a.n_red + a.n_ms * a.n_sb, st);
+        return;
+    }
     const bool march = nst > 1;
     auto first_of = [&](const SegInfo &sg) { return march ? sg.blk0 : sg.task0; };
     const int n_active = march ? h->blk0[na] : h->task0[na];
@@ -830,7 +869,7 @@ void advance(lb_wave *h, int64_t k, int n_launch)
     for (int ii = active_prefix(h, h->t); ii < live; ++ii) h->stop_buf[ii] = h->cur;
 }
 
-// nst lattice steps (1 to 3) for every live instance, with the measurement
+// nst lattice steps for every live instance, with the measurement
 // of the previous steps folded into the same launch.
 int enqueue_step(lb_wave *h, int nst)
 {
@@ -1093,7 +1132,10 @@ int lb_wave_create(const lb_wave_desc *descs, int32_t n_inst, void *dev_workspac
             I.mb_lo[a] = P.mbox.lo[a];
             I.mb_n[a] = P.mbox.n[a];
         }
-        for (int b = 0; b < kNumSlot; ++b) I.mom[b] = h->ws + P.off_mom[b];
+        I.mom = h->ws + P.off_mom;
+        I.mom_bytes = (int64_t)P.mom_bytes;
+        I.slots = L.slots;
+        I.resident = L.resident ? resident_of(d) : 0;
         I.n_surf = d.n_surf;
         I.n_chunks = P.n_chunks;
         I.surf = reinterpret_cast<const SurfPt *>(h->ws + P.off_surf);
@@ -1248,7 +1290,12 @@ int lb_wave_step_n(lb_wave *h, int64_t n_steps)
         const int most = most_steps(h), nst = std::min(most, std::max(h->graph_chunk, 1));
         const int k = h->graph_chunk / nst * nst;
         int st;
-        if (k >= 2 && left >= k && steady(h, k, nst)) {
+        if (h->lay.resident && left >= kResidentMin) {
+            const int64_t launches = (left + kResidentSteps - 1) / kResidentSteps;
+            const int n = (int)((left + launches - 1) / launches);  // equal shares: no short rest
+            st = enqueue_step(h, n);
+            left -= n;
+        } else if (k >= 2 && left >= k && steady(h, k, nst)) {
             st = replay_steps(h, k, nst);
             left -= k;
         } else {
@@ -1532,8 +1579,10 @@ int lb_wave_autotune(lb_wave *h, int32_t n_trial, double *best_ms)
         return LB_OK;
     };
     std::vector<std::array<int, 4>> cand;
+    const bool one = h->lay.resident;  // one kernel whatever the variant: time the present one
+    if (one) cand.push_back({h->vx, h->xm, h->nt, 1});
     for (int cpl : {1, 2, 4})
-        for (int xm = 0; xm <= xm_max; ++xm)
+        for (int xm = 0; xm <= xm_max && !one; ++xm)
             for (int nt = 0; nt <= 2; ++nt) cand.push_back({cpl, xm, nt, 1});
     if (h->fused_ok)
         for (int nt = 0; nt <= 1; ++nt) cand.push_back({1, xm_max, nt, 2});
