@@ -460,6 +460,7 @@ struct lb_wave {
     bool fused_ok = false;            // several steps per launch are allowed
     bool march_ok = false;            // every instance fits the march kernel
     int march_waves = 4;              // wavefronts per block of the march kernel
+    int march_depth = 2;              // most steps of its launches
     std::vector<MarchBox> boxes;      // internal order: march decomposition
     std::vector<int> blk0;            // internal order, size n + 1: march blocks
     char *ws = nullptr;
@@ -604,7 +605,7 @@ void launch_point(const lb_wave *h, const StepArgs &a, hipStream_t st)
     }
 }
 
-// Steps of one march launch, and rows per row group.  FP64 holds twice the registers and LDS.
+// Most steps of one march launch, and rows per row group.  FP64 holds twice the registers and LDS.
 int march_steps(int storage) { return storage == LB_F64 ? 2 : 3; }
 int march_rows(int storage) { return storage == LB_F64 ? 2 : 4; }
 // Wavefronts of a march block: 8 (one block per CU) or 4 (two).  With 4, a row of 256 cells or a
@@ -630,15 +631,16 @@ MarchBox march_box(const InstDev &I, int storage, int waves, int zchunk)
 // takes an eighth of the blocks, in order, and as one ends its place (a CU holds one block of 8
 // wavefronts or two of 4) takes the next.  A block runs its planes and the K - 1 halo planes at
 // both ends; two on a CU take 1.4 times as long as one alone (measured: 1.6 from HBM, 1.2 from the
-// memory-side cache).
-double march_time(const std::vector<InstDev> &inst, int storage, int waves, int zchunk)
+// memory-side cache), 1.15 times in 16-bit storage, where each waits for its own instructions (96^3
+// in FP16: 10.1 us per step with the chunks that this gives, 12.0 with those of 1.4).
+double march_time(const std::vector<InstDev> &inst, int storage, int k, int waves, int zchunk)
 {
     std::vector<std::pair<int64_t, double>> runs;  // blocks, iterations
     int64_t n = 0;
     for (const InstDev &I : inst) {
         const MarchBox m = march_box(I, storage, waves, zchunk);
         runs.push_back({m.blocks(), (double)(I.nz + m.nzc - 1) / (double)m.nzc +
-                                        2.0 * (march_steps(storage) - 1) + 1.0});
+                                        2.0 * (k - 1) + 1.0});
         n += m.blocks();
     }
     const int places = 32 * 8 / waves;
@@ -660,28 +662,44 @@ double march_time(const std::vector<InstDev> &inst, int storage, int waves, int 
         }
         worst = std::max(worst, last);
     }
-    return worst * (waves == 4 && n > 256 ? 1.4 : 1.0);
+    return worst * (waves == 4 && n > 256 ? (elem_bytes(storage) < 4 ? 1.15 : 1.4) : 1.0);
 }
 
 // The chunk length with the shortest such time; handles of very many blocks, where the ends
 // hardly matter, take long chunks without trying.  Measured against chunks of a fixed 64 planes
 // (FP32, us per step): 16 uneven boxes of 64 to 192 cells a side 198 against 231, four channels of
 // 1000 x 64 x 64 83 against 127, one sphere of 256 x 128 x 128 20 against 45 or more.
-int march_zchunk(const std::vector<InstDev> &inst, int storage, int waves)
+int march_zchunk(const std::vector<InstDev> &inst, int storage, int k, int waves)
 {
     int64_t n = 0;
     for (const InstDev &I : inst) n += march_box(I, storage, waves, 64).blocks();
     int best = 64;
     if (n > 8192) return best;
-    double best_time = march_time(inst, storage, waves, best);
+    double best_time = march_time(inst, storage, k, waves, best);
     for (int zc : {128, 96, 48, 40, 32, 28, 24, 20, 16, 12, 10, 8, 6, 5, 4, 3, 2, 1}) {
-        const double time = march_time(inst, storage, waves, zc);
+        const double time = march_time(inst, storage, k, waves, zc);
         if (time < best_time) {
             best_time = time;
             best = zc;
         }
     }
     return best;
+}
+
+// Steps of a launch: the most, but in 16-bit storage two where the boxes are short in z for the CUs
+// there are, so that the planes computed twice at the ends of the chunks count for more.  An iteration
+// of three steps takes 1.3 to 1.4 times as long as one of two, hence the line.  FP16 and BF16, us per
+// step with two and three: 96^3 10.1 and 13.2, 122 x 64 x 64 7.1 and 9.0, 134 x 128 x 128 17.9 and 19.4
+// (iterations per step of three to two: 0.82, 0.89 and 0.78); 4 of 134 x 128 x 128 (0.70) 52.5 and 50.3,
+// 16 of 256 x 128 x 128 (0.68) 207 and 179.
+int march_depth(const std::vector<InstDev> &inst, int storage, int waves)
+{
+    const int most = march_steps(storage);
+    if (elem_bytes(storage) >= 4) return most;
+    auto per_step = [&](int k) {
+        return march_time(inst, storage, k, waves, march_zchunk(inst, storage, k, waves)) / k;
+    };
+    return per_step(most) < 0.72 * per_step(2) ? most : 2;
 }
 
 // 8 wavefronts where most cells lie in rows that fill a block of 4 and the states outgrow the
@@ -764,7 +782,7 @@ int next_steps(int64_t n, int most)
 
 int most_steps(const lb_wave *h)
 {
-    return h->fused == 2 && h->march_ok ? march_steps(h->storage) : 1;
+    return h->fused == 2 && h->march_ok ? h->march_depth : 1;
 }
 
 // Measurement part of the launch whose lattice part starts at t_launch:
@@ -1227,7 +1245,8 @@ int lb_wave_create(const lb_wave_desc *descs, int32_t n_inst, void *dev_workspac
         h->blk0.assign(n_inst + 1, 0);
         if (h->fused_ok && fits) {
             h->march_waves = march_block_waves(h->hinst, h->storage);
-            const int zchunk = march_zchunk(h->hinst, h->storage, h->march_waves);
+            h->march_depth = march_depth(h->hinst, h->storage, h->march_waves);
+            const int zchunk = march_zchunk(h->hinst, h->storage, h->march_depth, h->march_waves);
             int64_t total = 0;
             for (int ii = 0; ii < n_inst && total < INT32_MAX / 2; ++ii) {
                 h->boxes[ii] = march_box(h->hinst[ii], h->storage, h->march_waves, zchunk);

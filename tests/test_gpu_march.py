@@ -85,3 +85,17 @@ def test_blocks_of_eight_wavefronts(P, storage, shape):
     p = problem(shape)
     same(run(P, [p], storage, 2, (20,), 0, random=False),
          run(P, [p], storage, 1, (20,), 0, random=False))
+
+
+@pytest.mark.parametrize("storage,shapes,depth", [
+    ("f16", [(257, 12, 150)] * 40, 3), ("bf16", [(65, 12, 40), (257, 12, 150)] + [(257, 12, 150)] * 38, 3),
+    ("f16", [(96, 16, 96)], 2), ("bf16", [(60, 16, 31)] * 3, 2)])
+def test_steps_of_a_launch_in_16_bit(P, storage, shapes, depth):
+    print(f"march vs one step, {storage}, {len(shapes)} boxes, {depth} steps a launch", flush=True)
+    probs = [problem(s, surf=False) for s in shapes]
+    h = P.LBWave(probs, storage=storage)
+    h.set_steps_per_launch(2)
+    assert h.launch_steps() == depth
+    h.close()
+    same(run(P, probs, storage, 2, (13,), 0, random=False),
+         run(P, probs, storage, 1, (13,), 0, random=False))
