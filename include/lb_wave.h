@@ -229,17 +229,22 @@ int lb_wave_autotune(lb_wave *h, int32_t n_trial, double *best_ms);
 /* Lattice steps per launch: 1 (step_kernel, the default) or 2, meaning
  * several: a fused kernel that advances t -> t + k with the values of the
  * steps in between held on chip, reading and writing the state about once per
- * k steps (k = 3, or 2 for FP64 storage; lb_wave_get_launch_steps).  It needs
+ * k steps (k = 3, or 2 for FP64 storage and for 16-bit storage of boxes short
+ * in z; lb_wave_get_launch_steps).  It needs
  * every instance 3D with driven x sheets and ny a multiple of R * 4 / nw rows
  * (R = 4 for FP32 and 2 for the other storage types; nw = pitch / 64
  * wavefronts cover a row up to 256 cells, nw = 4 for longer rows); otherwise
  * LB_EINVAL.  Results are bit-identical either way; launches are shorter where
  * an instance stops and for remainders.  lb_wave_autotune also tries several
- * steps per launch when allowed. */
+ * steps per launch when allowed.
+ *
+ * In 2D there is no choice to make: handles whose boxes are all driven and at
+ * most 128 x 64 or 64 x 128 cells advance up to 64 steps per launch in calls
+ * of at least eight steps (and then need no graph), with the same bits. */
 int lb_wave_set_steps_per_launch(lb_wave *h, int32_t k);
 int lb_wave_get_steps_per_launch(const lb_wave *h, int32_t *k);
 
-/* Lattice steps that one launch of this handle advances in a long run. */
+/* Lattice steps that one launch of this handle advances in a long run (3D). */
 int lb_wave_get_launch_steps(const lb_wave *h, int32_t *k);
 
 /* Replay steady steps as captured HIP graphs of `chunk` steps (0 = off,

@@ -350,6 +350,9 @@ struct Layout {
 // steps: 28, 8.5, 5.0 and 1.9, with a launch per step 10, 6.5, 5.9 and 4.7; 512 such boxes: 108, 35,
 // 22 and 10, with a launch per step 87, 80, 79 and 78.
 constexpr int kResidentMin = 8;
+// Its moment boxes, one for each step of two launches, may take this much: handles of thousands of
+// boxes with large surfaces keep the small workspace of one step per launch.
+constexpr size_t kResidentBytes = (size_t)8 << 30;
 int resident_of(const lb_wave_desc &d)
 {
     if (d.dim != 2 || d.xbc != LB_XBC_DRIVEN || d.src_kind != LB_SRC_SHEET) return 0;
@@ -366,10 +369,14 @@ Layout plan(const lb_wave_desc *descs, int n)
     off = align_up(off + sizeof(AccDev) * n);
     L.n_sb_total = 0;
     L.resident = true;
+    size_t slot_bytes = 0;
     for (int i = 0; i < n; ++i) {
         L.n_sb_total += (descs[i].n_surf + 63) / 64;
         if (!resident_of(descs[i])) L.resident = false;
+        if (L.resident)
+            slot_bytes += align_up(4 * compute_bytes(descs[i].storage) * measure_box(descs[i]).cells());
     }
+    if (slot_bytes > kResidentBytes / (2 * kResidentSteps)) L.resident = false;
     L.slots = L.resident ? 2 * kResidentSteps : kNumSlot;
     L.off_sbtab = off;
     off = align_up(off + sizeof(int32_t) * 2 * (size_t)L.n_sb_total);
