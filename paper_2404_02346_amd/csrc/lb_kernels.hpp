@@ -163,7 +163,7 @@ struct InstDev {
     double c0sq;             // fluid c0^2 (outside the box)
     int32_t bb_lo[3];        // sound-speed box origin
     int32_t bb_n[3];         // sound-speed box extent (0 -> no box)
-    const void *c2box;       // c^2 over the box in the compute type, x fastest, then c0^2
+    const void *c2box;       // c^2 over the box in the compute type, plane by plane (c2_plane)
     double src_amp;          // rho_a times the storage scale
     double omega, wall_phi;
     int64_t max_steps;       // frozen for t >= max_steps
@@ -186,6 +186,10 @@ struct InstDev {
     double *trace;           // trace_cap x 3
     int64_t trace_cap;
 };
+
+// Cells of the c^2 table from one plane of the sound-speed box to the next: its n0 x n1 cells, x
+// fastest, then one c0^2 for reads from outside the box
+__host__ __device__ inline int64_t c2_plane(int n0, int n1) { return (int64_t)n0 * n1 + 1; }
 
 // slot of step t, and the moment box there
 template <typename I> __device__ inline int slot_of(const I &inst, int64_t t)
@@ -471,7 +475,7 @@ __device__ inline void lattice_task(const StepArgs &a, const int64_t t, const in
             if (bx >= 0 && bx < bb_n0) {
                 const int by = y - bb_lo1;
                 const int bz = (DIM == 3) ? z - bb_lo2 : 0;
-                c2 = c2box[((int64_t)bz * bb_n1 + by) * bb_n0 + bx];
+                c2 = c2box[bz * c2_plane(bb_n0, bb_n1) + (int64_t)by * bb_n0 + bx];
             }
         }
         C out[Q];
@@ -770,24 +774,29 @@ __device__ inline void march_block(const StepArgs &a, const int64_t t, const int
                 (mb_n[0] > 0 && y0 + j - H < ny && mby >= 0 && mby < mb_n[1]) ? mby * mb_n[0] : -1);
         }
     }
-    auto box_z = [&](const int *lo, const int *n, int z) {
-        const int bz = z - lo[2];
-        return (n[0] > 0 && bz >= 0 && bz < n[2]) ? bz * n[1] * n[0] : -1;
+    auto mb_z = [&](int z) {
+        const int bz = z - mb_lo[2];
+        return (mb_n[0] > 0 && bz >= 0 && bz < mb_n[2]) ? bz * mb_n[1] * mb_n[0] : -1;
     };
     // c^2 of the lane's cell in the rows of level 1 of plane zq: lanes outside the box read the
-    // c0^2 stored after it
-    const int n_box = bb_n[0] * bb_n[1] * bb_n[2];
+    // c0^2 stored at the end of the plane.  The plane is addressed in 64 bits: a c^2 that varies
+    // over the whole lattice takes more than 4 GiB from 2^30 cells on in FP32 (2^29 in FP64).
+    const int n_plane = bb_n[0] * bb_n[1];
     const int bx = x - bb_lo[0];
     const bool xb = bx >= 0 && bx < bb_n[0];
     int bb_any = -1;  // some row of the block meets the box
 #pragma unroll
     for (int j = 0; j < N1; ++j) bb_any = max(bb_any, bb_y[j]);
     auto load_c2 = [&](int zq, C (&c)[N1]) {
-        const int bz = box_z(bb_lo, bb_n, zq);
-        if (__builtin_expect((bz | bb_any) >= 0, 0)) {
+        const int bz = zq - bb_lo[2];
+        if (__builtin_expect(bb_any >= 0 && bz >= 0 && bz < bb_n[2], 0)) {
+            const gptr<const C> plane_c2 = c2box + bz * c2_plane(bb_n[0], bb_n[1]);
+            // offsets formed in every plane of the box: kept for all rows they overflow the registers
+            int first = 0;
+            asm("" : "+s"(first) : "s"(bz));
 #pragma unroll
             for (int j = 0; j < N1; ++j)
-                c[j] = *at(c2box, (uint32_t)(xb && bb_y[j] >= 0 ? bz + bb_y[j] + bx : n_box));
+                c[j] = *at(plane_c2, (uint32_t)(xb && bb_y[j] >= 0 ? first + bb_y[j] + bx : n_plane));
         } else {
 #pragma unroll
             for (int j = 0; j < N1; ++j) c[j] = c0sq;
@@ -864,7 +873,7 @@ __device__ inline void march_block(const StepArgs &a, const int64_t t, const int
             for (int k = 0; k < K; ++k) {
                 pend[k] = C(0);
                 const int p = i - k;
-                mrow[k] = wave_uniform((p >= 0 && p < zlen) ? box_z(mb_lo, mb_n, z0 + p) : -1);
+                mrow[k] = wave_uniform((p >= 0 && p < zlen) ? mb_z(z0 + p) : -1);
             }
             E res[R][7];  // level K
 #pragma unroll
@@ -1443,7 +1452,8 @@ __global__ void point_source_kernel(const InstDev *inst, int n_inst, const int64
     const int bx = x - I.bb_lo[0], by = y - I.bb_lo[1], bz = (DIM == 3) ? z - I.bb_lo[2] : 0;
     if (I.bb_n[0] > 0 && bx >= 0 && bx < I.bb_n[0] && by >= 0 && by < I.bb_n[1] &&
         (DIM == 2 || (bz >= 0 && bz < I.bb_n[2])))
-        c2 = static_cast<const C *>(I.c2box)[((int64_t)bz * I.bb_n[1] + by) * I.bb_n[0] + bx];
+        c2 = static_cast<const C *>(
+            I.c2box)[bz * c2_plane(I.bb_n[0], I.bb_n[1]) + (int64_t)by * I.bb_n[0] + bx];
     const C rs = (C)(I.src_amp * sin(I.omega * (double)t));
     C out[Q];
     impose_rule<DIM, C>(f, c2, rs, out);

@@ -97,6 +97,9 @@ struct Box {
     size_t cells() const { return (size_t)n[0] * n[1] * n[2]; }
 };
 
+// cells of its c^2 table
+size_t c2_cells(const Box &b) { return (size_t)c2_plane(b.n[0], b.n[1]) * b.n[2]; }
+
 Box sound_speed_box(const lb_wave_desc &d)
 {
     Box b;
@@ -321,6 +324,9 @@ int check_all(const lb_wave_desc *descs, int n)
 // channels and banks (with power-of-two strides they collide; measured on
 // the 16 x 256 x 128 x 128 workload: 5.43 -> 5.90 TB/s).
 constexpr int64_t kPlaneRound = 8192, kPlaneSkew = 3072;
+// State buffers start on 4 KiB: where they lie then does not depend on the sizes of the tables
+// before them (four channels of 1000 x 64 x 64 in FP32: 80 us per step, 81 to 83 without).
+constexpr size_t kBufAlign = 4096;
 int64_t plane_stride(int64_t elems, size_t eb)
 {
     const int64_t bytes = (elems * (int64_t)eb + kPlaneRound - 1) / kPlaneRound * kPlaneRound;
@@ -399,14 +405,15 @@ Layout plan(const lb_wave_desc *descs, int n)
         off = align_up(off + sizeof(SurfPt) * d.n_surf);
         P.off_part = off;
         off = align_up(off + sizeof(double) * L.slots * 4 * (size_t)P.n_chunks);
-        P.off_trace = off;
-        off = align_up(off + sizeof(double) * 3 * (size_t)d.trace_steps);
-        P.off_box = off;  // the box, then one c0^2 sentinel for reads from outside it
-        off = align_up(off + compute_bytes(d.storage) * (P.box.cells() + 1));
+        P.off_box = off;
+        off = align_up(off + compute_bytes(d.storage) * c2_cells(P.box));
         for (int b = 0; b < kNumBuf; ++b) {
+            off = align_up(off, kBufAlign);
             P.off_buf[b] = off;
             off = align_up(off + elem_bytes(d.storage) * (size_t)P.plane * Q);
         }
+        P.off_trace = off;
+        off = align_up(off + sizeof(double) * 3 * (size_t)d.trace_steps);
     }
     L.total = off;
     return L;
@@ -1187,34 +1194,32 @@ int lb_wave_create(const lb_wave_desc *descs, int32_t n_inst, void *dev_workspac
             host_blobs.push_back(std::move(blob));
             blob_off.push_back(P.off_surf);
         }
-        // compact c^2 table in the compute type, followed by the c0^2 sentinel
-        {
+        // compact c^2 table in the compute type, c0^2 after every plane
+        if (P.box.cells() > 0) {
             const size_t cb = compute_bytes(d.storage);
-            std::vector<uint8_t> blob(cb * (P.box.cells() + 1));
+            std::vector<uint8_t> blob(cb * c2_cells(P.box));
             size_t q = 0;
-            for (int z = 0; z < P.box.n[2]; ++z)
+            auto put = [&](double c2) {
+                if (cb == 8) {
+                    std::memcpy(blob.data() + 8 * q, &c2, 8);
+                } else {
+                    const float f = (float)c2;
+                    std::memcpy(blob.data() + 4 * q, &f, 4);
+                }
+                ++q;
+            };
+            for (int z = 0; z < P.box.n[2]; ++z) {
                 for (int y = 0; y < P.box.n[1]; ++y)
-                    for (int x = 0; x < P.box.n[0]; ++x, ++q) {
+                    for (int x = 0; x < P.box.n[0]; ++x) {
                         const int gx = P.box.lo[0] + x, gy = P.box.lo[1] + y, gz = P.box.lo[2] + z;
                         double c;
                         if (d.c_field)
                             c = d.c_field[((size_t)gz * d.ny + gy) * d.nx + gx];
                         else
                             c = object_c(d, gx, gy, gz);
-                        const double c2 = c * c;
-                        if (cb == 8) {
-                            std::memcpy(blob.data() + 8 * q, &c2, 8);
-                        } else {
-                            const float f = (float)c2;
-                            std::memcpy(blob.data() + 4 * q, &f, 4);
-                        }
+                        put(c * c);
                     }
-            const double s2 = d.c0 * d.c0;  // rounded as the kernels round c0^2
-            if (cb == 8) {
-                std::memcpy(blob.data() + 8 * q, &s2, 8);
-            } else {
-                const float f = (float)s2;
-                std::memcpy(blob.data() + 4 * q, &f, 4);
+                put(d.c0 * d.c0);  // rounded as the kernels round c0^2
             }
             host_blobs.push_back(std::move(blob));
             blob_off.push_back(P.off_box);
@@ -1244,8 +1249,9 @@ int lb_wave_create(const lb_wave_desc *descs, int32_t n_inst, void *dev_workspac
         for (const InstDev &I : h->hinst) {
             const int groups = I.pitch > kMarchMaxPitch ? 1 : 4 / (I.pitch / 64);
             if (I.xbc != LB_XBC_DRIVEN || I.ny % (rule_rows(h->storage) * groups)) h->fused_ok = false;
-            // lane offsets inside one plane are 32-bit byte counts
-            if ((int64_t)I.ny * I.pitch * (int64_t)elem_bytes(h->storage) > (int64_t)UINT32_MAX)
+            // lane offsets inside one plane, of the state and of the c^2 table, are 32-bit byte counts
+            if ((int64_t)I.ny * I.pitch * (int64_t)elem_bytes(h->storage) > (int64_t)UINT32_MAX ||
+                c2_plane(I.bb_n[0], I.bb_n[1]) * (int64_t)compute_bytes(h->storage) > (int64_t)UINT32_MAX)
                 fits = false;
         }
         h->boxes.resize(n_inst);
