@@ -471,7 +471,7 @@ def main():
     else:
         tune_ms = h.autotune(6)
     variant = get_variant(h)
-    spl = h.launch_steps()
+    spl, plan = h.launch_steps(), h.launch_plan()
     h.set_graph(args.graph)
     h.step(args.warmup)
     if args.graph > 0 and args.steps > 2 * args.graph:
@@ -501,6 +501,8 @@ def main():
     # --- the lattice stage alone (same instances and variant, no surface blocks) ---
     g = P.LBWave(problems(x_mid, k, with_surface=False), storage=args.storage, stream=stream)
     set_variant(g, variant)
+    if plan[0] > 1:
+        g.set_launch_plan(*plan)
     g.set_graph(args.graph)
     g.step(2 * args.graph + 10)  # past the first graph capture
     n_k = min(max(args.steps // 10, 50), 1000)

@@ -214,7 +214,7 @@ int lb_wave_state_view(const lb_wave *h, int32_t inst, lb_state_view *v);
  *   nontemporal 0: plain loads and stores, 1: non-temporal stores,
  *     2: non-temporal loads and stores.
  * Every variant computes bit-identical results.  lb_wave_autotune times every
- * valid variant, and several steps per launch where allowed, for n_trial steps
+ * valid variant, and every plan of several steps per launch where allowed, for n_trial steps
  * (rounded up to whole launches) on the handle's own instances, keeps the fastest,
  * then resets the state (lb_wave_reset); best_ms (may be NULL) receives the
  * winning time per step in ms.  set_tile/get_tile change or read
@@ -229,8 +229,7 @@ int lb_wave_autotune(lb_wave *h, int32_t n_trial, double *best_ms);
 /* Lattice steps per launch: 1 (step_kernel, the default) or 2, meaning
  * several: a fused kernel that advances t -> t + k with the values of the
  * steps in between held on chip, reading and writing the state about once per
- * k steps (k = 3, or 2 for FP64 storage and for 16-bit storage of boxes short
- * in z; lb_wave_get_launch_steps).  It needs
+ * k steps (k = 2 or 3; lb_wave_get_launch_steps).  It needs
  * every instance 3D with driven x sheets and ny a multiple of R * 4 / nw rows
  * (R = 4 for FP32 and 2 for the other storage types; nw = pitch / 64
  * wavefronts cover a row up to 256 cells, nw = 4 for longer rows); otherwise
@@ -246,6 +245,14 @@ int lb_wave_get_steps_per_launch(const lb_wave *h, int32_t *k);
 
 /* Lattice steps that one launch of this handle advances in a long run (3D). */
 int lb_wave_get_launch_steps(const lb_wave *h, int32_t *k);
+
+/* The launches of several steps: `steps` lattice steps each (2 or 3; 2 in FP64) by blocks of
+ * `waves` wavefronts (4 or 8; 4 in 16-bit storage).  A handle starts with the plan that a model of
+ * its blocks' schedule prefers, and lb_wave_autotune times all of them.  Every plan gives the same
+ * bits.  set does not turn several steps per launch on; LB_EINVAL on a handle that always
+ * runs one step per launch, for which get gives 1 and 0. */
+int lb_wave_set_launch_plan(lb_wave *h, int32_t steps, int32_t waves);
+int lb_wave_get_launch_plan(const lb_wave *h, int32_t *steps, int32_t *waves);
 
 /* Replay steady steps as captured HIP graphs of `chunk` steps (0 = off,
  * otherwise 2..4096).  A sequence is captured once per launch shape and

@@ -7,7 +7,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <array>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -475,7 +474,6 @@ struct lb_wave {
     bool march_ok = false;            // every instance fits the march kernel
     int march_waves = 4;              // wavefronts per block of the march kernel
     int march_depth = 2;              // most steps of its launches
-    std::vector<MarchBox> boxes;      // internal order: march decomposition
     std::vector<int> blk0;            // internal order, size n + 1: march blocks
     char *ws = nullptr;
     size_t ws_bytes = 0;
@@ -622,6 +620,26 @@ void launch_point(const lb_wave *h, const StepArgs &a, hipStream_t st)
 // Most steps of one march launch, and rows per row group.  FP64 holds twice the registers and LDS.
 int march_steps(int storage) { return storage == LB_F64 ? 2 : 3; }
 int march_rows(int storage) { return storage == LB_F64 ? 2 : 4; }
+bool march_eight(int storage) { return storage == LB_F64 || storage == LB_F32; }
+
+using MarchFn = void (*)(StepArgs);
+template <typename S, int K, int R> MarchFn march_fn_t(int waves, int nt)
+{
+    if constexpr (sizeof(typename StoreTraits<S>::R) >= 4)  // march_eight
+        if (waves == 8) return nt ? march_kernel<S, K, R, 8, 1> : march_kernel<S, K, R, 8, 0>;
+    return nt ? march_kernel<S, K, R, 4, 1> : march_kernel<S, K, R, 4, 0>;
+}
+MarchFn march_fn(int storage, int steps, int waves, int nt)
+{
+    const bool three = steps == 3;
+    switch (storage) {
+    case LB_F64: return march_fn_t<double, 2, 2>(waves, nt);
+    case LB_F32: return three ? march_fn_t<float, 3, 4>(waves, nt) : march_fn_t<float, 2, 4>(waves, nt);
+    case LB_F16:
+        return three ? march_fn_t<_Float16, 3, 4>(waves, nt) : march_fn_t<_Float16, 2, 4>(waves, nt);
+    default: return three ? march_fn_t<bf16, 3, 4>(waves, nt) : march_fn_t<bf16, 2, 4>(waves, nt);
+    }
+}
 // Wavefronts of a march block: 8 (one block per CU) or 4 (two).  With 4, a row of 256 cells or a
 // strip makes a block of one row group, which reads (R + 4) / R = 2 times its own rows; 8 make
 // two groups that share their halo rows, 1.5 times.  That pays where the L2 misses of the halo
@@ -720,7 +738,7 @@ int march_depth(const std::vector<InstDev> &inst, int storage, int waves)
 // memory-side cache (see kMallBytes)
 int march_block_waves(const std::vector<InstDev> &inst, int storage)
 {
-    if (elem_bytes(storage) < 4) return 4;
+    if (!march_eight(storage)) return 4;
     int64_t cells = 0, wide = 0;
     for (const InstDev &I : inst) {
         const int64_t c = (int64_t)I.pitch * I.ny * I.nz;
@@ -730,47 +748,43 @@ int march_block_waves(const std::vector<InstDev> &inst, int storage)
     return 2 * wide > cells && cells * 7 * kNumBuf * (int64_t)elem_bytes(storage) > kMallBytes ? 8 : 4;
 }
 
+// Launches of `steps` lattice steps by blocks of `waves` wavefronts: the chunks of planes and the
+// blocks of every instance.  Returns false if a launch would have too many blocks.
+bool plan_march(lb_wave *h, int steps, int waves)
+{
+    const int zchunk = march_zchunk(h->hinst, h->storage, steps, waves);
+    std::vector<int> blk0(h->n + 1, 0);
+    std::vector<MarchBox> boxes(h->n);
+    int64_t total = 0;
+    for (int ii = 0; ii < h->n; ++ii) {
+        boxes[ii] = march_box(h->hinst[ii], h->storage, waves, zchunk);
+        total += boxes[ii].blocks();
+        if (total > INT32_MAX / 2) return false;
+        blk0[ii + 1] = (int)total;
+    }
+    h->march_depth = steps;
+    h->march_waves = waves;
+    for (SegInfo &sg : h->segs) {
+        sg.blk0 = blk0[sg.first];
+        sg.bpi = blk0[sg.first + 1] - blk0[sg.first];
+        sg.nsx = (int)boxes[sg.first].nsx;
+        sg.nyb = (int)boxes[sg.first].nyb;
+    }
+    h->blk0 = std::move(blk0);
+    return true;
+}
+
 // Several steps per launch need ny to be a multiple of the rows of a block: kRuleRows rows per
 // row group.  (The march kernel itself takes any ny; the rule is the interface's.)
 int rule_rows(int storage) { return storage == LB_F32 ? 4 : 2; }
 
-template <typename S, int K, int R, int W>
-void launch_march_w(const lb_wave *h, const StepArgs &a, int blocks, hipStream_t st)
-{
-    if (h->nt == 0)
-        hipLaunchKernelGGL((march_kernel<S, K, R, W, 0>), dim3(blocks), dim3(64 * W), 0, st, a);
-    else
-        hipLaunchKernelGGL((march_kernel<S, K, R, W, 1>), dim3(blocks), dim3(64 * W), 0, st, a);
-}
-
-template <typename S, int K, int R>
-void launch_march_t(const lb_wave *h, const StepArgs &a, int meas_blocks, hipStream_t st)
-{
-    if (h->march_waves == 8)
-        launch_march_w<S, K, R, 8>(h, a, (meas_blocks + 1) / 2 + a.ntask, st);
-    else
-        launch_march_w<S, K, R, 4>(h, a, meas_blocks + a.ntask, st);
-}
-
 void launch_march(const lb_wave *h, const StepArgs &a, int nst, int meas_blocks, hipStream_t st)
 {
-    if (meas_blocks + a.ntask <= 0) return;
-    const bool three = nst == 3;
-    switch (h->storage) {
-    case LB_F64: launch_march_t<double, 2, 2>(h, a, meas_blocks, st); break;
-    case LB_F32:
-        three ? launch_march_t<float, 3, 4>(h, a, meas_blocks, st)
-              : launch_march_t<float, 2, 4>(h, a, meas_blocks, st);
-        break;
-    case LB_F16:
-        three ? launch_march_t<_Float16, 3, 4>(h, a, meas_blocks, st)
-              : launch_march_t<_Float16, 2, 4>(h, a, meas_blocks, st);
-        break;
-    default:
-        three ? launch_march_t<bf16, 3, 4>(h, a, meas_blocks, st)
-              : launch_march_t<bf16, 2, 4>(h, a, meas_blocks, st);
-        break;
-    }
+    const int per = 64 * h->march_waves / kStepThreads;  // measurement blocks side by side
+    const int blocks = (meas_blocks + per - 1) / per + a.ntask;
+    if (blocks > 0)
+        hipLaunchKernelGGL(march_fn(h->storage, nst, h->march_waves, h->nt), dim3(blocks),
+                           dim3(64 * h->march_waves), 0, st, a);
 }
 
 // nst steps of every live box, one block each, with the measurement of the launches before
@@ -1242,34 +1256,6 @@ int lb_wave_create(const lb_wave_desc *descs, int32_t n_inst, void *dev_workspac
         host_blobs.push_back(std::move(blob));
         blob_off.push_back(L.off_sbtab);
     }
-    // march decomposition: row blocks, chunks of planes, strips
-    {
-        h->fused_ok = h->dim == 3 && !h->any_point;
-        bool fits = true;
-        for (const InstDev &I : h->hinst) {
-            const int groups = I.pitch > kMarchMaxPitch ? 1 : 4 / (I.pitch / 64);
-            if (I.xbc != LB_XBC_DRIVEN || I.ny % (rule_rows(h->storage) * groups)) h->fused_ok = false;
-            // lane offsets inside one plane, of the state and of the c^2 table, are 32-bit byte counts
-            if ((int64_t)I.ny * I.pitch * (int64_t)elem_bytes(h->storage) > (int64_t)UINT32_MAX ||
-                c2_plane(I.bb_n[0], I.bb_n[1]) * (int64_t)compute_bytes(h->storage) > (int64_t)UINT32_MAX)
-                fits = false;
-        }
-        h->boxes.resize(n_inst);
-        h->blk0.assign(n_inst + 1, 0);
-        if (h->fused_ok && fits) {
-            h->march_waves = march_block_waves(h->hinst, h->storage);
-            h->march_depth = march_depth(h->hinst, h->storage, h->march_waves);
-            const int zchunk = march_zchunk(h->hinst, h->storage, h->march_depth, h->march_waves);
-            int64_t total = 0;
-            for (int ii = 0; ii < n_inst && total < INT32_MAX / 2; ++ii) {
-                h->boxes[ii] = march_box(h->hinst[ii], h->storage, h->march_waves, zchunk);
-                total += h->boxes[ii].blocks();
-                h->blk0[ii + 1] = (int)std::min<int64_t>(total, INT32_MAX);
-            }
-            h->march_ok = total < INT32_MAX / 2;
-        }
-        if (!h->march_ok) std::fill(h->blk0.begin(), h->blk0.end(), 0);
-    }
     // segments: maximal runs of equal shape in internal order
     for (int ii = 0; ii < n_inst; ++ii) {
         const InstDev &I = h->hinst[ii];
@@ -1284,11 +1270,24 @@ int lb_wave_create(const lb_wave_desc *descs, int32_t n_inst, void *dev_workspac
             sg.nz = I.nz;
             sg.xsegs = (I.nx + 63) / 64;
             sg.tpi = sg.xsegs * I.ny * I.nz;
-            sg.blk0 = h->blk0[ii];
-            sg.bpi = h->blk0[ii + 1] - h->blk0[ii];
-            sg.nsx = (int)h->boxes[ii].nsx;
-            sg.nyb = (int)h->boxes[ii].nyb;
             h->segs.push_back(sg);
+        }
+    }
+    // march decomposition: row blocks, chunks of planes, strips
+    {
+        h->fused_ok = h->dim == 3 && !h->any_point;
+        bool fits = true;
+        for (const InstDev &I : h->hinst) {
+            const int groups = I.pitch > kMarchMaxPitch ? 1 : 4 / (I.pitch / 64);
+            if (I.xbc != LB_XBC_DRIVEN || I.ny % (rule_rows(h->storage) * groups)) h->fused_ok = false;
+            // lane offsets inside one plane, of the state and of the c^2 table, are 32-bit byte counts
+            if ((int64_t)I.ny * I.pitch * (int64_t)elem_bytes(h->storage) > (int64_t)UINT32_MAX ||
+                c2_plane(I.bb_n[0], I.bb_n[1]) * (int64_t)compute_bytes(h->storage) > (int64_t)UINT32_MAX)
+                fits = false;
+        }
+        if (h->fused_ok && fits) {
+            const int waves = march_block_waves(h->hinst, h->storage);
+            h->march_ok = plan_march(h, march_depth(h->hinst, h->storage, waves), waves);
         }
     }
 
@@ -1365,6 +1364,28 @@ int lb_wave_get_launch_steps(const lb_wave *h, int32_t *k)
 {
     if (!h || !k) return fail(LB_EINVAL, "NULL argument");
     *k = most_steps(h);
+    return LB_OK;
+}
+
+int lb_wave_set_launch_plan(lb_wave *h, int32_t steps, int32_t waves)
+{
+    if (!h) return fail(LB_EINVAL, "handle is NULL");
+    if (!h->march_ok) return fail(LB_EINVAL, "this handle runs one step per launch");
+    if (steps < 2 || steps > march_steps(h->storage))
+        return fail(LB_EINVAL, "steps must lie in 2 .. %d", march_steps(h->storage));
+    if (waves != 4 && (waves != 8 || !march_eight(h->storage)))
+        return fail(LB_EINVAL, "waves must be 4%s", march_eight(h->storage) ? " or 8" : "");
+    if (steps == h->march_depth && waves == h->march_waves) return LB_OK;
+    drop_graphs(h);
+    if (!plan_march(h, steps, waves)) return fail(LB_EINVAL, "too many blocks");
+    return LB_OK;
+}
+
+int lb_wave_get_launch_plan(const lb_wave *h, int32_t *steps, int32_t *waves)
+{
+    if (!h || !steps || !waves) return fail(LB_EINVAL, "NULL argument");
+    *steps = h->march_ok ? h->march_depth : 1;
+    *waves = h->march_ok ? h->march_waves : 0;
     return LB_OK;
 }
 
@@ -1592,7 +1613,10 @@ int lb_wave_autotune(lb_wave *h, int32_t n_trial, double *best_ms)
     HIP_TRY(hipEventCreate(&e0));
     HIP_TRY(hipEventCreate(&e1));
     double best = 1e300;
-    int bv[4] = {1, 0, 0, 1};  // cells per lane, x mode, nontemporal, steps per launch
+    struct Choice {
+        int cells, x_mode, nt, steps, waves;  // waves of a march block, 0: step_kernel
+    };
+    Choice bv = {1, 0, 0, 1, 0};
     const int xm_max = elem_bytes(h->storage) >= 4 ? 1 : 0;
     auto time_it = [&](double *per) -> int {
         const int nst = most_steps(h);
@@ -1610,32 +1634,36 @@ int lb_wave_autotune(lb_wave *h, int32_t n_trial, double *best_ms)
         *per = ms / trial;
         return LB_OK;
     };
-    std::vector<std::array<int, 4>> cand;
+    // every variant of the step kernel, then every plan of the march kernel: which number of steps and
+    // of wavefronts is the faster depends on how the boxes divide over the chip
+    std::vector<Choice> cand;
     const bool one = h->lay.resident;  // one kernel whatever the variant: time the present one
-    if (one) cand.push_back({h->vx, h->xm, h->nt, 1});
+    if (one) cand.push_back({h->vx, h->xm, h->nt, 1, 0});
     for (int cpl : {1, 2, 4})
         for (int xm = 0; xm <= xm_max && !one; ++xm)
-            for (int nt = 0; nt <= 2; ++nt) cand.push_back({cpl, xm, nt, 1});
-    if (h->fused_ok)
-        for (int nt = 0; nt <= 1; ++nt) cand.push_back({1, xm_max, nt, 2});
+            for (int nt = 0; nt <= 2; ++nt) cand.push_back({cpl, xm, nt, 1, 0});
+    for (int steps = 2; h->march_ok && steps <= march_steps(h->storage); ++steps)
+        for (int waves = 4; waves <= (march_eight(h->storage) ? 8 : 4); waves += 4)
+            for (int nt = 0; nt <= 1; ++nt) cand.push_back({1, xm_max, nt, steps, waves});
+    auto apply = [&](const Choice &c) -> int {
+        int st = lb_wave_set_steps_per_launch(h, c.steps > 1 ? 2 : 1);
+        if (!st && c.steps > 1) st = lb_wave_set_launch_plan(h, c.steps, c.waves);
+        return st ? st : lb_wave_set_variant(h, c.cells, c.x_mode, c.nt);
+    };
     for (const auto &c : cand) {
-        int st = lb_wave_set_steps_per_launch(h, c[3]);
-        if (st) return st;
-        st = lb_wave_set_variant(h, c[0], c[1], c[2]);
+        int st = apply(c);
         if (st) return st;
         double per = 0.0;
         st = time_it(&per);
         if (st) return st;
         if (per < best) {
             best = per;
-            for (int i = 0; i < 4; ++i) bv[i] = c[i];
+            bv = c;
         }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    int st = lb_wave_set_steps_per_launch(h, bv[3]);
-    if (st) return st;
-    st = lb_wave_set_variant(h, bv[0], bv[1], bv[2]);
+    int st = apply(bv);
     if (st) return st;
     if (best_ms) *best_ms = best;
     st = zero_state(h);

@@ -84,6 +84,8 @@ def lib():
         L.lb_wave_set_steps_per_launch.argtypes = [vp, C.c_int32]
         L.lb_wave_get_steps_per_launch.argtypes = [vp, C.POINTER(C.c_int32)]
         L.lb_wave_get_launch_steps.argtypes = [vp, C.POINTER(C.c_int32)]
+        L.lb_wave_set_launch_plan.argtypes = [vp, C.c_int32, C.c_int32]
+        L.lb_wave_get_launch_plan.argtypes = [vp, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]
         L.lb_wave_get_tile.argtypes = [vp, C.POINTER(C.c_int32)]
         L.lb_wave_autotune.argtypes = [vp, C.c_int32, _dp]
         L.lb_stream_copy.argtypes = [vp, vp, C.c_size_t, vp]
@@ -289,6 +291,16 @@ class LBWave:
         v = C.c_int32()
         _check(lib().lb_wave_get_launch_steps(self._h, C.byref(v)))
         return v.value
+
+    def set_launch_plan(self, steps: int, waves: int):
+        """Steps per launch (2 or 3) and wavefronts per block of the launches of several steps."""
+        _check(lib().lb_wave_set_launch_plan(self._h, int(steps), int(waves)))
+
+    def launch_plan(self):
+        """(steps, waves) of the launches of several steps; (1, 0) where there are none."""
+        a, b = C.c_int32(), C.c_int32()
+        _check(lib().lb_wave_get_launch_plan(self._h, C.byref(a), C.byref(b)))
+        return a.value, b.value
 
     def tile(self) -> int:
         v = C.c_int32()
