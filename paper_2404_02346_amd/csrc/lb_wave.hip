@@ -640,7 +640,15 @@ MarchFn march_fn(int storage, int steps, int waves, int nt)
     default: return three ? march_fn_t<bf16, 3, 4>(waves, nt) : march_fn_t<bf16, 2, 4>(waves, nt);
     }
 }
-// Wavefronts of a march block: 8 (one block per CU) or 4 (two).  With 4, a row of 256 cells or a
+// blocks of it that a CU holds at once
+int march_blocks_per_cu(int storage, int steps, int waves)
+{
+    int n = 0;
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &n, reinterpret_cast<const void *>(march_fn(storage, steps, waves, 1)), 64 * waves, 0);
+    return e == hipSuccess && n > 0 ? n : 8 / waves;
+}
+// Wavefronts of a march block: 8 (one block per CU) or 4 (two or three).  With 4, a row of 256 cells or a
 // strip makes a block of one row group, which reads (R + 4) / R = 2 times its own rows; 8 make
 // two groups that share their halo rows, 1.5 times.  That pays where the L2 misses of the halo
 // rows are on the critical path, in handles larger than the memory-side cache (16 FP32 spheres of
@@ -648,6 +656,12 @@ MarchFn march_fn(int storage, int steps, int waves, int nt)
 // 16-bit storage, which is bound by its instructions, two independent blocks hide each other's
 // barriers better (one FP32 sphere: 20.1 against 22.8; 16 in FP16: 178 against 197).
 constexpr int64_t kMallBytes = 256 << 20;
+int64_t state_bytes(const std::vector<InstDev> &inst, int storage)
+{
+    int64_t cells = 0;
+    for (const InstDev &I : inst) cells += (int64_t)I.pitch * I.ny * I.nz;
+    return cells * 7 * kNumBuf * (int64_t)elem_bytes(storage);
+}
 
 MarchBox march_box(const InstDev &I, int storage, int waves, int zchunk)
 {
@@ -660,12 +674,13 @@ MarchBox march_box(const InstDev &I, int storage, int waves, int zchunk)
 }
 
 // Time of one launch with chunks of at most zchunk planes, in iterations of a block: every XCD
-// takes an eighth of the blocks, in order, and as one ends its place (a CU holds one block of 8
-// wavefronts or two of 4) takes the next.  A block runs its planes and the K - 1 halo planes at
-// both ends; two on a CU take 1.4 times as long as one alone (measured: 1.6 from HBM, 1.2 from the
-// memory-side cache), 1.15 times in 16-bit storage, where each waits for its own instructions (96^3
-// in FP16: 10.1 us per step with the chunks that this gives, 12.0 with those of 1.4).
-double march_time(const std::vector<InstDev> &inst, int storage, int k, int waves, int zchunk)
+// takes an eighth of the blocks, in order, and as one ends its place (a CU holds per_cu blocks) takes
+// the next.  A block runs its planes and the K - 1 halo planes at both ends; two on a CU take 1.4
+// times as long as one alone (measured: 1.6 from HBM, 1.2 from the memory-side cache); in 16-bit
+// storage, where each waits for its own instructions, two take 1.15 and three 1.3 times as long (FP16,
+// us per step with the chunks that this gives and with those for two: 160^3 20.7 and 27.9,
+// 300 x 96 x 96 16.9 and 20.9, three of 488 x 32 x 32 11.4 and 12.3).
+double march_time(const std::vector<InstDev> &inst, int storage, int k, int waves, int per_cu, int zchunk)
 {
     std::vector<std::pair<int64_t, double>> runs;  // blocks, iterations
     int64_t n = 0;
@@ -675,7 +690,7 @@ double march_time(const std::vector<InstDev> &inst, int storage, int k, int wave
                                         2.0 * (k - 1) + 1.0});
         n += m.blocks();
     }
-    const int places = 32 * 8 / waves;
+    const int places = 32 * per_cu;
     double worst = 0.0;
     size_t r = 0;
     int64_t used = 0;
@@ -694,7 +709,8 @@ double march_time(const std::vector<InstDev> &inst, int storage, int k, int wave
         }
         worst = std::max(worst, last);
     }
-    return worst * (waves == 4 && n > 256 ? (elem_bytes(storage) < 4 ? 1.15 : 1.4) : 1.0);
+    const int64_t share = std::min<int64_t>(per_cu, (n + 255) / 256);
+    return worst * (1.0 + (elem_bytes(storage) < 4 ? 0.15 : 0.4) * (double)(share - 1));
 }
 
 // The chunk length with the shortest such time; handles of very many blocks, where the ends
@@ -707,9 +723,10 @@ int march_zchunk(const std::vector<InstDev> &inst, int storage, int k, int waves
     for (const InstDev &I : inst) n += march_box(I, storage, waves, 64).blocks();
     int best = 64;
     if (n > 8192) return best;
-    double best_time = march_time(inst, storage, k, waves, best);
+    const int per_cu = march_blocks_per_cu(storage, k, waves);
+    double best_time = march_time(inst, storage, k, waves, per_cu, best);
     for (int zc : {128, 96, 48, 40, 32, 28, 24, 20, 16, 12, 10, 8, 6, 5, 4, 3, 2, 1}) {
-        const double time = march_time(inst, storage, k, waves, zc);
+        const double time = march_time(inst, storage, k, waves, per_cu, zc);
         if (time < best_time) {
             best_time = time;
             best = zc;
@@ -718,20 +735,21 @@ int march_zchunk(const std::vector<InstDev> &inst, int storage, int k, int waves
     return best;
 }
 
-// Steps of a launch: the most, but in 16-bit storage two where the boxes are short in z for the CUs
-// there are, so that the planes computed twice at the ends of the chunks count for more.  An iteration
-// of three steps takes 1.3 to 1.4 times as long as one of two, hence the line.  FP16 and BF16, us per
-// step with two and three: 96^3 10.1 and 13.2, 122 x 64 x 64 7.1 and 9.0, 134 x 128 x 128 17.9 and 19.4
-// (iterations per step of three to two: 0.82, 0.89 and 0.78); 4 of 134 x 128 x 128 (0.70) 52.5 and 50.3,
-// 16 of 256 x 128 x 128 (0.68) 207 and 179.
+// Steps of a launch: the most, but in 16-bit storage two, whose blocks need the registers for three
+// on a CU, unless the states outgrow the memory-side cache, where the traffic of a launch counts, and
+// the schedule does not lose more.  FP16 and BF16, us per step with two and three: 96^3 10.0 and
+// 11.7, 192^3 27.3 and 32.7, 16 of 64^3 23.7 and 25.6; beyond the cache 16 of 256 x 128 x 128 (an
+// iteration count per step of three to two of 0.85) 214 and 178, 4 of them (0.88) 57 and 51, 8 of 192^3
+// (0.96) 178 and 201, 512 x 256 x 256 (0.99) 131 and 140.
 int march_depth(const std::vector<InstDev> &inst, int storage, int waves)
 {
     const int most = march_steps(storage);
     if (elem_bytes(storage) >= 4) return most;
     auto per_step = [&](int k) {
-        return march_time(inst, storage, k, waves, march_zchunk(inst, storage, k, waves)) / k;
+        return march_time(inst, storage, k, waves, march_blocks_per_cu(storage, k, waves),
+                          march_zchunk(inst, storage, k, waves)) / k;
     };
-    return per_step(most) < 0.72 * per_step(2) ? most : 2;
+    return state_bytes(inst, storage) > kMallBytes && per_step(most) < 0.92 * per_step(2) ? most : 2;
 }
 
 // 8 wavefronts where most cells lie in rows that fill a block of 4 and the states outgrow the
@@ -745,7 +763,7 @@ int march_block_waves(const std::vector<InstDev> &inst, int storage)
         cells += c;
         if (I.pitch >= 256) wide += c;
     }
-    return 2 * wide > cells && cells * 7 * kNumBuf * (int64_t)elem_bytes(storage) > kMallBytes ? 8 : 4;
+    return 2 * wide > cells && state_bytes(inst, storage) > kMallBytes ? 8 : 4;
 }
 
 // Launches of `steps` lattice steps by blocks of `waves` wavefronts: the chunks of planes and the
