@@ -735,21 +735,27 @@ int march_zchunk(const std::vector<InstDev> &inst, int storage, int k, int waves
     return best;
 }
 
-// Steps of a launch: the most, but in 16-bit storage two, whose blocks need the registers for three
-// on a CU, unless the states outgrow the memory-side cache, where the traffic of a launch counts, and
-// the schedule does not lose more.  FP16 and BF16, us per step with two and three: 96^3 10.0 and
-// 11.7, 192^3 27.3 and 32.7, 16 of 64^3 23.7 and 25.6; beyond the cache 16 of 256 x 128 x 128 (an
-// iteration count per step of three to two of 0.85) 214 and 178, 4 of them (0.88) 57 and 51, 8 of 192^3
-// (0.96) 178 and 201, 512 x 256 x 256 (0.99) 131 and 140.
+// Steps of a launch of a handle that is not tuned (FP64 has two only).  An iteration of three
+// steps takes 1.2 to 1.4 times as long as one of two, so three pay where the planes computed twice at
+// the ends of the chunks do not eat up the launch that is saved.
+//  * FP32: where the model's iterations per step are below 0.8 of those with two.  us per step with two
+//    and three: 64^3 (0.93) 6.4 and 7.2, 1456 x 32 x 32 (0.83) 12.6 and 17.4, 251 x 64 x 64 (0.83) 11.4
+//    and 11.8, 128^3 (0.83) 14.8 and 16.9, 96^3 (0.82) 12.8 and 12.7, two of 128^3 (0.78) 22.9 and 20.4,
+//    160^3 (0.73) 31.2 and 27.9, 16 of 256 x 128 x 128 (0.68) 412 and 268.
+//  * 16 bit: blocks of two steps leave registers for three on a CU.  Two, unless the states outgrow the
+//    memory-side cache, where the traffic of a launch counts, and the schedule does not lose more.
+//    FP16 and BF16, two and three: 96^3 10.0 and 11.7, 192^3 27.3 and 32.7, 16 of 64^3 23.7 and 25.6;
+//    beyond the cache 16 of 256 x 128 x 128 (0.85) 214 and 178, 4 of them (0.88) 57 and 51, 8 of 192^3
+//    (0.96) 178 and 201, 512 x 256 x 256 (0.99) 131 and 140.
 int march_depth(const std::vector<InstDev> &inst, int storage, int waves)
 {
-    const int most = march_steps(storage);
-    if (elem_bytes(storage) >= 4) return most;
+    if (march_steps(storage) == 2) return 2;
     auto per_step = [&](int k) {
         return march_time(inst, storage, k, waves, march_blocks_per_cu(storage, k, waves),
                           march_zchunk(inst, storage, k, waves)) / k;
     };
-    return state_bytes(inst, storage) > kMallBytes && per_step(most) < 0.92 * per_step(2) ? most : 2;
+    if (storage == LB_F32) return per_step(3) < 0.8 * per_step(2) ? 3 : 2;
+    return state_bytes(inst, storage) > kMallBytes && per_step(3) < 0.92 * per_step(2) ? 3 : 2;
 }
 
 // 8 wavefronts where most cells lie in rows that fill a block of 4 and the states outgrow the

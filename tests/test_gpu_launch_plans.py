@@ -107,3 +107,13 @@ def test_autotune_takes_a_plan_and_resets(P, storage):
         assert np.array_equal(h.get_state(i), ref[0][i]) and np.array_equal(h.trace(i, 20), ref[1][i])
     assert np.array_equal(h.force()[0], ref[2])
     h.close()
+
+
+@pytest.mark.parametrize("storage,shape,n,steps", [
+    ("f32", (128, 128, 128), 1, 2), ("f32", (1456, 32, 32), 1, 2), ("f32", (64, 64, 64), 1, 2),
+    ("f32", (128, 128, 128), 4, 3), ("f32", (192, 192, 192), 1, 3), ("f16", (192, 192, 192), 1, 2)])
+def test_untuned_steps_per_launch(P, storage, shape, n, steps):
+    # the faster of two and three steps where they differ by more than a tenth
+    h = P.LBWave([dict(problem(shape, 0.5 * shape[0]))] * n, storage=storage)
+    assert h.launch_plan()[0] == steps
+    h.close()
