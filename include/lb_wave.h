@@ -214,11 +214,13 @@ int lb_wave_state_view(const lb_wave *h, int32_t inst, lb_state_view *v);
  *   nontemporal 0: plain loads and stores, 1: non-temporal stores,
  *     2: non-temporal loads and stores.
  * Every variant computes bit-identical results.  lb_wave_autotune times every
- * valid variant, and every plan of several steps per launch where allowed, for n_trial steps
- * (rounded up to whole launches) on the handle's own instances, keeps the fastest,
- * then resets the state (lb_wave_reset); best_ms (may be NULL) receives the
- * winning time per step in ms.  set_tile/get_tile change or read
- * cells_per_lane only. */
+ * valid variant, and every plan of several steps per launch where allowed, for
+ * n_trial steps on the handle's own instances (fewer where one is clearly
+ * slower, more where the first are close), keeps the fastest, then resets the
+ * state (lb_wave_reset).  2D handles that run many steps per launch (see
+ * below) use the variant in shorter calls.  best_ms (may be NULL) receives the
+ * winning time per step of a long call in ms.  set_tile/get_tile change or
+ * read cells_per_lane only. */
 int lb_wave_set_variant(lb_wave *h, int32_t cells_per_lane, int32_t x_mode, int32_t nontemporal);
 int lb_wave_get_variant(const lb_wave *h, int32_t *cells_per_lane, int32_t *x_mode,
                         int32_t *nontemporal);

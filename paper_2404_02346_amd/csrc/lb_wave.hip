@@ -472,6 +472,7 @@ struct lb_wave {
     int fused = 1;                    // 1: one lattice step per launch, 2: several
     bool fused_ok = false;            // several steps per launch are allowed
     bool march_ok = false;            // every instance fits the march kernel
+    bool resident = false;            // long calls run the resident kernel
     int march_waves = 4;              // wavefronts per block of the march kernel
     int march_depth = 2;              // most steps of its launches
     std::vector<int> blk0;            // internal order, size n + 1: march blocks
@@ -874,7 +875,7 @@ void emit_step(const lb_wave *h, StepArgs a, int64_t t, int32_t dt, int dbuf, in
                hipStream_t st)
 {
     const int na = active_prefix(h, t);
-    if (h->lay.resident && nst > 1) {
+    if (h->resident && nst > 1) {
         a.dt = dt;
         a.dbuf = dbuf;
         a.nst = nst;
@@ -1048,6 +1049,34 @@ int replay_steps(lb_wave *h, int k, int nst)
     return LB_OK;
 }
 
+// n steps without the launches that finish their measurement
+int enqueue_steps(lb_wave *h, int64_t left)
+{
+    while (left > 0) {
+        // a replayed sequence holds launches of nst steps only: the chunk rounded down to them
+        const int most = most_steps(h), nst = std::min(most, std::max(h->graph_chunk, 1));
+        const int k = h->graph_chunk / nst * nst;
+        int st;
+        if (h->resident && left >= kResidentMin) {
+            const int64_t launches = (left + kResidentSteps - 1) / kResidentSteps;
+            const int n = (int)((left + launches - 1) / launches);  // equal shares: no short rest
+            st = enqueue_step(h, n);
+            left -= n;
+        } else if (k >= 2 && left >= k && steady(h, k, nst)) {
+            st = replay_steps(h, k, nst);
+            left -= k;
+        } else {
+            // before the first replay launches of its size fill the measurement pipeline
+            int n = k >= 2 && left >= k ? nst : next_steps(left, most);
+            n = fuse_steps(h, n);
+            st = enqueue_step(h, n);
+            left -= n;
+        }
+        if (st != LB_OK) return st;
+    }
+    return LB_OK;
+}
+
 void drop_graphs(lb_wave *h)
 {
     for (auto &g : h->graphs) (void)hipGraphExecDestroy(g.exec);
@@ -1134,6 +1163,7 @@ int lb_wave_create(const lb_wave_desc *descs, int32_t n_inst, void *dev_workspac
     h->ws_bytes = workspace_bytes;
     h->stream = static_cast<hipStream_t>(hip_stream);
     h->lay = L;
+    h->resident = L.resident;
     h->desc.assign(descs, descs + n_inst);
     for (auto &d : h->desc) {  // the host arrays are not kept
         d.c_field = nullptr;
@@ -1339,30 +1369,8 @@ int lb_wave_step_n(lb_wave *h, int64_t n_steps)
     if (!h) return fail(LB_EINVAL, "handle is NULL");
     if (n_steps < 0) return fail(LB_EINVAL, "n_steps < 0");
     if (h->nan_seen) return fail(LB_ENAN, "a previous force was not finite");
-    int64_t left = n_steps;
-    while (left > 0) {
-        // a replayed sequence holds launches of nst steps only: the chunk rounded down to them
-        const int most = most_steps(h), nst = std::min(most, std::max(h->graph_chunk, 1));
-        const int k = h->graph_chunk / nst * nst;
-        int st;
-        if (h->lay.resident && left >= kResidentMin) {
-            const int64_t launches = (left + kResidentSteps - 1) / kResidentSteps;
-            const int n = (int)((left + launches - 1) / launches);  // equal shares: no short rest
-            st = enqueue_step(h, n);
-            left -= n;
-        } else if (k >= 2 && left >= k && steady(h, k, nst)) {
-            st = replay_steps(h, k, nst);
-            left -= k;
-        } else {
-            // before the first replay launches of its size fill the measurement pipeline
-            int n = k >= 2 && left >= k ? nst : next_steps(left, most);
-            n = fuse_steps(h, n);
-            st = enqueue_step(h, n);
-            left -= n;
-        }
-        if (st != LB_OK) return st;
-    }
-    return flush_measure(h);
+    const int st = enqueue_steps(h, n_steps);
+    return st ? st : flush_measure(h);
 }
 
 int lb_wave_set_steps_per_launch(lb_wave *h, int32_t k)
@@ -1633,65 +1641,117 @@ int lb_wave_autotune(lb_wave *h, int32_t n_trial, double *best_ms)
 {
     if (!h) return fail(LB_EINVAL, "handle is NULL");
     if (n_trial < 1) return fail(LB_EINVAL, "n_trial must be >= 1");
-    hipEvent_t e0, e1;
-    HIP_TRY(hipEventCreate(&e0));
-    HIP_TRY(hipEventCreate(&e1));
-    double best = 1e300;
-    struct Choice {
-        int cells, x_mode, nt, steps, waves;  // waves of a march block, 0: step_kernel
-    };
-    Choice bv = {1, 0, 0, 1, 0};
-    const int xm_max = elem_bytes(h->storage) >= 4 ? 1 : 0;
-    auto time_it = [&](double *per) -> int {
-        const int nst = most_steps(h);
-        const int whole = std::max(2, nst);  // even, or whole launches of three steps
-        const int trial = (n_trial + whole - 1) / whole * whole;
-        int st = lb_wave_step_n(h, whole);  // warm-up
-        if (st) return st;
-        HIP_TRY(hipEventRecord(e0, h->stream));
-        st = lb_wave_step_n(h, trial);
-        if (st) return st;
-        HIP_TRY(hipEventRecord(e1, h->stream));
-        HIP_TRY(hipEventSynchronize(e1));
-        float ms = 0.f;
-        HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
-        *per = ms / trial;
+    if (h->nan_seen) return fail(LB_ENAN, "a previous force was not finite");
+    struct Scope {  // plain launches of the step or march kernel while tuning
+        lb_wave *h;
+        int chunk;
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        explicit Scope(lb_wave *w) : h(w), chunk(w->graph_chunk)
+        {
+            h->graph_chunk = 0;
+            h->resident = false;
+        }
+        ~Scope()
+        {
+            h->graph_chunk = chunk;
+            h->resident = h->lay.resident;
+            if (e0) (void)hipEventDestroy(e0);
+            if (e1) (void)hipEventDestroy(e1);
+        }
+    } scope(h);
+    HIP_TRY(hipEventCreate(&scope.e0));
+    HIP_TRY(hipEventCreate(&scope.e1));
+    // ms per step of `steps` steps after `warm` others, the least of `repeats` runs, each from step 0
+    // (no instance has stopped) and without the launches that finish the measurement of a call: in
+    // a long run they do not count.  The populations move on; they are reset at the end.
+    auto time_it = [&](int warm, int steps, int repeats, double *per) -> int {
+        *per = 1e300;
+        for (int r = 0; r < repeats; ++r) {
+            h->t = h->meas = h->red = 0;
+            set_counter(h);
+            int st = enqueue_steps(h, warm);
+            if (st) return st;
+            HIP_TRY(hipEventRecord(scope.e0, h->stream));
+            if ((st = enqueue_steps(h, steps))) return st;
+            HIP_TRY(hipEventRecord(scope.e1, h->stream));
+            if ((st = flush_measure(h))) return st;
+            HIP_TRY(hipEventSynchronize(scope.e1));
+            float ms = 0.f;
+            HIP_TRY(hipEventElapsedTime(&ms, scope.e0, scope.e1));
+            *per = std::min(*per, (double)ms / steps);
+        }
         return LB_OK;
     };
-    // every variant of the step kernel, then every plan of the march kernel: which number of steps and
-    // of wavefronts is the faster depends on how the boxes divide over the chip
-    std::vector<Choice> cand;
-    const bool one = h->lay.resident;  // one kernel whatever the variant: time the present one
-    if (one) cand.push_back({h->vx, h->xm, h->nt, 1, 0});
-    for (int cpl : {1, 2, 4})
-        for (int xm = 0; xm <= xm_max && !one; ++xm)
-            for (int nt = 0; nt <= 2; ++nt) cand.push_back({cpl, xm, nt, 1, 0});
-    for (int steps = 2; h->march_ok && steps <= march_steps(h->storage); ++steps)
-        for (int waves = 4; waves <= (march_eight(h->storage) ? 8 : 4); waves += 4)
-            for (int nt = 0; nt <= 1; ++nt) cand.push_back({1, xm_max, nt, steps, waves});
+    struct Choice {
+        int cells, x_mode, nt, steps, waves;  // waves of a march block, 0: step_kernel
+        double ms = 1e300;                    // per step
+    };
     auto apply = [&](const Choice &c) -> int {
         int st = lb_wave_set_steps_per_launch(h, c.steps > 1 ? 2 : 1);
         if (!st && c.steps > 1) st = lb_wave_set_launch_plan(h, c.steps, c.waves);
         return st ? st : lb_wave_set_variant(h, c.cells, c.x_mode, c.nt);
     };
-    for (const auto &c : cand) {
-        int st = apply(c);
-        if (st) return st;
-        double per = 0.0;
-        st = time_it(&per);
-        if (st) return st;
-        if (per < best) {
-            best = per;
-            bv = c;
+    int64_t life = INT32_MAX;  // steps until the first instance stops
+    for (const InstDev &I : h->hinst)
+        if (I.max_steps > 0) life = std::min(life, I.max_steps);
+    auto whole = [&](double n, int steps) {  // launches of `steps` for n steps, while all instances live
+        const int64_t most = std::max<int64_t>(steps, (life - steps) / steps * steps);
+        return (int)std::min((int64_t)std::ceil(n / steps) * steps, most);
+    };
+
+    // every plan of the march kernel (which number of steps and of wavefronts wins depends on how the
+    // boxes divide over the chip), and every variant of the step kernel
+    const int xm_max = elem_bytes(h->storage) >= 4 ? 1 : 0;
+    std::vector<Choice> cand;
+    for (int steps = 2; h->march_ok && steps <= march_steps(h->storage); ++steps)
+        for (int waves = 4; waves <= (march_eight(h->storage) ? 8 : 4); waves += 4)
+            for (int nt = 0; nt <= 1; ++nt) cand.push_back({1, xm_max, nt, steps, waves});
+    const size_t n_plans = cand.size();
+    for (int cpl : {1, 2, 4})
+        for (int xm = 0; xm <= xm_max; ++xm)
+            for (int nt = 0; nt <= 2; ++nt) cand.push_back({cpl, xm, nt, 1, 0});
+    double win = 1e300;
+    int st = LB_OK;
+    for (Choice &c : cand) {
+        if ((st = apply(c))) return st;
+        const int warm = std::max(2, c.steps);
+        // where a trial is long, a first look at three steps or one launch: what is a quarter slower is
+        // not looked at again
+        if (n_trial * win > 0.1 && win < 1e300) {
+            if ((st = time_it(warm, whole(3, c.steps), 1, &c.ms))) return st;
+            if (c.ms > 1.25 * win + 0.003) continue;
         }
+        if ((st = time_it(warm, whole(n_trial, c.steps), 1, &c.ms))) return st;
+        win = std::min(win, c.ms);
     }
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
-    int st = apply(bv);
-    if (st) return st;
-    if (best_ms) *best_ms = best;
-    st = zero_state(h);
-    if (st) return st;
+    const auto faster = [](const Choice &x, const Choice &y) { return x.ms < y.ms; };
+    Choice best = *std::min_element(cand.begin(), cand.end(), faster);
+    if (n_plans > 0) {
+        Choice plan = *std::min_element(cand.begin(), cand.begin() + n_plans, faster);
+        // short steps of plans that lie within a few percent of each other: the first three again,
+        // over at least 300 us, the least of three runs
+        if (n_trial * best.ms < 2.0) {
+            std::stable_sort(cand.begin(), cand.end(), faster);
+            cand.resize(3);
+            for (Choice &c : cand) {
+                const int n = whole(std::max((double)n_trial, std::min(96.0, 0.3 / best.ms)), c.steps);
+                if ((st = apply(c)) || (st = time_it(c.steps, n, 3, &c.ms))) return st;
+            }
+            best = *std::min_element(cand.begin(), cand.end(), faster);
+            if (best.steps > 1) plan = best;
+            win = best.ms;
+        }
+        if ((st = apply(plan))) return st;  // kept, also where one step per launch wins
+    }
+    if ((st = apply(best))) return st;
+    if (h->lay.resident) {  // long calls run the resident kernel, whatever the variant
+        h->resident = true;
+        double ms = 0.0;
+        if ((st = time_it(kResidentSteps, kResidentSteps, 1, &ms))) return st;
+        win = std::min(win, ms);
+    }
+    if (best_ms) *best_ms = win;
+    if ((st = zero_state(h))) return st;
     HIP_TRY(hipStreamSynchronize(h->stream));
     return LB_OK;
 }
