@@ -355,9 +355,17 @@ struct Layout {
 // steps: 28, 8.5, 5.0 and 1.9, with a launch per step 10, 6.5, 5.9 and 4.7; 512 such boxes: 108, 35,
 // 22 and 10, with a launch per step 87, 80, 79 and 78.
 constexpr int kResidentMin = 8;
-// Its moment boxes, one for each step of two launches, may take this much: handles of thousands of
-// boxes with large surfaces keep the small workspace of one step per launch.
+// Its moment boxes and partial sums, one for each step of two launches, may take this much: handles of
+// thousands of boxes with large surfaces keep the small workspace of one step per launch.  So do those
+// whose surface blocks, those of all steps in one launch, are more threads than a grid holds.
 constexpr size_t kResidentBytes = (size_t)8 << 30;
+// blocks of a launch over `boxes` boxes with `meas` measurement blocks of kStepThreads threads, which
+// run side by side
+int64_t resident_grid(int64_t boxes, int64_t meas)
+{
+    const int per = 64 * kResidentWaves / kStepThreads;
+    return boxes + (meas + per - 1) / per;
+}
 int resident_of(const lb_wave_desc &d)
 {
     if (d.dim != 2 || d.xbc != LB_XBC_DRIVEN || d.src_kind != LB_SRC_SHEET) return 0;
@@ -379,9 +387,12 @@ Layout plan(const lb_wave_desc *descs, int n)
         L.n_sb_total += (descs[i].n_surf + 63) / 64;
         if (!resident_of(descs[i])) L.resident = false;
         if (L.resident)
-            slot_bytes += align_up(4 * compute_bytes(descs[i].storage) * measure_box(descs[i]).cells());
+            slot_bytes += align_up(4 * compute_bytes(descs[i].storage) * measure_box(descs[i]).cells()) +
+                          sizeof(double) * 4 * (size_t)((descs[i].n_surf + 63) / 64);
     }
     if (slot_bytes > kResidentBytes / (2 * kResidentSteps)) L.resident = false;
+    if (resident_grid(n, n + (int64_t)kResidentSteps * L.n_sb_total) * 64 * kResidentWaves > (int64_t)UINT32_MAX)
+        L.resident = false;
     L.slots = L.resident ? 2 * kResidentSteps : kNumSlot;
     L.off_sbtab = off;
     off = align_up(off + sizeof(int32_t) * 2 * (size_t)L.n_sb_total);
@@ -815,8 +826,7 @@ void launch_march(const lb_wave *h, const StepArgs &a, int nst, int meas_blocks,
 // nst steps of every live box, one block each, with the measurement of the launches before
 void launch_resident(const lb_wave *h, const StepArgs &a, int meas_blocks, hipStream_t st)
 {
-    const int waves = kResidentWaves, per = 64 * waves / kStepThreads;
-    const dim3 grid(a.ntask + (meas_blocks + per - 1) / per), threads(64 * waves);
+    const dim3 grid((unsigned)resident_grid(a.ntask, meas_blocks)), threads(64 * kResidentWaves);
     switch (h->storage) {
     case LB_F64: hipLaunchKernelGGL(resident_kernel<double>, grid, threads, 0, st, a); break;
     case LB_F32: hipLaunchKernelGGL(resident_kernel<float>, grid, threads, 0, st, a); break;
