@@ -235,9 +235,11 @@ int lb_wave_autotune(lb_wave *h, int32_t n_trial, double *best_ms);
  * every instance 3D with driven x sheets and ny a multiple of R * 4 / nw rows
  * (R = 4 for FP32 and 2 for the other storage types; nw = pitch / 64
  * wavefronts cover a row up to 256 cells, nw = 4 for longer rows); otherwise
- * LB_EINVAL.  Results are bit-identical either way; launches are shorter where
- * an instance stops and for remainders.  lb_wave_autotune also tries several
- * steps per launch when allowed.
+ * LB_EINVAL, as where a launch would have 2^32 threads.  Results are
+ * bit-identical either way; launches are shorter where an instance stops and
+ * for remainders, and advance one step where a plane of the state or of the
+ * sound-speed table exceeds 4 GiB (lb_wave_get_launch_steps tells).
+ * lb_wave_autotune also tries several steps per launch when allowed.
  *
  * In 2D there is no choice to make: handles whose boxes are all driven and at
  * most 128 x 64 or 64 x 128 cells advance up to 64 steps per launch in calls

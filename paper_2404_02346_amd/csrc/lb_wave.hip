@@ -784,8 +784,16 @@ int march_block_waves(const std::vector<InstDev> &inst, int storage)
     return 2 * wide > cells && state_bytes(inst, storage) > kMallBytes ? 8 : 4;
 }
 
+// blocks of a launch: `lattice` blocks, and `meas` measurement blocks of kStepThreads threads side by side
+int64_t march_grid(int64_t lattice, int64_t meas, int waves)
+{
+    const int per = 64 * waves / kStepThreads;
+    return lattice + (meas + per - 1) / per;
+}
+
 // Launches of `steps` lattice steps by blocks of `waves` wavefronts: the chunks of planes and the
-// blocks of every instance.  Returns false if a launch would have too many blocks.
+// blocks of every instance.  Returns false if a launch, with the measurement of as many steps, would
+// have 2^32 threads or more.
 bool plan_march(lb_wave *h, int steps, int waves)
 {
     const int zchunk = march_zchunk(h->hinst, h->storage, steps, waves);
@@ -795,9 +803,11 @@ bool plan_march(lb_wave *h, int steps, int waves)
     for (int ii = 0; ii < h->n; ++ii) {
         boxes[ii] = march_box(h->hinst[ii], h->storage, waves, zchunk);
         total += boxes[ii].blocks();
-        if (total > INT32_MAX / 2) return false;
+        if (total > INT32_MAX) return false;
         blk0[ii + 1] = (int)total;
     }
+    if (march_grid(total, h->n + (int64_t)steps * h->lay.n_sb_total, waves) * 64 * waves > (int64_t)UINT32_MAX)
+        return false;
     h->march_depth = steps;
     h->march_waves = waves;
     for (SegInfo &sg : h->segs) {
@@ -816,8 +826,7 @@ int rule_rows(int storage) { return storage == LB_F32 ? 4 : 2; }
 
 void launch_march(const lb_wave *h, const StepArgs &a, int nst, int meas_blocks, hipStream_t st)
 {
-    const int per = 64 * h->march_waves / kStepThreads;  // measurement blocks side by side
-    const int blocks = (meas_blocks + per - 1) / per + a.ntask;
+    const unsigned blocks = (unsigned)march_grid(a.ntask, meas_blocks, h->march_waves);
     if (blocks > 0)
         hipLaunchKernelGGL(march_fn(h->storage, nst, h->march_waves, h->nt), dim3(blocks),
                            dim3(64 * h->march_waves), 0, st, a);
@@ -1351,7 +1360,9 @@ int lb_wave_create(const lb_wave_desc *descs, int32_t n_inst, void *dev_workspac
         }
         if (h->fused_ok && fits) {
             const int waves = march_block_waves(h->hinst, h->storage);
-            h->march_ok = plan_march(h, march_depth(h->hinst, h->storage, waves), waves);
+            h->march_ok = plan_march(h, march_depth(h->hinst, h->storage, waves), waves) ||
+                          plan_march(h, 2, 4);
+            h->fused_ok = h->march_ok;  // refused, not run one step at a time
         }
     }
 
@@ -1389,7 +1400,7 @@ int lb_wave_set_steps_per_launch(lb_wave *h, int32_t k)
     if (k != 1 && k != 2) return fail(LB_EINVAL, "steps per launch must be 1 or 2");
     if (k == 2 && !h->fused_ok)
         return fail(LB_EINVAL, "several steps per launch need 3D instances with driven x sheets "
-                               "and ny a multiple of the row block");
+                               "and ny a multiple of the row block, few enough for one grid");
     if (k != h->fused) drop_graphs(h);
     h->fused = k;
     return LB_OK;
@@ -1419,7 +1430,7 @@ int lb_wave_set_launch_plan(lb_wave *h, int32_t steps, int32_t waves)
         return fail(LB_EINVAL, "waves must be 4%s", march_eight(h->storage) ? " or 8" : "");
     if (steps == h->march_depth && waves == h->march_waves) return LB_OK;
     drop_graphs(h);
-    if (!plan_march(h, steps, waves)) return fail(LB_EINVAL, "too many blocks");
+    if (!plan_march(h, steps, waves)) return fail(LB_EINVAL, "too many blocks in a launch");
     return LB_OK;
 }
 
@@ -1723,7 +1734,9 @@ int lb_wave_autotune(lb_wave *h, int32_t n_trial, double *best_ms)
     double win = 1e300;
     int st = LB_OK;
     for (Choice &c : cand) {
-        if ((st = apply(c))) return st;
+        st = apply(c);
+        if (st == LB_EINVAL && c.steps > 1) continue;  // too many blocks for one grid
+        if (st) return st;
         const int warm = std::max(2, c.steps);
         // where a trial is long, a first look at three steps or one launch: what is a quarter slower is
         // not looked at again
