@@ -243,7 +243,8 @@ int lb_wave_autotune(lb_wave *h, int32_t n_trial, double *best_ms);
  *
  * In 2D there is no choice to make: handles whose boxes are all driven and at
  * most 128 x 64 or 64 x 128 cells advance up to 64 steps per launch in calls
- * of at least eight steps (and then need no graph), with the same bits. */
+ * of at least eight steps (some twelve; they then need no graph), with the
+ * same bits. */
 int lb_wave_set_steps_per_launch(lb_wave *h, int32_t k);
 int lb_wave_get_steps_per_launch(const lb_wave *h, int32_t *k);
 

@@ -1190,10 +1190,15 @@ __global__ void __launch_bounds__(64 * W, 2) march_kernel(StepArgs a)
 // them, all steps side by side on the other CUs.
 //
 // What bounds it: the instruction rate of one CU (about 110 FP64 instructions and
-// 32 lane moves of a wavefront per step at 128 x 64 cells).  There, in us per step,
-// one box and 32 at once: 1.7 and 1.8 in FP64 (4.0 and 7.0 with a launch per step),
-// 1.2 for one in FP32 (3.9).  Rows instead of columns: 3.1 and 5.0 in FP64.  c^2 of
-// FP64 from LDS: kept in registers, which then spill, 2.3 and 2.6.
+// 32 lane moves of a wavefront per step at 128 x 64 cells).  us per step in a long call, one box and 32
+// at once, with a launch per step in brackets:
+//   boxes that fill their tile of wavefronts and lanes (FULL), FP64: 128 x 64 1.7, 1.8 (4.0, 6.8),
+//   64 x 64 1.1, 1.3 (4.1, 5.6), 64 x 128 2.4, 2.8 (4.1, 7.1); FP32 1.2, 1.3, 0.8, 1.0 and 1.5, 1.8;
+//   others, which mask columns and rows and find the last row's neighbour by hand, FP64: 127 x 63 2.8,
+//   2.9 (4.1, 6.7), 116 x 55 2.6, 2.8 (4.3, 6.0), 100 x 50 2.3, 2.4, 33 x 33 1.1, 1.2; FP32 127 x 63 1.8, 1.9.
+// Rows instead of columns: 3.1 and 5.0 in FP64 (128 x 64).  c^2 of FP64 from LDS: kept in registers,
+// which then spill, 2.3 and 2.6.  A launch costs the box's way in and out, in vectors of a lane's
+// columns: 127 x 63, a call of 8 steps in FP64 50 us, in FP32 35 (69 and 61 column by column).
 // ---------------------------------------------------------------------------
 constexpr int kResidentWaves = 16;
 // configuration CX << 8 | RY (columns of a wavefront, cells of a lane in a column) of a box, 0 if it
@@ -1203,6 +1208,21 @@ __host__ __device__ inline int resident_config(int nx, int ny)
     const int cols = (nx + kResidentWaves - 1) / kResidentWaves;
     const int cx = cols <= 4 ? 4 : 8, ry = ny <= 64 ? 1 : 2;
     return cols <= 8 && ny <= 128 && cx * ry <= 8 ? cx << 8 | ry : 0;
+}
+
+// the first n of the columns v[LO .. LO + N), in stores as wide as they go
+template <typename E, int LO, int N> __device__ inline void store_columns(gptr<E> p, const E *v, int n)
+{
+    if (n >= N) {
+        using U = typename VecT<E, N>::type __attribute__((aligned(sizeof(E))));
+        typename VecT<E, N>::type w;
+#pragma unroll
+        for (int c = 0; c < N; ++c) vset<E, N>(w, c, v[LO + c]);
+        *(gptr<U>)(p + LO) = w;
+    } else if constexpr (N > 1) {
+        store_columns<E, LO, N / 2>(p, v, n);
+        store_columns<E, LO + N / 2, N / 2>(p, v, n - N / 2);
+    }
 }
 
 // FULL: every wavefront owns CX columns and every lane RY cells of each; the other form takes any box
@@ -1215,6 +1235,7 @@ __device__ inline void resident_box(const StepArgs &a, int box, const int64_t t,
     using E = typename T::R;
     using C = typename T::C;
     using V = typename VecT<E, CX>::type;
+    using U = V __attribute__((aligned(sizeof(E) * (FULL ? CX : 1))));
     constexpr int W = kResidentWaves;
     const auto &I = to_const(a.inst)[box];
     const int nx = FULL ? W * CX : I.nx, ny = FULL ? 64 * RY : I.ny, pitch = I.pitch;
@@ -1239,15 +1260,11 @@ __device__ inline void resident_box(const StepArgs &a, int box, const int64_t t,
         const bool in = FULL || y < ny;
 #pragma unroll
         for (int i = 0; i < 5; ++i) {
-            const int64_t at = i * plane + (int64_t)y * pitch + x0;
-            if constexpr (FULL) {
-                const V v = *(gptr<const V>)(src + at);
+            // CX columns from x0 on lie inside the padded row, whatever the share of this wavefront
+            V v = V{};
+            if (in) v = *(gptr<const U>)(src + i * plane + (int64_t)y * pitch + x0);
 #pragma unroll
-                for (int c = 0; c < CX; ++c) q[i][c][r] = T::to_c(vget<E, CX>(v, c));
-            } else {
-#pragma unroll
-                for (int c = 0; c < CX; ++c) q[i][c][r] = in && c < cols ? T::to_c(src[at + c]) : C(0);
-            }
+            for (int c = 0; c < CX; ++c) q[i][c][r] = FULL || c < cols ? T::to_c(vget<E, CX>(v, c)) : C(0);
         }
         const gptr<const C> c2box = to_global<C>(I.c2box);
         const int bb_n0 = I.bb_n[0], by = y - I.bb_lo[1];
@@ -1358,17 +1375,11 @@ __device__ inline void resident_box(const StepArgs &a, int box, const int64_t t,
         const int y = lane + 64 * r;
 #pragma unroll
         for (int i = 0; i < 5; ++i) {
-            const int64_t at = i * plane + (int64_t)y * pitch + x0;
-            if constexpr (FULL) {
-                V v;
+            E v[CX];
 #pragma unroll
-                for (int c = 0; c < CX; ++c) vset<E, CX>(v, c, T::to_r(q[i][c][r]));
-                *(gptr<V>)(dst + at) = v;
-            } else if (y < ny) {
-#pragma unroll
-                for (int c = 0; c < CX; ++c)
-                    if (c < cols) dst[at + c] = T::to_r(q[i][c][r]);
-            }
+            for (int c = 0; c < CX; ++c) v[c] = T::to_r(q[i][c][r]);
+            if (FULL || y < ny)
+                store_columns<E, 0, CX>(dst + i * plane + (int64_t)y * pitch + x0, v, cols);
         }
     }
 }
@@ -1399,14 +1410,20 @@ template <typename S> __global__ void __launch_bounds__(64 * kResidentWaves) res
     __syncthreads();
     const int cx = I.resident >> 8, ry = I.resident & 255;
     const bool full = I.nx == W * cx && I.ny == 64 * ry;
-    if (cx == 8 && full)
-        resident_box<S, 8, 1, true>(a, b, t, bsrc, edges, c2lds, drive);
-    else if (cx == 8)
-        resident_box<S, 8, 1, false>(a, b, t, bsrc, edges, c2lds, drive);
+    auto run = [&](auto columns, auto rows) {
+        constexpr int CX = decltype(columns)::value, RY = decltype(rows)::value;
+        if (full)
+            resident_box<S, CX, RY, true>(a, b, t, bsrc, edges, c2lds, drive);
+        else
+            resident_box<S, CX, RY, false>(a, b, t, bsrc, edges, c2lds, drive);
+    };
+    using std::integral_constant;
+    if (cx == 8)
+        run(integral_constant<int, 8>{}, integral_constant<int, 1>{});
     else if (ry == 2)
-        resident_box<S, 4, 2, false>(a, b, t, bsrc, edges, c2lds, drive);
+        run(integral_constant<int, 4>{}, integral_constant<int, 2>{});
     else
-        resident_box<S, 4, 1, false>(a, b, t, bsrc, edges, c2lds, drive);
+        run(integral_constant<int, 4>{}, integral_constant<int, 1>{});
 }
 
 // Point source (the paper's oscillating point source): after the lattice

@@ -349,12 +349,15 @@ struct Layout {
     std::vector<InstPlan> p;
 };
 
-// The resident kernel takes handles whose boxes are all 2D, driven and small enough: from eight steps
-// on it is the faster one at every size it takes and any number of boxes.  A launch costs the box's
-// way into the registers and back.  128 x 64 cells in FP64, us per step of a call of 1, 4, 8 and 64
-// steps: 28, 8.5, 5.0 and 1.9, with a launch per step 10, 6.5, 5.9 and 4.7; 512 such boxes: 108, 35,
-// 22 and 10, with a launch per step 87, 80, 79 and 78.
-constexpr int kResidentMin = 8;
+// The resident kernel takes handles whose boxes are all 2D, driven and small enough, for calls of at
+// least eight steps: a launch costs the box's way into the registers and back.  us per step of a call
+// of 8, 16 and 64 steps (with a launch per step): FP64 one box of 128 x 64 5.0, 3.3, 1.9 (5.4, 4.7, 4.4),
+// of 64 x 64 3.5, 2.3, 1.3 (5.5, 5.0, 4.6), 512 of 127 x 63 24, 18, 12 (74 each); FP32 127 x 63 4.3, 3.1,
+// 2.0 (5.3, 5.0, 4.5).  FP64 boxes that almost fill their tile mask most of their columns: a few of
+// them pay from twelve steps on (127 x 63 6.3, 4.5, 3.0 against 5.5, 5.0, 4.6; 116 x 55 5.9, 4.2, 2.8
+// against 5.5, 5.1, 4.7; 100 x 50 5.3, 3.8, 2.5 against 5.2, 5.0, 4.5).
+constexpr int kResidentMin = 8, kResidentMinMasked = 12;
+constexpr int kMaskedCells = 5000, kMaskedBoxes = 16;
 // Its moment boxes and partial sums, one for each step of two launches, may take this much: handles of
 // thousands of boxes with large surfaces keep the small workspace of one step per launch.  So do those
 // whose surface blocks, those of all steps in one launch, are more threads than a grid holds.
@@ -370,6 +373,16 @@ int resident_of(const lb_wave_desc &d)
 {
     if (d.dim != 2 || d.xbc != LB_XBC_DRIVEN || d.src_kind != LB_SRC_SHEET) return 0;
     return resident_config(d.nx, d.ny);
+}
+
+int resident_min(const lb_wave_desc *descs, int n)
+{
+    for (int i = 0; i < n && n < kMaskedBoxes && descs[0].storage == LB_F64; ++i) {
+        const int c = resident_of(descs[i]);
+        const bool full = descs[i].nx == kResidentWaves * (c >> 8) && descs[i].ny == 64 * (c & 255);
+        if (!full && descs[i].nx * descs[i].ny > kMaskedCells) return kResidentMinMasked;
+    }
+    return kResidentMin;
 }
 
 Layout plan(const lb_wave_desc *descs, int n)
@@ -484,6 +497,7 @@ struct lb_wave {
     bool fused_ok = false;            // several steps per launch are allowed
     bool march_ok = false;            // every instance fits the march kernel
     bool resident = false;            // long calls run the resident kernel
+    int resident_min = 0;             // ... from this many steps on
     int march_waves = 4;              // wavefronts per block of the march kernel
     int march_depth = 2;              // most steps of its launches
     std::vector<int> blk0;            // internal order, size n + 1: march blocks
@@ -1076,7 +1090,7 @@ int enqueue_steps(lb_wave *h, int64_t left)
         const int most = most_steps(h), nst = std::min(most, std::max(h->graph_chunk, 1));
         const int k = h->graph_chunk / nst * nst;
         int st;
-        if (h->resident && left >= kResidentMin) {
+        if (h->resident && left >= h->resident_min) {
             const int64_t launches = (left + kResidentSteps - 1) / kResidentSteps;
             const int n = (int)((left + launches - 1) / launches);  // equal shares: no short rest
             st = enqueue_step(h, n);
@@ -1183,6 +1197,7 @@ int lb_wave_create(const lb_wave_desc *descs, int32_t n_inst, void *dev_workspac
     h->stream = static_cast<hipStream_t>(hip_stream);
     h->lay = L;
     h->resident = L.resident;
+    if (L.resident) h->resident_min = resident_min(descs, n_inst);
     h->desc.assign(descs, descs + n_inst);
     for (auto &d : h->desc) {  // the host arrays are not kept
         d.c_field = nullptr;
