@@ -302,13 +302,12 @@ def run_batch(problems, storage: str = "f32", autotune: bool = True, stream=None
     tune = None
     if autotune:
         tune = h.autotune(2)
-    else:
-        # untuned, several steps per launch where the boxes allow it: one FP32 box of 251 x 64 x 64
-        # cells takes 11.5 us per step with three and 15.6 with one
-        try:
-            h.set_steps_per_launch(2)
-        except lbwave.LBError:
-            pass
+    elif h.launch_plan()[0] > 1:
+        # untuned, several steps per launch where the boxes allow it: over 150 handles of 20 to 1500 x 16 to
+        # 192 x 12 to 192 cells, 1 to 32 boxes with a surface each, in the four storages, they took 1.0 to
+        # 3.2 times less time than one (FP32, us per step: one box of 251 x 64 x 64 11.4 against 14.6, of
+        # 338 x 32 x 12 6.6 against 7.9; the least gain 132 x 64 x 18 7.8 against 8.0)
+        h.set_steps_per_launch(2)
     h.set_graph(graph)
     n = max(int(p["n_steps"]) for p in problems)
     if graph > 0 and n > 2 * graph:
