@@ -67,10 +67,11 @@ int lb_mlp_get_params(lb_mlp *h, float *host_params);
  * stream. */
 int lb_mlp_forward(lb_mlp *h, const float *dev_x, int32_t B, float *dev_y);
 
-/* The training forward's kernel for B <= max_batch samples, without the
- * backward half; same arguments as lb_mlp_forward.  Both run the same MFMA
- * sequence per output (sums starting at the bias, K in the same 32-wide steps)
- * and the same roundings, so their outputs agree bit for bit.  Asynchronous. */
+/* The training forward for B <= max_batch samples: the forward half of the
+ * training kernel, activations kept in the workspace; same arguments as
+ * lb_mlp_forward.  Both run the same MFMA sequence per output (sums starting
+ * at the bias, K in the same 32-wide steps) and the same roundings, so their
+ * outputs agree bit for bit.  Asynchronous. */
 int lb_mlp_forward_layered(lb_mlp *h, const float *dev_x, int32_t B, float *dev_y);
 
 /* Gradient of the mean squared error L = (1/B) sum (y - t)^2 with respect to

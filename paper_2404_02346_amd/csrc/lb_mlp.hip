@@ -149,7 +149,7 @@ constexpr int kActLd = kHidden + 8;  // LDS row of BF16 activations: 16-byte rea
 
 struct SweepArgs {
     const float *x;         // B x 4
-    const float *target;    // B targets (training), or NULL: forward only
+    const float *target;    // B targets (kTrain)
     int B;
     float inv_b2;           // 2 / B
     const float *p;         // parameters
@@ -193,16 +193,17 @@ struct LayerFrags {
 // samples per block (RT = 2 row tiles) fill 150 CUs at that batch; the column
 // sums below are those of 32 samples, so fewer would change the order of the
 // sums.  One launch replaces nine (five products forward, four back, 7-16 us
-// each).  Without TRAIN it is the forward pass of small batches.
-template <int RT, bool TRAIN>
+// each).  The other modes are the forward pass of small batches, and the training forward alone.
+enum SweepMode { kInfer, kForward, kTrain };  // kForward and kTrain leave the activations in memory
+template <int RT, SweepMode MODE>
 __global__ void __launch_bounds__(64 * kSweepWaves, 2) sweep_kernel(SweepArgs a)
 {
-    static_assert(!TRAIN || RT == kSweepRows / 16, "column sums are those of kSweepRows samples");
+    static_assert(MODE == kInfer || RT == kSweepRows / 16, "column sums are those of kSweepRows samples");
     constexpr int kRows = 16 * RT;
-    constexpr bool train = TRAIN;
+    constexpr bool train = MODE != kInfer, back = MODE == kTrain;
     __shared__ __attribute__((aligned(16))) uint16_t act[kRows][kActLd];
     // pre-activations, [layer][tile][thread], each thread's own
-    __shared__ f32x4 z[TRAIN ? kLayers - 1 : 1][TRAIN ? 2 * RT : 1][TRAIN ? 64 * kSweepWaves : 1];
+    __shared__ f32x4 z[back ? kLayers - 1 : 1][back ? 2 * RT : 1][back ? 64 * kSweepWaves : 1];
     __shared__ __attribute__((aligned(16))) uint16_t w_out[kHidden];
     __shared__ uint16_t d_out[kRows];
     __shared__ float t_out[kRows];
@@ -259,7 +260,7 @@ __global__ void __launch_bounds__(64 * kSweepWaves, 2) sweep_kernel(SweepArgs a)
         for (int i = 0; i < RT; ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                if (train) z[l][2 * i + j][threadIdx.x] = acc[i][j];
+                if (back) z[l][2 * i + j][threadIdx.x] = acc[i][j];
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     g[i][j][v] = m0 + 16 * i + row + v < a.B ? gelu(acc[i][j][v]) : 0.f;
@@ -300,7 +301,7 @@ __global__ void __launch_bounds__(64 * kSweepWaves, 2) sweep_kernel(SweepArgs a)
         f.load(a.pb + hidden_offset(1), a.p + param_offset_b(1), w, lane);
         if (threadIdx.x < kHidden)
             w_out[threadIdx.x] = a.pb[param_offset_w(kLayers - 1) + threadIdx.x];
-        if (train && threadIdx.x < kRows)
+        if (back && threadIdx.x < kRows)
             t_out[threadIdx.x] = m0 + (int)threadIdx.x < a.B ? a.target[m0 + threadIdx.x] : 0.f;
 #pragma unroll
         for (int i = 0; i < RT; ++i)
@@ -317,7 +318,7 @@ __global__ void __launch_bounds__(64 * kSweepWaves, 2) sweep_kernel(SweepArgs a)
         product();
         if (l + 1 < kLayers - 1)
             f.load(a.pb + hidden_offset(l + 1), a.p + hidden_offset(l + 1) + kHidden * kHidden, w, lane);
-        else if (train)
+        else if (back)
             f.load(a.pbT + hidden_offset(l), nullptr, w, lane);  // the way back
         __syncthreads();  // every wavefront has read this layer's input
         activate(l);
@@ -353,7 +354,7 @@ __global__ void __launch_bounds__(64 * kSweepWaves, 2) sweep_kernel(SweepArgs a)
                     d[v] = 0.f;
                     if (m < a.B) {
                         a.y[m] = o[i][v];
-                        if (train) {
+                        if (back) {
                             const float e = o[i][v] - t_out[16 * i + row + v];
                             d[v] = e * a.inv_b2;
                             lsum += (double)e * (double)e;
@@ -361,7 +362,7 @@ __global__ void __launch_bounds__(64 * kSweepWaves, 2) sweep_kernel(SweepArgs a)
                         }
                     }
                 }
-                if (train) {
+                if (back) {
                     const uint32_t lo = to_bf16x2(d[0], d[1]), hi = to_bf16x2(d[2], d[3]);
                     const int r = 16 * i + row;
                     d_out[r] = (uint16_t)lo;
@@ -373,7 +374,7 @@ __global__ void __launch_bounds__(64 * kSweepWaves, 2) sweep_kernel(SweepArgs a)
                 }
             }
         }
-        if (train) {
+        if (back) {
             csum += __shfl_xor(csum, 16);
             csum += __shfl_xor(csum, 32);
             lsum += __shfl_xor(lsum, 16);
@@ -384,12 +385,12 @@ __global__ void __launch_bounds__(64 * kSweepWaves, 2) sweep_kernel(SweepArgs a)
             }
         }
     }
-    if constexpr (TRAIN) {
+    if constexpr (back) {
     __syncthreads();
 
     {
         // delta_4 W_4: K = 1, one 32-wide step whose other k are zero
-        static_assert(!TRAIN || RT == 2);
+        static_assert(RT == 2);
         bf16x8 af[2], bf[2];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
@@ -992,20 +993,21 @@ void sweep_forward(const lb_mlp *h, const float *x, int B, float *y)
     const SweepArgs a = sweep_args(h, x, B, y);
     const dim3 threads(64 * kSweepWaves);
     if (B <= 16 * 256)
-        hipLaunchKernelGGL((sweep_kernel<1, false>), dim3((B + 15) / 16), threads, 0, h->stream, a);
+        hipLaunchKernelGGL((sweep_kernel<1, kInfer>), dim3((B + 15) / 16), threads, 0, h->stream, a);
     else
-        hipLaunchKernelGGL((sweep_kernel<2, false>), dim3((B + 31) / 32), threads, 0, h->stream, a);
+        hipLaunchKernelGGL((sweep_kernel<2, kInfer>), dim3((B + 31) / 32), threads, 0, h->stream, a);
 }
 // Batches up to this size run through the sweep, larger ones through infer_kernel, whose 128
 // samples per block reuse each weight four times as often but take 25 us however few they are
 // (24576 samples: 23.7 us in the sweep, 27.4 in infer_kernel; 32768: 28.7 and 27.6).
 constexpr int kSweepInfer = 24576;
 
-// forward for B samples and back to the errors of every layer
-void sweep_train(const lb_mlp *h, const float *x, int B, const float *t)
+// training forward for B samples (activations to the workspace, outputs to y) and, with targets, back to
+// the errors of every layer
+void sweep_train(const lb_mlp *h, const float *x, int B, const float *t, float *y)
 {
     const Layout &L = h->L;
-    SweepArgs a = sweep_args(h, x, B, h->at<float>(L.y));
+    SweepArgs a = sweep_args(h, x, B, y);
     a.target = t;
     a.inv_b2 = 2.0f / (float)B;
     for (int l = 0; l < kLayers; ++l) {
@@ -1015,7 +1017,11 @@ void sweep_train(const lb_mlp *h, const float *x, int B, const float *t)
     }
     a.lpart = h->at<double>(L.lpart);
     const int blocks = round_up(B, kTile) / kSweepRows;  // the padding rows are written too
-    hipLaunchKernelGGL((sweep_kernel<2, true>), dim3(blocks), dim3(64 * kSweepWaves), 0, h->stream, a);
+    const dim3 threads(64 * kSweepWaves);
+    if (t)
+        hipLaunchKernelGGL((sweep_kernel<2, kTrain>), dim3(blocks), threads, 0, h->stream, a);
+    else
+        hipLaunchKernelGGL((sweep_kernel<2, kForward>), dim3(blocks), threads, 0, h->stream, a);
 }
 
 // weight gradients (chunk sums) of every layer from what the sweep left
@@ -1091,7 +1097,7 @@ int check_adam(float lr, float beta1, float beta2, float eps)
 void adam_step(lb_mlp *h, const float *x, const float *t, int B, float lr, float beta1,
                float beta2, float eps)
 {
-    sweep_train(h, x, B, t);
+    sweep_train(h, x, B, t, h->at<float>(h->L.y));
     wgrad(h, B);
     h->step++;
     FinishArgs f = finish_args(h, B);
@@ -1201,7 +1207,7 @@ int lb_mlp_forward_layered(lb_mlp *h, const float *dev_x, int32_t B, float *dev_
     int st = check_batch(h, B);
     if (st) return st;
     if (!dev_x || !dev_y) return lbw_fail_msg(LB_EINVAL, "NULL argument");
-    sweep_forward(h, dev_x, B, dev_y);
+    sweep_train(h, dev_x, B, nullptr, dev_y);
     MLP_TRY(hipGetLastError());
     return LB_OK;
 }
@@ -1212,7 +1218,7 @@ int lb_mlp_grad(lb_mlp *h, const float *dev_x, const float *dev_t, int32_t B, fl
     int st = check_batch(h, B);
     if (st) return st;
     if (!dev_x || !dev_t || !host_grads) return lbw_fail_msg(LB_EINVAL, "NULL argument");
-    sweep_train(h, dev_x, B, dev_t);
+    sweep_train(h, dev_x, B, dev_t, h->at<float>(h->L.y));
     wgrad(h, B);
     finish(h, finish_args(h, B));
     MLP_TRY(hipGetLastError());
