@@ -113,24 +113,22 @@ def get_variant(h):
     return tuple(h.variant()) + (h.steps_per_launch(),)
 
 
-def kernel_name(storage, v):
+def kernel_name(storage, v, plan):
     if v[3] == 2:
-        return "march_kernel<{},nt={}>".format(storage, min(v[2], 1))
+        return "march_kernel<{},steps={},waves={},nt={}>".format(storage, *plan, min(v[2], 1))
     return "step_kernel<3,{},{},{},{}>".format(storage, *v[:3])
 
 
-def measured_traffic(storage, variant):
-    """HBM bytes per step-kernel launch from the committed counter summary, if current."""
-    name = ("step2_kernel_sphere16_traffic.json" if storage == "f32"
-            else f"step2_kernel_sphere16_{storage}_traffic.json")
-    path = os.path.join(ROOT, "profiles", name)
+def measured_traffic(storage, variant, plan):
+    """HBM bytes per launch from the committed counter summary, if current."""
+    path = os.path.join(ROOT, "profiles", f"march_kernel_sphere16_{storage}_traffic.json")
     try:
         with open(path) as fh:
             d = json.load(fh)
     except OSError:
         return None
-    if (d.get("kernel_source_sha") != kernel_source_sha() or d.get("storage") != storage
-            or tuple(d.get("variant", ())) != tuple(variant)):
+    if (d.get("kernel_source_sha") != kernel_source_sha()
+            or tuple(d.get("variant", ())) != tuple(variant) or tuple(d.get("plan", ())) != tuple(plan)):
         return None
     return d.get("hbm_bytes_per_launch")
 
@@ -517,7 +515,7 @@ def main():
     # once (2 Q s per cell), however many steps the launch advances
     bytes_per_launch = 2 * Q * s * cells
     achieved = bytes_per_launch / (launch_ms * 1e-3) / 1e9
-    traffic = measured_traffic(args.storage, variant)
+    traffic = measured_traffic(args.storage, variant, plan)
 
     # --- copy reference: the same bytes through one read and one write stream ---
     half = bytes_per_launch // 2
@@ -578,7 +576,7 @@ def main():
             "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
             "traffic": traffic,
-            "kernel": kernel_name(args.storage, variant),
+            "kernel": kernel_name(args.storage, variant, plan),
             "kernel_ms": round(launch_ms, 5),
             "steps_per_launch": spl,
             "algorithmic_bytes_per_launch": bytes_per_launch,

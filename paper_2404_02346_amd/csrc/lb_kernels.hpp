@@ -147,7 +147,7 @@ struct AccDev {
 
 // State buffers, read and written in turn by successive launches.  Two, not three indexed by the
 // step: one FP32 sphere of 256 x 128 x 128 (117 MB a buffer) stays inside the 256 MB memory-side
-// cache and takes 24.5 us a step, 29.0 with three.
+// cache (24.5 us a step against 29.0 with three, when a launch advanced two steps).
 constexpr int kNumBuf = 2;
 // Moment boxes and partial sums, indexed by step mod InstDev::slots: a launch writes those of its
 // steps while the ones of the launch before are read, so twice the most steps of a launch, rounded
@@ -221,7 +221,7 @@ struct SegInfo {
 //    store rho1, J1 of each f(s) in the moment box of its slot;
 //  * surface blocks interpolate F(s) for the n_ms steps s = t - meas_off ..
 //    that earlier launches advanced, from their moment boxes, and write one
-//    partial sum per 64 elements into slot s mod 4;
+//    partial sum per 64 elements into the slot of s;
 //  * reducer blocks sum the partials of the n_rs steps t - red_off .. (in
 //    step order, one block per instance) in a fixed order, scale, trace and
 //    accumulate.
@@ -524,14 +524,16 @@ __device__ inline void lattice_task(const StepArgs &a, const int64_t t, const in
 //
 // What bounds it: in FP32 and FP64 the traffic behind the L2, 2 Q s bytes per
 // cell in K steps plus the halo rows that miss the L2 (16 spheres of 256 x 128 x
-// 128 in FP32, blocks of four wavefronts: 3.0 GB read and 1.9 GB written per
-// launch of three steps against 1.9 and 1.9, at 5.8 TB/s; a copy reaches 6.2);
-// in 16-bit storage the instructions of a plane.  Measured against the kernel
-// before it (two steps, every load through registers), us per step: those 16
-// spheres FP32 384 -> 268, FP16 244 -> 181, one sphere 24.5 -> 20, 16 uneven
-// boxes of 64 to 192 cells a side 307 -> 184, four channels of 1000 x 64 x 64
-// 123 -> 82, four spheres in FP64 208 -> 186.  K = 3 is what the register file
-// holds (70 values of the levels, a plane's 56 loads and 28 results of the 256).
+// 128 in FP32, blocks of eight wavefronts: 2.05 GB read and 1.90 GB written per
+// launch of three steps against 1.88 each, at 5.0 TB/s; of four 3.0 GB read; a
+// copy reaches 6.2 TB/s); in 16-bit storage the instructions of a plane (FP16:
+// 2.46 GB against 1.88 at 4.6 TB/s).  Measured against the kernel before it
+// (two steps, every load through registers), us per step: those 16 spheres FP32
+// 384 -> 264, FP16 244 -> 178, one sphere 24.5 -> 18.8, 16 uneven boxes of 64 to
+// 192 cells a side 307 -> 180, four channels of 1000 x 64 x 64 123 -> 80, four
+// spheres in FP64 208 -> 182.  K = 3 is the most that the register file holds
+// (70 values of the levels, a plane's 56 loads and 28 results of the 256); K = 2
+// is the faster one where a block has few planes.
 //
 // The per-cell arithmetic is cell_rule, as in lattice_task, and 16-bit
 // storage rounds every level through the storage type, so the state is
@@ -1572,7 +1574,6 @@ constexpr int kCavHalo = 16;                      // divides 64
 constexpr int kCavOwn = 64 * 4 - 2 * kCavHalo;    // CPL = 4
 constexpr int kCavMaxWaves = (kCavMaxNx + kCavOwn - 1) / kCavOwn;
 
-// the value v of lane k
 template <int CPL, bool MANY>
 __global__ void __launch_bounds__(MANY ? 64 * kCavMaxWaves : 64)
 cavity_kernel(int nx, double c0sq, double omega, double rho_a, double phi, int64_t n_total,

@@ -623,7 +623,7 @@ void launch(const lb_wave *h, const StepArgs &a, int blocks, hipStream_t st)
 }
 
 // The point sources of step t (the lattice launches of step t come first in
-// stream order); two-step launches never run on a handle with point sources.
+// stream order); launches of several steps never run on a handle with point sources.
 template <int DIM, typename S>
 void launch_point_s(const lb_wave *h, const StepArgs &a, hipStream_t st)
 {
@@ -678,9 +678,10 @@ int march_blocks_per_cu(int storage, int steps, int waves)
 // strip makes a block of one row group, which reads (R + 4) / R = 2 times its own rows; 8 make
 // two groups that share their halo rows, 1.5 times.  That pays where the L2 misses of the halo
 // rows are on the critical path, in handles larger than the memory-side cache (16 FP32 spheres of
-// 256 x 128 x 128: 268 us per step against 278; FP64, 4 spheres: 165 against 187); in it, and in
-// 16-bit storage, which is bound by its instructions, two independent blocks hide each other's
-// barriers better (one FP32 sphere: 20.1 against 22.8; 16 in FP16: 178 against 197).
+// 256 x 128 x 128: 266 us per step against 273; FP64, 16 spheres 721 against 756, 4 spheres 182
+// against 186; four FP32 channels of 1000 x 64 x 64 79 against 85); in it, and in 16-bit storage,
+// which is bound by its instructions, independent blocks hide each other's barriers better (one FP32
+// sphere: 18.9 against 20.8; 16 in FP16: 178 against 197).
 constexpr int64_t kMallBytes = 256 << 20;
 int64_t state_bytes(const std::vector<InstDev> &inst, int storage)
 {
@@ -741,8 +742,8 @@ double march_time(const std::vector<InstDev> &inst, int storage, int k, int wave
 
 // The chunk length with the shortest such time; handles of very many blocks, where the ends
 // hardly matter, take long chunks without trying.  Measured against chunks of a fixed 64 planes
-// (FP32, us per step): 16 uneven boxes of 64 to 192 cells a side 198 against 231, four channels of
-// 1000 x 64 x 64 83 against 127, one sphere of 256 x 128 x 128 20 against 45 or more.
+// (FP32, us per step): 16 uneven boxes of 64 to 192 cells a side 180 against 208, four channels of
+// 1000 x 64 x 64 85 against 95, one sphere of 256 x 128 x 128 19 against 74.
 int march_zchunk(const std::vector<InstDev> &inst, int storage, int k, int waves)
 {
     int64_t n = 0;
