@@ -253,8 +253,8 @@ int lb_wave_get_launch_steps(const lb_wave *h, int32_t *k);
 
 /* The launches of several steps: `steps` lattice steps each (2 or 3; 2 in FP64) by blocks of
  * `waves` wavefronts (4 or 8; 4 in 16-bit storage).  A handle starts with the plan that a model of
- * its blocks' schedule prefers, and lb_wave_autotune times all of them.  Every plan gives the same
- * bits.  set does not turn several steps per launch on; LB_EINVAL on a handle that always
+ * its blocks' schedule prefers, and lb_wave_autotune times all of them, and for the fastest how many
+ * planes a block marches through (set takes the model's choice).  Every plan gives the same bits.  set does not turn several steps per launch on; LB_EINVAL on a handle that always
  * runs one step per launch, for which get gives 1 and 0. */
 int lb_wave_set_launch_plan(lb_wave *h, int32_t steps, int32_t waves);
 int lb_wave_get_launch_plan(const lb_wave *h, int32_t *steps, int32_t *waves);

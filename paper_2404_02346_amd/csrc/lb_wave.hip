@@ -500,6 +500,8 @@ struct lb_wave {
     int resident_min = 0;             // ... from this many steps on
     int march_waves = 4;              // wavefronts per block of the march kernel
     int march_depth = 2;              // most steps of its launches
+    int march_chunk = 0;              // most planes of a block
+    int model_chunk[2][2] = {};       // ... by the model, by steps and wavefronts (0: not asked yet)
     std::vector<int> blk0;            // internal order, size n + 1: march blocks
     char *ws = nullptr;
     size_t ws_bytes = 0;
@@ -744,6 +746,7 @@ double march_time(const std::vector<InstDev> &inst, int storage, int k, int wave
 // hardly matter, take long chunks without trying.  Measured against chunks of a fixed 64 planes
 // (FP32, us per step): 16 uneven boxes of 64 to 192 cells a side 180 against 208, four channels of
 // 1000 x 64 x 64 85 against 95, one sphere of 256 x 128 x 128 19 against 74.
+constexpr int kChunks[] = {128, 96, 64, 48, 40, 32, 28, 24, 20, 16, 12, 10, 8, 6, 5, 4, 3, 2, 1};
 int march_zchunk(const std::vector<InstDev> &inst, int storage, int k, int waves)
 {
     int64_t n = 0;
@@ -752,7 +755,10 @@ int march_zchunk(const std::vector<InstDev> &inst, int storage, int k, int waves
     if (n > 8192) return best;
     const int per_cu = march_blocks_per_cu(storage, k, waves);
     double best_time = march_time(inst, storage, k, waves, per_cu, best);
-    for (int zc : {128, 96, 48, 40, 32, 28, 24, 20, 16, 12, 10, 8, 6, 5, 4, 3, 2, 1}) {
+    for (int zc : kChunks) {
+        int64_t blocks = 0;
+        for (const InstDev &I : inst) blocks += march_box(I, storage, waves, zc).blocks();
+        if (blocks > 8192) break;  // and shorter ones, whose halo planes only cost more
         const double time = march_time(inst, storage, k, waves, per_cu, zc);
         if (time < best_time) {
             best_time = time;
@@ -806,12 +812,16 @@ int64_t march_grid(int64_t lattice, int64_t meas, int waves)
     return lattice + (meas + per - 1) / per;
 }
 
-// Launches of `steps` lattice steps by blocks of `waves` wavefronts: the chunks of planes and the
-// blocks of every instance.  Returns false if a launch, with the measurement of as many steps, would
+// Launches of `steps` lattice steps by blocks of `waves` wavefronts: the chunks of planes (of zchunk at
+// most, 0: what the model prefers) and the blocks of every instance.  Returns false if a launch, with the measurement of as many steps, would
 // have 2^32 threads or more.
-bool plan_march(lb_wave *h, int steps, int waves)
+bool plan_march(lb_wave *h, int steps, int waves, int zchunk = 0)
 {
-    const int zchunk = march_zchunk(h->hinst, h->storage, steps, waves);
+    int &model = h->model_chunk[steps - 2][waves / 8];
+    if (!zchunk) {
+        if (!model) model = march_zchunk(h->hinst, h->storage, steps, waves);
+        zchunk = model;
+    }
     std::vector<int> blk0(h->n + 1, 0);
     std::vector<MarchBox> boxes(h->n);
     int64_t total = 0;
@@ -825,6 +835,7 @@ bool plan_march(lb_wave *h, int steps, int waves)
         return false;
     h->march_depth = steps;
     h->march_waves = waves;
+    h->march_chunk = zchunk;
     for (SegInfo &sg : h->segs) {
         sg.blk0 = blk0[sg.first];
         sg.bpi = blk0[sg.first + 1] - blk0[sg.first];
@@ -1444,7 +1455,6 @@ int lb_wave_set_launch_plan(lb_wave *h, int32_t steps, int32_t waves)
         return fail(LB_EINVAL, "steps must lie in 2 .. %d", march_steps(h->storage));
     if (waves != 4 && (waves != 8 || !march_eight(h->storage)))
         return fail(LB_EINVAL, "waves must be 4%s", march_eight(h->storage) ? " or 8" : "");
-    if (steps == h->march_depth && waves == h->march_waves) return LB_OK;
     drop_graphs(h);
     if (!plan_march(h, steps, waves)) return fail(LB_EINVAL, "too many blocks in a launch");
     return LB_OK;
@@ -1721,11 +1731,16 @@ int lb_wave_autotune(lb_wave *h, int32_t n_trial, double *best_ms)
     };
     struct Choice {
         int cells, x_mode, nt, steps, waves;  // waves of a march block, 0: step_kernel
+        int chunk = 0;                        // planes of a march block, 0: what the model prefers
         double ms = 1e300;                    // per step
     };
     auto apply = [&](const Choice &c) -> int {
         int st = lb_wave_set_steps_per_launch(h, c.steps > 1 ? 2 : 1);
-        if (!st && c.steps > 1) st = lb_wave_set_launch_plan(h, c.steps, c.waves);
+        if (!st && c.steps > 1) {
+            st = lb_wave_set_launch_plan(h, c.steps, c.waves);
+            if (!st && c.chunk && c.chunk != h->march_chunk && !plan_march(h, c.steps, c.waves, c.chunk))
+                st = fail(LB_EINVAL, "too many blocks in a launch");
+        }
         return st ? st : lb_wave_set_variant(h, c.cells, c.x_mode, c.nt);
     };
     int64_t life = INT32_MAX;  // steps until the first instance stops
@@ -1767,19 +1782,48 @@ int lb_wave_autotune(lb_wave *h, int32_t n_trial, double *best_ms)
     Choice best = *std::min_element(cand.begin(), cand.end(), faster);
     if (n_plans > 0) {
         Choice plan = *std::min_element(cand.begin(), cand.begin() + n_plans, faster);
-        // short steps of plans that lie within a few percent of each other: the first three again,
-        // over at least 300 us, the least of three runs
-        if (n_trial * best.ms < 2.0) {
+        // Again over at least 200 us, the least of two runs, where steps are short: the first three of
+        // those within 5%, then the winner's chunks of planes a little shorter or longer.
+        const bool brief = n_trial * best.ms < 2.0;
+        auto again = [&](Choice &c) -> int {
+            const int st = apply(c);
+            const double n = std::max((double)n_trial, std::min(96.0, 0.2 / best.ms));
+            return st ? st : time_it(c.steps, whole(n, c.steps), brief ? 2 : 1, &c.ms);
+        };
+        if (brief) {
             std::stable_sort(cand.begin(), cand.end(), faster);
-            cand.resize(3);
-            for (Choice &c : cand) {
-                const int n = whole(std::max((double)n_trial, std::min(96.0, 0.3 / best.ms)), c.steps);
-                if ((st = apply(c)) || (st = time_it(c.steps, n, 3, &c.ms))) return st;
-            }
+            size_t near = 1;
+            while (near < 3 && near < cand.size() && cand[near].ms < 1.05 * cand[0].ms) ++near;
+            cand.resize(near);
+            for (Choice &c : cand)
+                if ((st = again(c))) return st;
             best = *std::min_element(cand.begin(), cand.end(), faster);
-            if (best.steps > 1) plan = best;
-            win = best.ms;
         }
+        if (best.steps > 1) {
+            if ((st = apply(best))) return st;
+            best.chunk = h->march_chunk;
+            const int n_chunks = (int)(sizeof kChunks / sizeof *kChunks);
+            const int here = (int)(std::find(kChunks, kChunks + n_chunks, best.chunk) - kChunks);
+            for (int dir : {1, -1}) {
+                int blocks = h->blk0[h->n];
+                for (int i = here + dir; i >= 0 && i < n_chunks; i += dir) {
+                    Choice c = best;
+                    c.chunk = kChunks[i];
+                    st = apply(c);
+                    if (st == LB_EINVAL) break;  // too many blocks for one grid
+                    if (st) return st;
+                    if (h->blk0[h->n] == blocks) continue;  // the same chunks
+                    blocks = h->blk0[h->n];
+                    if ((st = again(c))) return st;
+                    if (c.ms > 0.995 * best.ms) break;
+                    best = c;
+                }
+                if (best.chunk != kChunks[here]) break;
+                if ((st = apply(best))) return st;
+            }
+            plan = best;
+        }
+        win = best.ms;
         if ((st = apply(plan))) return st;  // kept, also where one step per launch wins
     }
     if ((st = apply(best))) return st;
