@@ -793,9 +793,10 @@ __device__ inline void march_block(const StepArgs &a, const int64_t t, const int
         const int bz = zq - bb_lo[2];
         if (__builtin_expect(bb_any >= 0 && bz >= 0 && bz < bb_n[2], 0)) {
             const gptr<const C> plane_c2 = c2box + bz * c2_plane(bb_n[0], bb_n[1]);
-            // offsets formed in every plane of the box: kept for all rows they overflow the registers
+            // with three steps the offsets are formed in every plane of the box: kept for all rows they
+            // overflow the registers (two steps keep them: 1% faster in 16-bit storage)
             int first = 0;
-            asm("" : "+s"(first) : "s"(bz));
+            if constexpr (K == 3) asm("" : "+s"(first) : "s"(bz));
 #pragma unroll
             for (int j = 0; j < N1; ++j)
                 c[j] = *at(plane_c2, (uint32_t)(xb && bb_y[j] >= 0 ? first + bb_y[j] + bx : n_plane));

@@ -708,8 +708,13 @@ MarchBox march_box(const InstDev &I, int storage, int waves, int zchunk)
 // times as long as one alone (measured: 1.6 from HBM, 1.2 from the memory-side cache); in 16-bit
 // storage, where each waits for its own instructions, two take 1.15 and three 1.3 times as long (FP16,
 // us per step with the chunks that this gives and with those for two: 160^3 20.7 and 27.9,
-// 300 x 96 x 96 16.9 and 20.9, three of 488 x 32 x 32 11.4 and 12.3).
-double march_time(const std::vector<InstDev> &inst, int storage, int k, int waves, int per_cu, int zchunk)
+// 300 x 96 x 96 16.9 and 20.9, three of 488 x 32 x 32 11.4 and 12.3).  Measurement blocks (surf per
+// step, and one per instance) that outnumber the places follow, each a little over an iteration: fewer
+// lattice blocks then leave places free for them (FP16 16 boxes of 64^3 with a surface each 22.1 and
+// 23.8, 24 of 60 x 48 x 48 25.3 and 27.8; FP64 16 of 55 x 64 x 40 43.9 and 48.5).  Not in FP32, where
+// full places are the faster choice all the same (8 boxes of 79 x 64 x 64 23.0 and 28.8).
+double march_time(const std::vector<InstDev> &inst, int storage, int64_t surf, int k, int waves, int per_cu,
+                  int zchunk)
 {
     std::vector<std::pair<int64_t, double>> runs;  // blocks, iterations
     int64_t n = 0;
@@ -720,6 +725,8 @@ double march_time(const std::vector<InstDev> &inst, int storage, int k, int wave
         n += m.blocks();
     }
     const int places = 32 * per_cu;
+    int64_t meas = (k * surf + (int64_t)inst.size()) / (kNumXcd * (waves / 4));
+    if (storage == LB_F32 || meas <= places) meas = 0;
     double worst = 0.0;
     size_t r = 0;
     int64_t used = 0;
@@ -736,6 +743,11 @@ double march_time(const std::vector<InstDev> &inst, int storage, int k, int wave
             last = std::max(last, free_at.back() += runs[r].second);
             std::push_heap(free_at.begin(), free_at.end(), std::greater<double>());
         }
+        for (int64_t m = meas; m > 0; --m) {
+            std::pop_heap(free_at.begin(), free_at.end(), std::greater<double>());
+            last = std::max(last, free_at.back() += 1.2);
+            std::push_heap(free_at.begin(), free_at.end(), std::greater<double>());
+        }
         worst = std::max(worst, last);
     }
     const int64_t share = std::min<int64_t>(per_cu, (n + 255) / 256);
@@ -747,19 +759,19 @@ double march_time(const std::vector<InstDev> &inst, int storage, int k, int wave
 // (FP32, us per step): 16 uneven boxes of 64 to 192 cells a side 180 against 208, four channels of
 // 1000 x 64 x 64 85 against 95, one sphere of 256 x 128 x 128 19 against 74.
 constexpr int kChunks[] = {128, 96, 64, 48, 40, 32, 28, 24, 20, 16, 12, 10, 8, 6, 5, 4, 3, 2, 1};
-int march_zchunk(const std::vector<InstDev> &inst, int storage, int k, int waves)
+int march_zchunk(const std::vector<InstDev> &inst, int storage, int64_t surf, int k, int waves)
 {
     int64_t n = 0;
     for (const InstDev &I : inst) n += march_box(I, storage, waves, 64).blocks();
     int best = 64;
     if (n > 8192) return best;
     const int per_cu = march_blocks_per_cu(storage, k, waves);
-    double best_time = march_time(inst, storage, k, waves, per_cu, best);
+    double best_time = march_time(inst, storage, surf, k, waves, per_cu, best);
     for (int zc : kChunks) {
         int64_t blocks = 0;
         for (const InstDev &I : inst) blocks += march_box(I, storage, waves, zc).blocks();
         if (blocks > 8192) break;  // and shorter ones, whose halo planes only cost more
-        const double time = march_time(inst, storage, k, waves, per_cu, zc);
+        const double time = march_time(inst, storage, surf, k, waves, per_cu, zc);
         if (time < best_time) {
             best_time = time;
             best = zc;
@@ -780,12 +792,12 @@ int march_zchunk(const std::vector<InstDev> &inst, int storage, int k, int waves
 //    FP16 and BF16, two and three: 96^3 10.0 and 11.7, 192^3 27.3 and 32.7, 16 of 64^3 23.7 and 25.6;
 //    beyond the cache 16 of 256 x 128 x 128 (0.85) 214 and 178, 4 of them (0.88) 57 and 51, 8 of 192^3
 //    (0.96) 178 and 201, 512 x 256 x 256 (0.99) 131 and 140.
-int march_depth(const std::vector<InstDev> &inst, int storage, int waves)
+int march_depth(const std::vector<InstDev> &inst, int storage, int64_t surf, int waves)
 {
     if (march_steps(storage) == 2) return 2;
     auto per_step = [&](int k) {
-        return march_time(inst, storage, k, waves, march_blocks_per_cu(storage, k, waves),
-                          march_zchunk(inst, storage, k, waves)) / k;
+        return march_time(inst, storage, surf, k, waves, march_blocks_per_cu(storage, k, waves),
+                          march_zchunk(inst, storage, surf, k, waves)) / k;
     };
     if (storage == LB_F32) return per_step(3) < 0.8 * per_step(2) ? 3 : 2;
     return state_bytes(inst, storage) > kMallBytes && per_step(3) < 0.92 * per_step(2) ? 3 : 2;
@@ -819,7 +831,7 @@ bool plan_march(lb_wave *h, int steps, int waves, int zchunk = 0)
 {
     int &model = h->model_chunk[steps - 2][waves / 8];
     if (!zchunk) {
-        if (!model) model = march_zchunk(h->hinst, h->storage, steps, waves);
+        if (!model) model = march_zchunk(h->hinst, h->storage, h->lay.n_sb_total, steps, waves);
         zchunk = model;
     }
     std::vector<int> blk0(h->n + 1, 0);
@@ -1387,7 +1399,7 @@ int lb_wave_create(const lb_wave_desc *descs, int32_t n_inst, void *dev_workspac
         }
         if (h->fused_ok && fits) {
             const int waves = march_block_waves(h->hinst, h->storage);
-            h->march_ok = plan_march(h, march_depth(h->hinst, h->storage, waves), waves) ||
+            h->march_ok = plan_march(h, march_depth(h->hinst, h->storage, L.n_sb_total, waves), waves) ||
                           plan_march(h, 2, 4);
             h->fused_ok = h->march_ok;  // refused, not run one step at a time
         }
