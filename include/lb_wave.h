@@ -218,7 +218,8 @@ int lb_wave_state_view(const lb_wave *h, int32_t inst, lb_state_view *v);
  * n_trial steps on the handle's own instances (fewer where one is clearly
  * slower, more where the first are close), keeps the fastest, then resets the
  * state (lb_wave_reset).  2D handles that run many steps per launch (see
- * below) use the variant in shorter calls.  best_ms (may be NULL) receives the
+ * below) use the variant in shorter calls only; it is tuned where they hold
+ * more than 2048 tasks of 64 cells, and the first one otherwise.  best_ms (may be NULL) receives the
  * winning time per step of a long call in ms.  set_tile/get_tile change or
  * read cells_per_lane only. */
 int lb_wave_set_variant(lb_wave *h, int32_t cells_per_lane, int32_t x_mode, int32_t nontemporal);

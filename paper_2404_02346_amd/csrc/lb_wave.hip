@@ -546,6 +546,14 @@ struct lb_wave {
 
 namespace {
 
+// wave tasks of one step of all instances, `cells` of a row to a task
+int64_t one_step_tasks(const lb_wave *h, int cells)
+{
+    int64_t n = 0;
+    for (const InstDev &I : h->hinst) n += (int64_t)((I.nx + cells - 1) / cells) * I.ny * I.nz;
+    return n;
+}
+
 // the buffer that holds the current state of an instance
 int state_buf(const lb_wave *h, int internal)
 {
@@ -1771,9 +1779,15 @@ int lb_wave_autotune(lb_wave *h, int32_t n_trial, double *best_ms)
         for (int waves = 4; waves <= (march_eight(h->storage) ? 8 : 4); waves += 4)
             for (int nt = 0; nt <= 1; ++nt) cand.push_back({1, xm_max, nt, steps, waves});
     const size_t n_plans = cand.size();
+    // Only short calls of a handle with a resident kernel use a variant, and up to 2048 wave tasks, two
+    // per SIMD, the first is within 2% of the best (us per step in calls of six, first / best / worst:
+    // FP64 one box of 128 x 64 5.5 / 5.4 / 7.0, 16 boxes 6.9 / 6.8 / 7.9, 32 boxes 8.2 / 7.6 / 9.6): the
+    // trials of the others would take longer than many a run.
+    const bool first_only = h->lay.resident && one_step_tasks(h, 64) <= 2048;
     for (int cpl : {1, 2, 4})
         for (int xm = 0; xm <= xm_max; ++xm)
-            for (int nt = 0; nt <= 2; ++nt) cand.push_back({cpl, xm, nt, 1, 0});
+            for (int nt = 0; nt <= 2; ++nt)
+                if (!first_only || cpl + xm + nt == 1) cand.push_back({cpl, xm, nt, 1, 0});
     double win = 1e300;
     int st = LB_OK;
     for (Choice &c : cand) {
